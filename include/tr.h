@@ -141,8 +141,7 @@ int32_t tr_mode(uint64_t seed, uint64_t step, int32_t N);
  * p(i) = ||G_k(:,i,:)||_F^2 / ||G_k||_F^2).  core_k: G_{k(2)} in the core
  * dtype.  cdf_k: uint64 [I_k], inclusive prefix sums of the weights.
  * Leverage scores are l_i = g_i^T (G^T G)^{-1} g_i with the FP64 Gram
- * G^T G of G = G_{k(2)}, inverted by the blocked FP64 sweep for
- * R_k R_{k+1} <= 128 and through an FP64 Cholesky above.  The rank is
+ * G^T G of G = G_{k(2)}, inverted by the blocked FP64 sweep.  The rank is
  * found on the Gram: when a pivot of that factorisation is at or below
  * 2^-43 of the largest diagonal entry, or when I_k <= R_k R_{k+1}, the
  * scores come from a Cholesky with diagonal pivoting of G^T G stopped at
@@ -222,10 +221,9 @@ size_t tr_gram_workspace_size(const tr_desc* d, int32_t m_H);
 /* ------------------------------------------------------------------ */
 
 /* Direction p = -g (gram == NULL) or p = -g (h + damping I)^{-1} with
- * h = gram (eq:scaledsg_direction and the amended preconditioner): for
- * RR <= 128 the FP64 blocked symmetric sweep forms -(h + damping I)^{-1}
- * and a row-parallel product applies it; for RR > 128 an FP64 Cholesky
- * and two triangular solves.  If h + damping I is not
+ * h = gram (eq:scaledsg_direction and the amended preconditioner): the
+ * FP64 blocked symmetric sweep forms -(h + damping I)^{-1} and a
+ * row-parallel product applies it.  If h + damping I is not
  * positive definite the solve retries with damping + 10^(k-10) tr(h)/RR,
  * k = 0..6 (TR_DEV_DAMPED), else leaves the core unchanged
  * (TR_DEV_NOT_SPD).  Then core_n is updated in place by ``rule`` at step t;
@@ -319,7 +317,7 @@ tr_status tr_run_events(const tr_problem* p, const tr_config* c, uint64_t* t_dev
 /* Options of tr_run_ex (all fields may be NULL).
  *   aux, ev_fork, ev_gram, ev_join: a second stream and three hipEvent_t
  *     handles, created by the caller (default stream priority).  With them
- *     a scaled step (RR <= 128) runs the Gram, its reduction and the
+ *     a scaled step runs the Gram, its reduction and the
  *     inverse (equation eq:scaledsg_direction) on ``aux`` and the gradient
  *     on ``stream``: ev_fork is recorded on ``stream`` after the draws and
  *     waited on by ``aux``; ev_gram is recorded on ``aux`` once the Gram's
@@ -332,7 +330,7 @@ tr_status tr_run_events(const tr_problem* p, const tr_config* c, uint64_t* t_dev
  *     one-stream run.  All four must be set together, or all NULL.
  *   ev_begin, ev_end: as in tr_run_events.
  *   ev_inv_begin, ev_inv_end: the same for the dispatch of the RR x RR
- *     inverse of step i (scaled steps with RR <= 128). */
+ *     inverse of step i (scaled steps). */
 typedef struct {
     tr_stream_t aux;
     void* ev_fork;

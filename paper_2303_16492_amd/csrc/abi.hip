@@ -365,7 +365,8 @@ tr_status tr_update(const tr_desc* d, int32_t n, void* core_n, const void* g, co
     if (gram) {
         const UpdWs L = upd_ws_layout(*d);
         if (!ws || ws_bytes < L.total) return TR_E_WORKSPACE;
-        return hip_status(launch_scaled_update(*d, ms, gram, damping, g, cores, acc, *rule, dev_status, ws, L, st));
+        return hip_status(launch_sweep_update(*d, ms, gram, damping, g, nullptr, cores, acc, *rule, dev_status, ws, L,
+                                              StepBump{}, st));
     }
     return hip_status(launch_plain_update(*d, ms, g, cores, acc, *rule, dev_status, st));
 }
@@ -504,7 +505,7 @@ tr_status tr_run_ex(const tr_problem* p, const tr_config* c, uint64_t* t_dev, in
         // a damping schedule needs t: then the shape-only kernels read it too
         const ModeSrc ms_shape = same_shape ? ModeSrc{sched ? t_dev : nullptr, 0, 0, c->seed} : ms;
         double* loss = loss_out ? loss_out + it : lossw;
-        // Scaled steps (RR <= 128) with a second stream: the Gram, its
+        // Scaled steps with a second stream: the Gram, its
         // reduction and the inverse need only the draws, so they run on
         // ``hs``; the gradient waits for the Gram's group sums (it is not
         // on the critical path) and then runs beside the reduction and the
@@ -513,7 +514,7 @@ tr_status tr_run_ex(const tr_problem* p, const tr_config* c, uint64_t* t_dev, in
         // ``hs`` reads the step's draws: the branch forks before them, and
         // its sample kernel draws the step's mode itself (the same counter,
         // so the same mode) and runs beside the step's own.
-        const bool fork = any_aux && c->scaled && sweep_supported(d);
+        const bool fork = any_aux && c->scaled;
         const bool fork_early = fork && c->m_H > 0 && same_shape;
         hipStream_t hs = fork ? (hipStream_t)o.aux : st;
         if (c->law == TR_LAW_OPTIMAL)
@@ -525,8 +526,7 @@ tr_status tr_run_ex(const tr_problem* p, const tr_config* c, uint64_t* t_dev, in
         if (e == hipSuccess)
             e = launch_sample_subchain(d, ms_draw, c->m, cdf, c->law == TR_LAW_OPTIMAL ? p->cdf_J : nullptr,
                                        TR_STREAM_IDX, cores, idx, pF, S, true, true, st);
-        if (c->scaled && sweep_supported(d)) {
-            const Shape sh = shape_of(d);
+        if (c->scaled) {
             if (e == hipSuccess && fork && !fork_early) {
                 e = hipEventRecord((hipEvent_t)o.ev_fork, st);
                 if (e == hipSuccess) e = hipStreamWaitEvent(hs, (hipEvent_t)o.ev_fork, 0);
@@ -572,31 +572,9 @@ tr_status tr_run_ex(const tr_problem* p, const tr_config* c, uint64_t* t_dev, in
                                  ev_end ? (hipEvent_t)ev_end[it] : nullptr);
                 e = launch_grad_partial(d, ms, cores, xs, idx, S, pF, c->m, c->prec, w + L.grad, L.gl, st);
             }
-            if (e != hipSuccess) break;
-            if (c->scaled) {   // RR > 128: Cholesky path
-                e = launch_grad_reduce(d, ms, w + L.grad, L.gl, g, loss, false, MutPtrs{}, MutPtrs{}, c->rule,
-                                       dev_status, st);
-                if (e == hipSuccess) {
-                    if (c->m_H > 0) {
-                        int32_t* idxH = reinterpret_cast<int32_t*>(w + L.idxH);
-                        double* pH = reinterpret_cast<double*>(w + L.pH);
-                        void* SH = w + L.SH;
-                        e = launch_sample_subchain(d, ms, c->m_H, cdf,
-                                                   c->law == TR_LAW_OPTIMAL ? p->cdf_J : nullptr, TR_STREAM_H, cores,
-                                                   idxH, pH, SH, true, true, st);
-                        if (e == hipSuccess) e = launch_gram(d, ms, SH, pH, c->m_H, gram, w + L.gramws, L.mlH, st);
-                    } else {
-                        e = launch_gram(d, ms, S, pF, c->m, gram, w + L.gramws, L.ml, st);
-                    }
-                }
-                if (e == hipSuccess)
-                    e = launch_scaled_update(d, ms, gram, damp, g, mcores, acc, c->rule, dev_status, w + L.upd,
-                                             L.ul, st);
-                if (e == hipSuccess && fused.t) e = launch_bump(t_dev, st);
-            } else {
+            if (e == hipSuccess)
                 e = launch_grad_reduce(d, ms, w + L.grad, L.gl, nullptr, loss, true, mcores, acc, c->rule,
                                        dev_status, st, fused);
-            }
         }
         if (e == hipSuccess && refresh)   // the law's last kernel also advances the step counter
             e = launch_dist(d, ms, true, 0, c->law, cores, p->cdf, dev_status, w + L.dist, st, t_dev);
@@ -702,8 +680,8 @@ tr_status tr_sweep_run(const tr_problem* p, const tr_sweep_config* c, uint64_t* 
                                        dev_status, st);
                 if (e == hipSuccess) e = launch_gram(d, ms, S, pF, m, gram, w + L.gramws, L.ml, st);
                 if (e == hipSuccess)
-                    e = launch_scaled_update(d, ms, gram, c->damping, g, mcores, acc, rule, dev_status, w + L.upd,
-                                             L.ul, st);
+                    e = launch_sweep_update(d, ms, gram, c->damping, g, nullptr, mcores, acc, rule, dev_status,
+                                            w + L.upd, L.ul, StepBump{}, st);
             }
             if (e == hipSuccess) e = launch_bump(t_dev, st);
             if (e == hipSuccess && refresh)

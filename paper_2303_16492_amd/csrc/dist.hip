@@ -2,12 +2,11 @@
 //
 //   Euclidean (Lemma euc_est): p(i) = ||G_k(:,i,:)||_F^2 / ||G_k||_F^2.
 //   Leverage (Lemma lev_est):  p(i) = l_i(G_{k(2)}) / rank, l_i = g_i^T (G^T G)^{-1} g_i
-//                              with the FP64 Gram G^T G of G = G_{k(2)} (the sweep
-//                              inverse for R_k R_{k+1} <= 128, ||L^{-1} g_i||^2 with
-//                              its Cholesky factor L above); a Gram that is singular
-//                              or close to it, and I_k <= R_k R_{k+1}, take the
-//                              rank-revealing route (pivoted Cholesky, scores on the
-//                              chosen columns, divided by the rank found).
+//                              with the FP64 Gram G^T G of G = G_{k(2)} and its
+//                              sweep inverse; a Gram that is singular or close to
+//                              it, and I_k <= R_k R_{k+1}, take the rank-revealing
+//                              route (pivoted Cholesky, scores on the chosen
+//                              columns, divided by the rank found).
 //   Optimal (eq:optimal_prob): q(j) ~ ||X_[n](:,j) - G_{n(2)} s_j|| * ||s_j||
 //                              over the J_n columns, FP64.
 // Weights w = floor(p 2^40) + 1 and their inclusive prefix sums are exact
@@ -277,103 +276,7 @@ __device__ void leverage_pivoted(const TC* __restrict__ G, int Ik, int RR, doubl
     __syncthreads();
 }
 
-// Leverage law of core k (one block): Gram, Cholesky, row solves.
-template <typename TC>
-__global__ __launch_bounds__(1024) void k_dist_leverage(tr_desc d, ModeSrc ms, int use_mode, int k_fixed,
-                                                        Ptrs cores, MutPtrs cdf_out, int32_t* status,
-                                                        double* __restrict__ A, uint64_t* bump) {
-    uint64_t t;
-    int k = k_fixed;
-    if (use_mode) resolve_mode(ms, d.N, &t, &k);
-    const int Ik = d.I[k];
-    const int RR = d.R[k] * d.R[ring_next(k, d.N)];
-    const TC* G = static_cast<const TC*>(cores.p[k]);
-    uint64_t* w = static_cast<uint64_t*>(cdf_out.p[k]);
-    double* lev = reinterpret_cast<double*>(w);
-    for (int e = threadIdx.x; e < RR * RR; e += blockDim.x) {
-        const int a = e % RR, b = e / RR;
-        double s = 0.0;
-        for (int i = 0; i < Ik; ++i) s += (double)G[(int64_t)i * RR + a] * (double)G[(int64_t)i * RR + b];
-        A[e] = s;
-    }
-    __syncthreads();
-    if (Ik <= RR) {   // the Gram is singular: pivoted; full row rank gives the uniform law
-        leverage_pivoted(G, Ik, RR, A, w, status);
-        finish_cdf(w, w, Ik, bump);
-        return;
-    }
-    __shared__ double dmax[16];
-    double mx = 0.0;
-    for (int c = threadIdx.x; c < RR; c += blockDim.x) mx = fmax(mx, A[c + (int64_t)RR * c]);
-    for (int o = 32; o > 0; o >>= 1) mx = fmax(mx, __shfl_xor(mx, o, 64));
-    if ((threadIdx.x & 63) == 0) dmax[threadIdx.x >> 6] = mx;
-    __syncthreads();
-    mx = 0.0;
-    for (int q = 0; q < (int)(blockDim.x >> 6); ++q) mx = fmax(mx, dmax[q]);
-    const double ptol = kLevTrigger * mx;
-    // Right-looking Cholesky in A (column-major); a pivot at or below ptol
-    // sends the law to the rank-revealing route.
-    __shared__ int bad;
-    if (threadIdx.x == 0) bad = 0;
-    for (int j = 0; j < RR; ++j) {
-        __syncthreads();
-        const double djj = A[j + (int64_t)RR * j];
-        if (!(djj > ptol) || !isfinite(djj)) {
-            if (threadIdx.x == 0) bad = 1;
-            break;
-        }
-        const double ljj = sqrt(djj);
-        __syncthreads();
-        for (int i = j + threadIdx.x; i < RR; i += blockDim.x)
-            A[i + (int64_t)RR * j] = i == j ? ljj : A[i + (int64_t)RR * j] / ljj;
-        __syncthreads();
-        const int wd = RR - j - 1;
-        for (int e = threadIdx.x; e < wd * wd; e += blockDim.x) {
-            const int i = j + 1 + e % wd, c = j + 1 + e / wd;
-            if (c <= i) A[i + (int64_t)RR * c] -= A[i + (int64_t)RR * j] * A[c + (int64_t)RR * j];
-        }
-    }
-    __syncthreads();
-    if (bad) {   // rank deficient (or close to it): the Gram again, then pivoted
-        for (int e = threadIdx.x; e < RR * RR; e += blockDim.x) {
-            const int a = e % RR, b = e / RR;
-            double s = 0.0;
-            for (int i = 0; i < Ik; ++i) s += (double)G[(int64_t)i * RR + a] * (double)G[(int64_t)i * RR + b];
-            A[e] = s;
-        }
-        __syncthreads();
-        leverage_pivoted(G, Ik, RR, A, w, status);
-        finish_cdf(w, w, Ik, bump);
-        return;
-    }
-    // l_i = ||L^{-1} g_i||^2 by forward substitution, one row per thread.
-    for (int i = threadIdx.x; i < Ik; i += blockDim.x) {
-        double z[kMaxRR];
-        double s = 0.0;
-        for (int j = 0; j < RR; ++j) {
-            double v = (double)G[(int64_t)i * RR + j];
-            for (int c = 0; c < j; ++c) v -= A[j + (int64_t)RR * c] * z[c];
-            v /= A[j + (int64_t)RR * j];
-            z[j] = v;
-            s += v * v;
-        }
-        lev[i] = s;
-    }
-    __syncthreads();
-    for (int i = threadIdx.x; i < Ik; i += blockDim.x) w[i] = quantize(lev[i] / (double)RR);
-    __syncthreads();
-    finish_cdf(w, w, Ik, bump);
-}
-
-// The same law for R_k R_{k+1} <= 128 with the factor kept in LDS (one
-// block of 1024 threads): (1) the lower triangle of A = G^T G, rows of G
-// staged through LDS in chunks, every entry summed over i ascending; (2)
-// right-looking Cholesky A = L L^T; (3) L^{-1} in place, column by column
-// from the last (column j below the diagonal is -(1/L_jj) L22^{-1} L(j+1:, j)
-// with L22^{-1} already formed); (4) l_i = ||L^{-1} g_i||^2, the rows of G
-// staged again, each row's RR entries of L^{-1} g_i split over a group of
-// threads and their squares summed by a shuffle reduction.
-// Leverage law for R_k R_{k+1} <= 128 in four launches across the GPU: the
+// Leverage law of core k in four launches across the GPU: the
 // FP64 Gram of G_{k(2)} (the sampled-Gram kernels on the core's own rows),
 // -(G^T G)^{-1} by the one-workgroup sweep, then
 //     l_i = g_i^T (G^T G)^{-1} g_i = -g_i . (g_i (-(G^T G)^{-1}))
@@ -382,11 +285,12 @@ __global__ __launch_bounds__(1024) void k_dist_leverage(tr_desc d, ModeSrc ms, i
 
 constexpr int kLevRows = 16;
 
-// l_i for 16 rows per block: wavefront w owns output columns 16 n.., n = w
-// and w + 4 (K = RR <= 128 in steps of 4), each lane's partial dot products
+// l_i for 16 rows per block: wavefront w owns output columns 16 n.., n = w,
+// w + 4, ... (K = RR <= RB in steps of 4), each lane's partial dot products
 // are added across its 16 lanes, then across the four wavefronts in a fixed
-// order.  Loads at clamped indices, masked afterwards.
-template <typename TC>
+// order.  Loads at clamped indices, masked afterwards; up to RB = 128 both
+// column blocks' loads are in flight together, above it one block's.
+template <typename TC, int RB>
 __global__ __launch_bounds__(256) void k_lev_rows(tr_desc d, ModeSrc ms, int use_mode, int k_fixed, Ptrs cores,
                                                   const double* __restrict__ hm, double* __restrict__ lev) {
     uint64_t t;
@@ -398,46 +302,55 @@ __global__ __launch_bounds__(256) void k_lev_rows(tr_desc d, ModeSrc ms, int use
     if (r0 >= Ik) return;
     const TC* G = static_cast<const TC*>(cores.p[k]);
     const int tid = threadIdx.x, l = tid & 63, lr = l & 15, lk = l >> 4, w = tid >> 6;
-    constexpr int KS = 32;
+    constexpr int KS = RB / 4, U = RB <= 128 ? RB / 64 : 1;
     const int row = r0 + lr, rowc = row < Ik ? row : Ik - 1;
     TC ga[KS];
-    double hb[2][KS];
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) {
         const int kk = 4 * ks + lk, kc = kk < RR ? kk : RR - 1;
-        if (4 * ks < RR) {   // uniform
-            ga[ks] = G[(int64_t)rowc * RR + kc];
-#pragma unroll
-            for (int u = 0; u < 2; ++u) {
-                const int c = 16 * (w + 4 * u) + lr, cc = c < RR ? c : RR - 1;
-                hb[u][ks] = hm[(int64_t)kc * RR + cc];
-            }
-        }
+        ga[ks] = TC(0);
+        if (4 * ks < RR) ga[ks] = G[(int64_t)rowc * RR + kc];   // uniform
     }
-    TC gd[2][4];   // G[r0 + 4 j + lk][c], the entries this lane's outputs pair with
-#pragma unroll
-    for (int u = 0; u < 2; ++u)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int r = r0 + 4 * j + lk, rc = r < Ik ? r : Ik - 1;
-            const int c = 16 * (w + 4 * u) + lr, cc = c < RR ? c : RR - 1;
-            gd[u][j] = G[(int64_t)rc * RR + cc];
-        }
     double part[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll 1
+    for (int u0 = 0; u0 < RB / 64; u0 += U) {
+        if (16 * (w + 4 * u0) >= RR) break;   // uniform
+        double hb[U][KS];
+        TC gd[U][4];   // G[r0 + 4 j + lk][c], the entries this lane's outputs pair with
 #pragma unroll
-    for (int u = 0; u < 2; ++u) {
-        const int c = 16 * (w + 4 * u) + lr;
-        dbl4 acc = {0.0, 0.0, 0.0, 0.0};
+        for (int ks = 0; ks < KS; ++ks) {
+            const int kk = 4 * ks + lk, kc = kk < RR ? kk : RR - 1;
+            if (4 * ks < RR) {   // uniform
 #pragma unroll
-        for (int ks = 0; ks < KS; ++ks)
-            if (4 * ks < RR) {
-                const int kk = 4 * ks + lk;
-                const double a = (row < Ik && kk < RR) ? (double)ga[ks] : 0.0;
-                const double b = (kk < RR && c < RR) ? hb[u][ks] : 0.0;
-                acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, acc, 0, 0, 0);
+                for (int u = 0; u < U; ++u) {
+                    const int c = 16 * (w + 4 * (u0 + u)) + lr, cc = c < RR ? c : RR - 1;
+                    hb[u][ks] = hm[(int64_t)kc * RR + cc];
+                }
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const int r = r0 + 4 * j + lk, rc = r < Ik ? r : Ik - 1;
+                const int c = 16 * (w + 4 * (u0 + u)) + lr, cc = c < RR ? c : RR - 1;
+                gd[u][j] = G[(int64_t)rc * RR + cc];
             }
 #pragma unroll
-        for (int j = 0; j < 4; ++j) part[j] += c < RR ? (double)gd[u][j] * acc[j] : 0.0;
+        for (int u = 0; u < U; ++u) {
+            const int c = 16 * (w + 4 * (u0 + u)) + lr;
+            dbl4 acc = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks)
+                if (4 * ks < RR) {
+                    const int kk = 4 * ks + lk;
+                    const double a = (row < Ik && kk < RR) ? (double)ga[ks] : 0.0;
+                    const double b = (kk < RR && c < RR) ? hb[u][ks] : 0.0;
+                    acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, acc, 0, 0, 0);
+                }
+#pragma unroll
+            for (int j = 0; j < 4; ++j) part[j] += c < RR ? (double)gd[u][j] * acc[j] : 0.0;
+        }
     }
     __shared__ double sp[4][kLevRows];
 #pragma unroll
@@ -503,7 +416,7 @@ size_t dist_ws_bytes(const tr_desc& d, int law) {
     const Shape sh = shape_of(d);
     if (law == TR_LAW_EUCLID) return align_up((size_t)sh.maxI * 8);   // row norms
     if (law != TR_LAW_LEVERAGE) return 256;
-    return sh.maxRR <= 128 ? lev_ws_layout(d).total : align_up((size_t)sh.maxRR * sh.maxRR * 8);
+    return lev_ws_layout(d).total;
 }
 
 hipError_t launch_dist(const tr_desc& d, ModeSrc ms, bool use_mode, int k, int law, Ptrs cores,
@@ -525,7 +438,7 @@ hipError_t launch_dist(const tr_desc& d, ModeSrc ms, bool use_mode, int k, int l
         if (e != hipSuccess) return e;
         hipLaunchKernelGGL(k_euc_cdf, dim3(1), dim3(1024), lds, st, d, ms, (int)use_mode, k, rn, out, status, bump,
                            lds_rows);
-    } else if (law == TR_LAW_LEVERAGE && sh.maxRR <= 128) {
+    } else if (law == TR_LAW_LEVERAGE) {
         // the mode source of the Gram, the inverse and the scores: the step's
         // mode, or core k
         const ModeSrc mk = use_mode ? ms : ModeSrc{nullptr, 0, k, 0};
@@ -547,10 +460,16 @@ hipError_t launch_dist(const tr_desc& d, ModeSrc ms, bool use_mode, int k, int l
         // plus the staged weights stay within 64 KB
         const int lev_lds_rows = sh.maxI <= kLevLdsRows ? sh.maxI : 0;
         const size_t lev_lds = (size_t)lev_lds_rows * 8;
-        if (f64)
-            hipLaunchKernelGGL(k_lev_rows<double>, grid, dim3(256), 0, st, d, ms, (int)use_mode, k, cores, hm, lev);
-        else
-            hipLaunchKernelGGL(k_lev_rows<float>, grid, dim3(256), 0, st, d, ms, (int)use_mode, k, cores, hm, lev);
+#define TRK_LEV_ROWS(TC, RB) \
+    hipLaunchKernelGGL((k_lev_rows<TC, RB>), grid, dim3(256), 0, st, d, ms, (int)use_mode, k, cores, hm, lev)
+        if (f64) {
+            if (sh.maxRR <= 128) TRK_LEV_ROWS(double, 128);
+            else TRK_LEV_ROWS(double, 256);
+        } else {
+            if (sh.maxRR <= 128) TRK_LEV_ROWS(float, 128);
+            else TRK_LEV_ROWS(float, 256);
+        }
+#undef TRK_LEV_ROWS
         if ((e = hipGetLastError()) != hipSuccess) return e;
         if (f64)
             hipLaunchKernelGGL(k_lev_cdf<double>, dim3(1), dim3(1024), lev_lds, st, d, ms, (int)use_mode, k, cores,
@@ -558,14 +477,6 @@ hipError_t launch_dist(const tr_desc& d, ModeSrc ms, bool use_mode, int k, int l
         else
             hipLaunchKernelGGL(k_lev_cdf<float>, dim3(1), dim3(1024), lev_lds, st, d, ms, (int)use_mode, k, cores,
                                gram, lev, flag, out, status, bump, lev_lds_rows);
-    } else if (law == TR_LAW_LEVERAGE) {
-        double* A = static_cast<double*>(ws);
-        if (f64)
-            hipLaunchKernelGGL(k_dist_leverage<double>, dim3(1), dim3(1024), 0, st, d, ms, (int)use_mode, k,
-                               cores, out, status, A, bump);
-        else
-            hipLaunchKernelGGL(k_dist_leverage<float>, dim3(1), dim3(1024), 0, st, d, ms, (int)use_mode, k,
-                               cores, out, status, A, bump);
     } else {
         return hipErrorInvalidValue;
     }

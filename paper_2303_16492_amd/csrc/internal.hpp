@@ -173,16 +173,12 @@ hipError_t launch_gram(const tr_desc& d, ModeSrc ms, const void* S, const double
                        double* gram, void* ws, const GramWs& L, hipStream_t st, hipEvent_t mid = nullptr,
                        Ptrs rows = Ptrs{});
 
-// a7/a8: Cholesky of gram + damping (with fallback) then solve and update.
+// a7/a8: -(gram + damping I)^{-1} by the blocked sweep, then p and the rule
+// (g already reduced).
 struct UpdWs {
-    size_t L_off, dinv_off, flag_off, total;
+    size_t L_off, flag_off, total;
 };
 UpdWs upd_ws_layout(const tr_desc& d);
-hipError_t launch_scaled_update(const tr_desc& d, ModeSrc ms, const double* gram, Damp damping,
-                                const void* g, MutPtrs cores, MutPtrs accum, tr_step rule,
-                                int32_t* status, void* ws, const UpdWs& L, hipStream_t st);
-// The same for RR <= 128 through the blocked sweep (g already reduced).
-bool sweep_supported(const tr_desc& d);
 hipError_t launch_sweep_update(const tr_desc& d, ModeSrc ms, const double* gram, Damp damping, const void* g,
                                double* loss, MutPtrs cores, MutPtrs accum, tr_step rule, int32_t* status, void* ws,
                                const UpdWs& L, StepBump step, hipStream_t st);

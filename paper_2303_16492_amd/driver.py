@@ -83,7 +83,7 @@ class TRSolver:
         self.config = c
         self.ws = api.workspace(api.tr_run_workspace_size(p, c), dev)
         self.rse_ws = None
-        # scaled steps: the Gram/inverse branch on a second stream (RR <= 128)
+        # scaled steps: the Gram/inverse branch on a second stream
         self.opts = None
         if overlap and scaled:
             self.aux = torch.cuda.Stream(device=dev)

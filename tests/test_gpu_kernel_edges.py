@@ -1,0 +1,63 @@
+"""Kernel variants at the edges of their ranges (tiles, remainders, smallest
+and largest sizes), against the oracle."""
+import numpy as np
+import pytest
+import torch
+
+from gpu_util import DEV, TOL, problem, rel, say, unfold
+from oracle import brsgd
+from paper_2303_16492_amd import _lib as L
+from paper_2303_16492_amd import api
+
+pytestmark = pytest.mark.gpu
+
+
+# R_n R_{n+1}: 144 x3; 130, 208, 160; 256, 176, 176; 240, 208, 195; 256, 16, 16;
+# 154, 77, 98 - every slot count of the wide sweep, one partial last pivot
+# block, tile columns far below the widest mode's.
+@pytest.mark.parametrize("R", [[12, 12, 12], [10, 13, 16], [16, 16, 11], [15, 16, 13], [16, 16, 1], [14, 11, 7]])
+@pytest.mark.parametrize("dtype", [torch.float32, torch.float64])
+def test_scaled_update_wide_sweep(R, dtype):
+    I = [2 * max(R) + 5, 2 * max(R) + 4, 2 * max(R) + 3]
+    I, R, cores, X, dcores, dX = problem(23, 3, I, R, dtype)
+    desc = api.make_desc(I, R, dtype)
+    prec = L.TR_PREC_F64 if dtype == torch.float64 else L.TR_PREC_F32
+    for n in range(3):
+        RRn = R[n] * R[(n + 1) % 3]
+        m = 6 * RRn + 17
+        say("wide sweep", R, "mode", n, "RR", RRn, dtype)
+        idx, pF = api.tr_sample(desc, 8, n, n, m)
+        S = api.tr_subchain(desc, n, dcores, idx, m)
+        g, loss, gram = api.tr_grad(desc, n, dcores[n], dX, idx, S, pF, m, prec, want_gram=True)
+        core = dcores[n].clone()
+        st = api.tr_update(desc, n, core, g, gram=gram, rule=api.step_rule("fixed", alpha=0.7), t=0)
+        p, sref = brsgd.scaled_direction(g.double().cpu().numpy(), gram.cpu().numpy())
+        assert int(st) == sref == 0
+        cond = np.linalg.cond(gram.cpu().numpy())
+        assert rel(core.cpu().numpy(), unfold(cores[n]) + 0.7 * p) < max(TOL[dtype], 1e-15 * cond), cond
+
+
+@pytest.mark.parametrize("R", [[12, 12, 12], [16, 16, 16]])
+def test_wide_sweep_damping_ladder(R):
+    """A Gram with an exactly zero row and column: the ladder takes its first
+    rung, as the oracle's does, and a zero Gram leaves the core unchanged."""
+    dtype = torch.float64
+    rr = R[0] * R[1]
+    desc = api.make_desc([40, 30, 30], R, dtype)
+    rng = np.random.default_rng(4)
+    A = rng.standard_normal((3 * rr, rr))
+    A[:, rr // 2] = 0.0
+    h = A.T @ A / (3 * rr)
+    g = rng.standard_normal((40, rr))
+    core0 = rng.standard_normal((40, rr))
+    to = lambda a: torch.from_numpy(a).to(DEV)
+    say("wide ladder", R)
+    core = to(core0).clone()
+    st = int(api.tr_update(desc, 0, core, to(g), gram=to(h), rule=api.step_rule("fixed", alpha=1.0)))
+    p, sref = brsgd.scaled_direction(g, h)
+    assert st == sref == brsgd.DEV_DAMPED
+    hd = h + 1e-10 * np.trace(h) / rr * np.eye(rr)
+    assert rel(core.cpu().numpy(), core0 + p) < 1e-15 * np.linalg.cond(hd)
+    core = to(core0).clone()
+    st = int(api.tr_update(desc, 0, core, to(g), gram=to(0.0 * h), rule=api.step_rule("fixed", alpha=1.0)))
+    assert st == L.TR_DEV_NOT_SPD and np.array_equal(core.cpu().numpy(), core0)
