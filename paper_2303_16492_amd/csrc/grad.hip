@@ -8,160 +8,13 @@
 //
 // Work split: blocks tile (rows of G_{n(2)}) x (groups of sample chunks).
 // A block gathers the X_F tile straight from HBM (one fiber per sample,
-// contiguous when a mode-major replica is given), forms E in LDS and keeps
-// its g rows in registers across its chunks; partial sums per group go to
-// the workspace and are added in a fixed order by the reduce kernel, so
-// results are bitwise reproducible.
+// contiguous when a mode-major replica is given) and keeps its g rows in
+// registers across its chunks; partial sums per group go to the workspace
+// and are added in a fixed order by the reduce kernel, so results are bitwise
+// reproducible.
 #include "internal.hpp"
 
 namespace trk {
-
-namespace {
-
-template <typename TC>
-struct GradCfg;
-template <> struct GradCfg<double> { static constexpr int TI = 32, TF = 32; };
-
-__device__ inline void fiber_strides(const tr_desc& d, int n, bool replica, int64_t* xs) {
-    if (!replica) {
-        for (int k = 0; k < d.N; ++k) xs[k] = d.x_stride[k];
-        return;
-    }
-    int64_t s = d.I[n];
-    xs[n] = 1;
-    int k = n;
-    for (int q = 1; q < d.N; ++q) {
-        k = ring_next(k, d.N);
-        xs[k] = s;
-        s *= d.I[k];
-    }
-}
-
-}  // namespace
-
-template <typename TC, typename TX>
-__global__ __launch_bounds__(256) void k_grad_partial(tr_desc d, ModeSrc ms, Ptrs cores, XSrc xsrc,
-                                                      const int32_t* __restrict__ idx,
-                                                      const TC* __restrict__ S,
-                                                      const double* __restrict__ pF, int m,
-                                                      int groups, int row_tiles_max, int RRp,
-                                                      TC* __restrict__ gpart,
-                                                      double* __restrict__ lpart, int maxIRR) {
-    int rtile, grp;
-    if (!xcd_tile_group(row_tiles_max, groups, rtile, grp)) return;
-    constexpr int TI = GradCfg<TC>::TI, TF = GradCfg<TC>::TF;
-    constexpr int MAXO = TI * kMaxRR / 256;
-    uint64_t t;
-    int n;
-    resolve_mode(ms, d.N, &t, &n);
-    const int N = d.N;
-    const int In = d.I[n];
-    const int RR = d.R[n] * d.R[ring_next(n, N)];
-    const int i0 = rtile * TI;
-    if (i0 >= In) return;
-    const int tid = threadIdx.x;
-
-    extern __shared__ __align__(16) unsigned char smem_raw[];
-    TC* sS = reinterpret_cast<TC*>(smem_raw);       // [TF][RRp]
-    TC* sG = sS + TF * RRp;                         // [TI][RRp]
-    TC* sE = sG + TI * RRp;                         // [TI][TF+1]
-    TC* sW = sE + TI * (TF + 1);                    // [TF]
-    double* sL = reinterpret_cast<double*>(sW + TF + (TF & 1));   // [TF]
-    int64_t* sB = reinterpret_cast<int64_t*>(sL + TF);            // [TF]
-
-    const TC* Gn = static_cast<const TC*>(cores.p[n]);
-    for (int e = tid; e < TI * RRp; e += 256) {
-        const int i = e / RRp, c = e - (e / RRp) * RRp;
-        sG[e] = (i0 + i < In && c < RR) ? Gn[(int64_t)(i0 + i) * RR + c] : TC(0);
-    }
-    const bool rep = xsrc.rep[n] != nullptr;
-    const TX* X = static_cast<const TX*>(rep ? xsrc.rep[n] : xsrc.X);
-    int64_t xs[kMaxOrder];
-    fiber_strides(d, n, rep, xs);
-    const int64_t xsn = xs[n];
-
-    TC acc[MAXO];
-#pragma unroll
-    for (int q = 0; q < MAXO; ++q) acc[q] = TC(0);
-    double lsum = 0.0;
-    const double Jn = (double)J_of(d, n);
-    const double wbase = 1.0 / ((double)m * Jn);
-
-    const int nchunks = (m + TF - 1) / TF;
-    const int cpg = (nchunks + groups - 1) / groups;
-    const int cbeg = grp * cpg, cend = min(nchunks, cbeg + cpg);
-    for (int ch = cbeg; ch < cend; ++ch) {
-        const int f0 = ch * TF;
-        __syncthreads();
-        for (int e = tid; e < TF * RRp; e += 256) {
-            const int f = e / RRp, c = e - (e / RRp) * RRp;
-            sS[e] = (f0 + f < m && c < RR) ? S[(int64_t)(f0 + f) * RR + c] : TC(0);
-        }
-        if (tid < TF) {
-            const int f = f0 + tid;
-            bool ok = f < m;
-            int64_t off = 0;
-            if (ok) {
-                for (int k = 0; k < N; ++k) {
-                    if (k == n) continue;
-                    const int ik = idx[(int64_t)f * N + k];
-                    if (ik < 0 || ik >= d.I[k]) ok = false;
-                    off += (int64_t)ik * xs[k];
-                }
-            }
-            if (ok) {
-                sB[tid] = off;
-                sW[tid] = (TC)(wbase / pF[f]);
-                sL[tid] = 1.0 / (2.0 * (double)m * pF[f]);
-            } else {   // past the end, or an invalid caller index: contributes nothing
-                sB[tid] = 0;
-                sW[tid] = TC(0);
-                sL[tid] = 0.0;
-            }
-        }
-        __syncthreads();
-        // E = X_F - G S^T for the tile, scaled by -w_f into sE.
-        for (int o = tid; o < TI * TF; o += 256) {
-            const int i = o % TI, f = o / TI;
-            TC val = TC(0);
-            if (i0 + i < In && f0 + f < m && sW[f] != TC(0)) {
-                TC dot = TC(0);
-                const TC* gr = sG + i * RRp;
-                const TC* sr = sS + f * RRp;
-                for (int c = 0; c < RR; ++c) dot += gr[c] * sr[c];
-                const TC x = (TC)to_f64(X[sB[f] + (int64_t)(i0 + i) * xsn]);
-                const TC e = x - dot;
-                lsum += (double)e * (double)e * sL[f];
-                val = -e * sW[f];
-            }
-            sE[i * (TF + 1) + f] = val;
-        }
-        __syncthreads();
-#pragma unroll
-        for (int q = 0; q < MAXO; ++q) {
-            const int o = tid + 256 * q;
-            if (o < TI * RR) {
-                const int i = o / RR, c = o - (o / RR) * RR;
-                const TC* er = sE + i * (TF + 1);
-                TC a = acc[q];
-                for (int f = 0; f < TF; ++f) a += er[f] * sS[f * RRp + c];
-                acc[q] = a;
-            }
-        }
-    }
-    TC* out = gpart + (int64_t)grp * maxIRR;
-#pragma unroll
-    for (int q = 0; q < MAXO; ++q) {
-        const int o = tid + 256 * q;
-        if (o < TI * RR) {
-            const int i = o / RR, c = o - (o / RR) * RR;
-            if (i0 + i < In) out[(int64_t)(i0 + i) * RR + c] = acc[q];
-        }
-    }
-    __shared__ double red[4];
-    const double tot = block_sum(lsum, red);
-    if (tid == 0) lpart[(int64_t)grp * row_tiles_max + rtile] = tot;
-}
 
 // Fixed-order sum of the partials; optional plain update G += rule(-g).
 template <typename TC>
@@ -208,8 +61,8 @@ GradWs grad_ws_layout(const tr_desc& d, int m, int prec) {
     GradWs L{};
     const Shape sh = shape_of(d);
     const bool f64 = d.core_dtype == TR_F64;
-    L.ti = f64 ? GradCfg<double>::TI : 64;   // FP32 runs the matrix-core kernel (64-row tiles)
-    L.tf = f64 ? GradCfg<double>::TF : 64;
+    L.ti = f64 ? kGradF64Rows : 64;   // rows of a block
+    L.tf = f64 ? kGradF64Samples : 64;
     L.row_tiles = (sh.maxI + L.ti - 1) / L.ti;
     // about one block per CU (two for FP64): fewer partial slices to add
     // afterwards.  With the XCD-aware order (a group's row tiles on one XCD
@@ -238,20 +91,12 @@ GradWs grad_ws_layout(const tr_desc& d, int m, int prec) {
 hipError_t launch_grad_partial(const tr_desc& d, ModeSrc ms, Ptrs cores, XSrc xs, const int32_t* idx,
                                const void* S, const double* pF, int m, int prec, void* ws,
                                const GradWs& L, hipStream_t st) {
-    const Shape sh = shape_of(d);
-    const int RRp = sh.maxRR | 1;   // odd row pitch: rows of sG/sS fall in different LDS banks
-    const dim3 grid(xcd_grid(L.row_tiles, L.groups));
     char* w = static_cast<char*>(ws);
-    const int maxIRR = sh.maxI * sh.maxRR;
     if (d.core_dtype == TR_F64) {
-        constexpr int TI = GradCfg<double>::TI, TF = GradCfg<double>::TF;
-        const size_t shm = (size_t)(TF * RRp + TI * RRp + TI * (TF + 1) + TF + 1) * 8 + TF * 16;
         if (d.x_dtype != TR_F64) return hipErrorInvalidValue;
-        if (!allow_lds(reinterpret_cast<const void*>(&k_grad_partial<double, double>), shm)) return hipErrorInvalidValue;
-        launch_timed(k_grad_partial<double, double>, grid, dim3(256), shm, st, d, ms, cores, xs, idx,
-                     static_cast<const double*>(S), pF, m, L.groups, L.row_tiles, RRp,
-                     reinterpret_cast<double*>(w + L.gpart_off), reinterpret_cast<double*>(w + L.lpart_off),
-                     maxIRR);
+        return launch_grad_f64(d, ms, cores, xs, idx, static_cast<const double*>(S), pF, m, L.groups, L.row_tiles,
+                               reinterpret_cast<double*>(w + L.gpart_off), reinterpret_cast<double*>(w + L.lpart_off),
+                               st);
     } else if (prec == TR_PREC_BF16 || prec == TR_PREC_F16) {
         return launch_grad_mixed(d, ms, cores, xs, idx, static_cast<const float*>(S), pF, m, prec, L.groups,
                                  L.row_tiles, reinterpret_cast<float*>(w + L.gpart_off),
@@ -261,7 +106,6 @@ hipError_t launch_grad_partial(const tr_desc& d, ModeSrc ms, Ptrs cores, XSrc xs
                                     reinterpret_cast<float*>(w + L.gpart_off), reinterpret_cast<double*>(w + L.lpart_off),
                                     L.tf, st);
     }
-    return hipGetLastError();
 }
 
 hipError_t launch_grad_reduce(const tr_desc& d, ModeSrc ms, const void* ws, const GradWs& L, void* g,

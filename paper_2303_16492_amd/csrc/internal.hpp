@@ -91,6 +91,11 @@ struct GradWs {
     int groups, row_tiles, ti, tf;
 };
 GradWs grad_ws_layout(const tr_desc& d, int m, int prec);
+// FP64: rows of a block and samples of a staged chunk.
+constexpr int kGradF64Rows = 64, kGradF64Samples = 32;
+hipError_t launch_grad_f64(const tr_desc& d, ModeSrc ms, Ptrs cores, XSrc xs, const int32_t* idx, const double* S,
+                           const double* pF, int m, int groups, int row_tiles, double* gp, double* lp,
+                           hipStream_t st);
 // tf: samples per staged chunk (64, or 128 for at most 8 column tiles).
 hipError_t launch_grad_mfma_f32(const tr_desc& d, ModeSrc ms, Ptrs cores, XSrc xs, const int32_t* idx,
                                 const float* S, const double* pF, int m, int groups, int row_tiles, float* gp,

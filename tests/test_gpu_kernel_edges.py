@@ -61,3 +61,26 @@ def test_wide_sweep_damping_ladder(R):
     core = to(core0).clone()
     st = int(api.tr_update(desc, 0, core, to(g), gram=to(0.0 * h), rule=api.step_rule("fixed", alpha=1.0)))
     assert st == L.TR_DEV_NOT_SPD and np.array_equal(core.cpu().numpy(), core0)
+
+
+# rows at the edges of 16-row tiles and 64-row blocks, samples at the edges of
+# 16-sample tiles and 32-sample chunks (and several chunks per group), ranks at
+# the edges of 16-column tiles and of every register width
+@pytest.mark.parametrize("I,R,m", [([1, 16, 17], [4, 4, 4], 31), ([15, 63, 64], [1, 1, 1], 32),
+                                   ([65, 16, 33], [5, 16, 5], 33), ([129, 17, 15], [9, 9, 9], 1),
+                                   ([64, 48, 20], [8, 16, 8], 64), ([20, 70, 18], [13, 10, 16], 97),
+                                   ([400, 12, 9], [3, 5, 2], 3001)])
+def test_grad_fp64_tiles(I, R, m):
+    dtype = torch.float64
+    I, R, cores, X, dcores, dX = problem(33, 3, I, R, dtype)
+    desc = api.make_desc(I, R, dtype)
+    for n in range(3):
+        say("grad f64", I, R, m, "mode", n)
+        idx, pF = api.tr_sample(desc, 4, 1, n, m)
+        S = api.tr_subchain(desc, n, dcores, idx, m)
+        g, loss, _ = api.tr_grad(desc, n, dcores[n], dX, idx, S, pF, m, L.TR_PREC_F64)
+        idn, pFn = idx.cpu().numpy(), pF.cpu().numpy()
+        gref, lref = brsgd.stoch_grad(unfold(cores[n]), S.cpu().numpy(), brsgd.gather_fibers(X, n, idn), pFn,
+                                      brsgd.J_of(I, n))
+        assert rel(g.cpu().numpy(), gref) < TOL[dtype]
+        assert abs(float(loss) - lref) <= TOL[dtype] * abs(lref)
