@@ -62,20 +62,30 @@ GradWs grad_ws_layout(const tr_desc& d, int m, int prec) {
     const Shape sh = shape_of(d);
     const bool f64 = d.core_dtype == TR_F64;
     L.ti = f64 ? kGradF64Rows : 64;   // rows of a block
-    L.tf = f64 ? kGradF64Samples : 64;
+    L.tf = f64 ? kGradF64Samples : kGradF32Samples;
     L.row_tiles = (sh.maxI + L.ti - 1) / L.ti;
-    // about one block per CU (two for FP64): fewer partial slices to add
-    // afterwards.  With the XCD-aware order (a group's row tiles on one XCD
-    // of 32 CUs) a multiple of 8 groups with at most that many blocks per
-    // XCD, so that no XCD takes a second round of blocks.
-    const int per_xcd = f64 ? 64 : 32;
-    int groups = ((f64 ? 512 : 256) + L.row_tiles - 1) / L.row_tiles;
-    if (L.row_tiles <= per_xcd && groups >= 8) groups = 8 * (per_xcd / L.row_tiles);
-    // FP32 with R_n R_{n+1} <= 128: chunks of 128 samples when that still
-    // gives at least half of those blocks
-    if (!f64 && sh.maxRR <= 128 && 2 * ((m + 127) / 128) >= groups) L.tf = 128;
+    // About one block per CU: fewer partial slices to add afterwards.  Two
+    // for FP64, and for FP32 groups of more than one chunk of 128 samples or
+    // of shapes the 16-byte one-chunk form does not serve: there the second
+    // block covers the first one's barriers.  With the XCD-aware order (a
+    // group's row tiles on one XCD of 32 CUs) a multiple of 8 groups with at
+    // most that many blocks per XCD, so that no XCD takes a second round of
+    // blocks.
+    auto groups_for = [&](int per_xcd) {
+        int g = (8 * per_xcd + L.row_tiles - 1) / L.row_tiles;
+        if (L.row_tiles <= per_xcd && g >= 8) g = 8 * (per_xcd / L.row_tiles);
+        return g < 1 ? 1 : g;
+    };
+    int groups = groups_for(f64 ? 64 : 32);
+    if (!f64) {
+        bool wide = sh.maxRR > 32 && sh.maxRR <= 128;
+        for (int k = 0; k < d.N; ++k) wide = wide && (d.R[k] * d.R[ring_next(k, d.N)]) % 4 == 0;
+        if (prec == TR_PREC_F32 && (!wide || (m + 127) / 128 > groups)) groups = groups_for(64);
+        // chunks of 128 samples when that still gives at least half of those
+        // blocks (the streaming FP32 form keeps its chunks of 64)
+        else if (sh.maxRR <= 128 && 2 * ((m + 127) / 128) >= groups) L.tf = 128;
+    }
     const int nchunks = (m + L.tf - 1) / L.tf;
-    groups = groups < 1 ? 1 : groups;
     groups = groups > nchunks ? nchunks : groups;
     const int cpg = (nchunks + groups - 1) / groups;
     L.groups = (nchunks + cpg - 1) / cpg;
@@ -84,7 +94,6 @@ GradWs grad_ws_layout(const tr_desc& d, int m, int prec) {
     L.gpart_off = 0;
     L.lpart_off = align_up((size_t)L.groups * sh.maxI * sh.maxRR * es);
     L.total = L.lpart_off + align_up((size_t)L.groups * L.row_tiles * 8);
-    (void)prec;
     return L;
 }
 
@@ -104,7 +113,7 @@ hipError_t launch_grad_partial(const tr_desc& d, ModeSrc ms, Ptrs cores, XSrc xs
     } else {
         return launch_grad_mfma_f32(d, ms, cores, xs, idx, static_cast<const float*>(S), pF, m, L.groups, L.row_tiles,
                                     reinterpret_cast<float*>(w + L.gpart_off), reinterpret_cast<double*>(w + L.lpart_off),
-                                    L.tf, st);
+                                    st);
     }
 }
 

@@ -96,10 +96,11 @@ constexpr int kGradF64Rows = 64, kGradF64Samples = 32;
 hipError_t launch_grad_f64(const tr_desc& d, ModeSrc ms, Ptrs cores, XSrc xs, const int32_t* idx, const double* S,
                            const double* pF, int m, int groups, int row_tiles, double* gp, double* lp,
                            hipStream_t st);
-// tf: samples per staged chunk (64, or 128 for at most 8 column tiles).
+// FP32: samples of a staged chunk of the streaming form.
+constexpr int kGradF32Samples = 64;
 hipError_t launch_grad_mfma_f32(const tr_desc& d, ModeSrc ms, Ptrs cores, XSrc xs, const int32_t* idx,
                                 const float* S, const double* pF, int m, int groups, int row_tiles, float* gp,
-                                double* lp, int tf, hipStream_t st);
+                                double* lp, hipStream_t st);
 hipError_t launch_grad_mixed(const tr_desc& d, ModeSrc ms, Ptrs cores, XSrc xs, const int32_t* idx, const float* S,
                              const double* pF, int m, int prec, int groups, int row_tiles, float* gp, double* lp,
                              hipStream_t st);

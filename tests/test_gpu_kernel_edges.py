@@ -84,3 +84,30 @@ def test_grad_fp64_tiles(I, R, m):
                                       brsgd.J_of(I, n))
         assert rel(g.cpu().numpy(), gref) < TOL[dtype]
         assert abs(float(loss) - lref) <= TOL[dtype] * abs(lref)
+
+
+# every column-tile count of the streaming FP32 form (R_n R_{n+1} = 16 to 256,
+# with and without whole 16-byte rows), one sample to several chunks of 64 per
+# group (the last one ragged), FP32 and FP16 tensors
+@pytest.mark.parametrize("I,R,m", [([70, 16, 15], [4, 4, 4], 64), ([65, 17, 16], [5, 5, 5], 63),
+                                   ([130, 12, 9], [10, 10, 10], 32001), ([66, 12, 9], [9, 9, 9], 40001),
+                                   ([64, 12, 9], [7, 7, 7], 65), ([63, 20, 9], [11, 11, 11], 1),
+                                   ([450, 20, 9], [8, 6, 7], 9001), ([70, 12, 30], [13, 11, 13], 700),
+                                   ([400, 12, 9], [15, 15, 15], 10007), ([80, 33, 17], [16, 14, 16], 130)])
+@pytest.mark.parametrize("xdt", [torch.float32, torch.float16])
+def test_grad_fp32_streaming(I, R, m, xdt):
+    dtype = torch.float32
+    I, R, cores, X, dcores, dX = problem(34, 3, I, R, dtype)
+    dX = dX.to(xdt)
+    X = dX.double().cpu().numpy().reshape(I, order="F")
+    desc = api.make_desc(I, R, dtype, xdt)
+    for n in range(3):
+        say("grad f32", I, R, m, xdt, "mode", n)
+        idx, pF = api.tr_sample(desc, 4, 1, n, m)
+        S = api.tr_subchain(desc, n, dcores, idx, m)
+        g, loss, _ = api.tr_grad(desc, n, dcores[n], dX, idx, S, pF, m, L.TR_PREC_F32)
+        idn, pFn = idx.cpu().numpy(), pF.cpu().numpy()
+        gref, lref = brsgd.stoch_grad(unfold(cores[n]), S.double().cpu().numpy(), brsgd.gather_fibers(X, n, idn), pFn,
+                                      brsgd.J_of(I, n))
+        assert rel(g.cpu().numpy(), gref) < TOL[dtype]
+        assert abs(float(loss) - lref) <= TOL[dtype] * abs(lref)
