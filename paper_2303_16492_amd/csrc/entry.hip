@@ -1,115 +1,46 @@
 // a10: sampled-entry loss L = 1/(2B) sum_b (Trace(G_0(i_0^b) ... G_{N-1}(i_{N-1}^b)) - x_b)^2
 // and its gradient with respect to every core.
 //
-// Forward: one thread per (entry b, row s of the ring product), the row
-// carried through the N slices in registers; the diagonal entries are
-// summed per entry in LDS.  Only the residuals leave the kernel.
-//
-// Backward: dTrace/dG_k(i_k) = M_{!=k}^T with M_{!=k} = G_{k+1}(i_{k+1}) ...
+// dTrace/dG_k(i_k) = M_{!=k}^T with M_{!=k} = G_{k+1}(i_{k+1}) ...
 // G_{k-1}(i_{k-1}), i.e. the row of G^{!=k}_[2] at entry b (the block
-// gradient of eq:gradient restricted to sampled entries).  Every M_{!=k} is
-// recomputed from the slices (nothing from the forward is kept but the
-// residuals): one thread per (entry, core k, row of M_{!=k}).  Contributions
-// of a block's entries are added in entry order into a block-private slice of
-// the workspace, each gradient position owned by one thread; two more
-// kernels add the block slices in a fixed order.  No float atomics: results
-// are bitwise reproducible.
+// gradient of eq:gradient restricted to sampled entries).
+//
+// Slice products run on the matrix cores (v_mfma_f32_16x16x4_f32) in
+// transposed form: with T = S_1 ... S_q, T^T sits in the result layout (lane
+// l, entry j: row 4 (l / 16) + j, column l % 16), which is also the B operand
+// of the next product T^T <- S^T T^T when K step j takes k = 4 (l / 16) + j,
+// and the A operand of that step is S(4 (l / 16) + j, l % 16): four
+// consecutive entries of the stored slice.  So a chain of slices never leaves
+// the registers and needs no LDS.  Slices of ranks <= 8 (<= 4) are packed as
+// 2 (4) diagonal blocks of one 16 x 16 operand, one entry each.
+//
+// Forward: one wavefront per pack of entries; the trace is the sum of
+// T^T S over the last slice.  Only the residuals leave the kernel.
+//
+// Backward: a workgroup owns the gradient slice of one (core, index).  Each of
+// its wavefronts scans its share of the batch's indices of that mode, compacts
+// the entries that fall on the slice into an LDS list in entry order, forms
+// their M_{!=k} and adds r M_{!=k} by accumulating the chain's last product;
+// the wavefronts' sums are added in a fixed order.  No float atomics: results
+// are bitwise reproducible.  (One 4-byte compare per entry and slice is far
+// cheaper than private gradient slices per workgroup, whose zeroing, scattered
+// read-modify-writes and reduction took most of the time, or than a stable
+// sort by index, a serial 26 us per call at B 8192.)
+//
+// Bound: a chain of dependent memory round trips (indices of the mode, list to
+// entry, entry to slices) and instruction issue (operand addresses, masks); the
+// products are a few percent.  Measured: order 5, 32 per mode, ranks 8, B 8192:
+// forward 13.4 -> 7.3 us (one thread per row of the ring product before),
+// backward 40 -> 25 us (private slices); completion, 301 x 250 x 127, ranks
+// 10/9/7, B 16384: 35 -> 10 us and 100 -> 30 us, a whole step 169 -> 47 us.
 #include <algorithm>
+#include <type_traits>
 
 #include "internal.hpp"
 
 namespace trk {
 
 constexpr int kEntBlock = 256;
-
-// Row ``s`` of A_{k0} A_{k0+1} ... (``len`` slices cyclically from k0) for
-// entry idx.  RM bounds every rank (loops have fixed trip counts); slice
-// entries are loaded at clamped in-bounds indices and the products masked
-// afterwards, so no load waits behind a branch and a slice's loads are all
-// in flight together.  v[c] = 0 for c >= the row's length.
-template <int RM>
-__device__ inline void chain_row(const tr_desc& d, const Ptrs& cores, const int32_t* ik, int k0, int len, int s,
-                                 float* v) {
-    const int N = d.N;
-    int k = k0;
-    {
-        const int Rk = d.R[k], Rk1 = d.R[ring_next(k, N)];
-        const float* A = static_cast<const float*>(cores.p[k]) + (int64_t)ik[k] * Rk * Rk1;
-#pragma unroll
-        for (int c = 0; c < RM; ++c) {
-            const float a = A[s + Rk * (c < Rk1 ? c : Rk1 - 1)];
-            v[c] = c < Rk1 ? a : 0.f;
-        }
-    }
-    for (int q = 1; q < len; ++q) {
-        k = ring_next(k, N);
-        const int Rk = d.R[k], Rk1 = d.R[ring_next(k, N)];
-        const float* A = static_cast<const float*>(cores.p[k]) + (int64_t)ik[k] * Rk * Rk1;
-        float w[RM];
-#pragma unroll
-        for (int c = 0; c < RM; ++c) {
-            const float* col = A + Rk * (c < Rk1 ? c : Rk1 - 1);
-            float a[RM];
-#pragma unroll
-            for (int r = 0; r < RM; ++r) a[r] = col[r < Rk ? r : Rk - 1];
-            float acc = 0.f;
-#pragma unroll
-            for (int r = 0; r < RM; ++r) acc += r < Rk ? v[r] * a[r] : 0.f;
-            w[c] = c < Rk1 ? acc : 0.f;
-        }
-#pragma unroll
-        for (int c = 0; c < RM; ++c) v[c] = w[c];
-    }
-}
-
-// Rank bound of the entry kernels: the largest R_k rounded up to 4, 8, 12 or 16.
-static inline int rank_bound(const tr_desc& d) {
-    int mr = 0;
-    for (int k = 0; k < d.N; ++k) mr = d.R[k] > mr ? d.R[k] : mr;
-    return mr <= 4 ? 4 : (mr <= 8 ? 8 : (mr <= 12 ? 12 : 16));
-}
-
-template <typename TX, int RM>
-__global__ __launch_bounds__(kEntBlock) void k_entry_fwd(tr_desc d, Ptrs cores, const int32_t* __restrict__ idx,
-                                                         const TX* __restrict__ x, int B, float* __restrict__ resid,
-                                                         double* __restrict__ part) {
-    const int N = d.N, R0 = d.R[0];
-    const int per = kEntBlock / R0;
-    const int lb = threadIdx.x / R0, s = threadIdx.x % R0;
-    const int64_t b = (int64_t)blockIdx.x * per + lb;
-    __shared__ float diag[kEntBlock];
-    float mine = 0.f;
-    if (lb < per && b < B) {
-        int ik[kMaxOrder];
-        bool ok = true;
-        for (int k = 0; k < N; ++k) {
-            ik[k] = idx[b * N + k];
-            if (ik[k] < 0 || ik[k] >= d.I[k]) ok = false;
-        }
-        if (ok) {
-            float v[RM];
-            chain_row<RM>(d, cores, ik, 0, N, s, v);
-#pragma unroll
-            for (int c = 0; c < RM; ++c)
-                if (c == s) mine = v[c];
-        } else {
-            mine = NAN;   // invalid caller index
-        }
-    }
-    diag[threadIdx.x] = mine;
-    __syncthreads();
-    double sq = 0.0;
-    if (s == 0 && lb < per && b < B) {
-        float tr_ = 0.f;
-        for (int q = 0; q < R0; ++q) tr_ += diag[threadIdx.x + q];
-        const float r = tr_ - (float)to_f64(x[b]);
-        resid[b] = r;
-        sq = (double)r * (double)r;
-    }
-    __shared__ double red[kEntBlock / 64];
-    const double tot = block_sum(sq, red);
-    if (threadIdx.x == 0) part[blockIdx.x] = tot;
-}
 
 // loss = 1/(2B) sum of the forward's block partials: strided per thread in
 // block order, then the block tree (a fixed order).
@@ -121,215 +52,381 @@ __global__ __launch_bounds__(256) void k_entry_loss(const double* __restrict__ p
     if (threadIdx.x == 0) *loss = s / (2.0 * (double)B);
 }
 
-// LDS layout of the backward: every slice zero-padded to RM x RM (entry
-// (r, c) at r + RM c) and followed by one float of padding, the entry stride
-// odd, so that the slices of one entry and the entries of a chunk start in
-// different LDS banks.
-template <int RM>
-struct EntLds {
-    static constexpr int SS = RM * RM + 1;
-    __host__ __device__ static int es(int N) { return (N * SS) | 1; }
+// ------------------------------------------------ matrix-core entry kernels --
+
+typedef float ef4 __attribute__((ext_vector_type(4)));
+
+// A lane's place in a 16 x 16 operand of 16 / RB diagonal RB x RB blocks:
+// block p (off-diagonal lanes: on = false, zeros), rows row4 .. row4 + 3 and
+// column col inside the block.
+template <int RB>
+struct EntLane {
+    int p, row4, col;
+    bool on;
+    __device__ __forceinline__ EntLane() {
+        const int l = threadIdx.x & 63, lr = l & 15, lk = l >> 4;
+        p = lr / RB;
+        on = p == 4 * lk / RB;
+        row4 = (4 * lk) % RB;
+        col = lr % RB;
+    }
 };
 
-// Backward, phase 1: per block of EPB entries, in slabs of PF entries whose
-// indices and scaled residuals are read once, and chunks of SB entries:
-// (i) the chunk's slices are staged in LDS (padded as above; an entry with an
-// invalid index is staged from row 0 and skipped); (ii) one thread per
-// (entry, core k, row s of M_{!=k}) carries the row through the N-1 other
-// slices at fixed offsets (the zero padding keeps the products exact for any
-// ranks <= RM) and writes resid * row into the chunk's contributions, laid
-// out like the slices; (iii) one thread per gradient position (k, a, b) adds
-// the chunk's contributions to the block's private gradient slice in entry
-// order.  SLICE_LDS: the slice is accumulated in LDS and written out once;
-// the order of the additions, hence the result, is the same either way.
-template <bool SLICE_LDS, int RM>
-__global__ __launch_bounds__(1024) void k_entry_bwd_acc(tr_desc d, Ptrs cores, const int32_t* __restrict__ idx,
-                                                        const float* __restrict__ resid, int B, int EPB, int SB,
-                                                        int PF, float scale, const double* __restrict__ dscale,
-                                                        float* __restrict__ gpart, int64_t slice_len) {
-    constexpr int SS = EntLds<RM>::SS, RM2 = RM * RM;
-    const int N = d.N, ES = EntLds<RM>::es(N), BT = blockDim.x, tid = threadIdx.x;
-    extern __shared__ __align__(16) unsigned char smem_raw[];
-    float* sl = reinterpret_cast<float*>(smem_raw);              // [SB][ES] staged slices
-    float* cb = sl + (size_t)SB * ES;                             // [SB][ES] contributions
-    int* sidx = reinterpret_cast<int*>(cb + (size_t)SB * ES);     // [PF][N]; first index -1: entry skipped
-    float* sres = reinterpret_cast<float*>(sidx + PF * N);        // [PF] scaled residuals
-    float* Gout = gpart + (int64_t)blockIdx.x * slice_len;
-    float* G = SLICE_LDS ? sres + PF : Gout;                      // [slice_len]
-    for (int64_t e = tid; e < slice_len; e += BT) G[e] = 0.f;
-    // dL/dG_k of L = 1/(2B) sum r^2: the 1/B of the mean applied here
-    const float sc = (float)((double)scale * (dscale ? *dscale : 1.0) / (double)B);
-    const int64_t b0 = (int64_t)blockIdx.x * EPB;
-    const int64_t b1 = min((int64_t)B, b0 + EPB);
-    for (int64_t ps = b0; ps < b1; ps += PF) {
-        const int np = (int)min((int64_t)PF, b1 - ps);
-        __syncthreads();   // the previous slab is done with sidx and sres
-        for (int lb = tid; lb < np; lb += BT) {
-            bool ok = true;
-            for (int k = 0; k < N; ++k) {
-                const int v = idx[(ps + lb) * N + k];
-                ok = ok && v >= 0 && v < d.I[k];
-                sidx[lb * N + k] = v;
+// Byte offsets inside a slice of the four entries a lane loads, and their
+// masks, for the slices of a chain of ``len`` cores from k0 (len <= NM): the
+// first slice transposed, S(col, row4 + j), the others S(row4 + j, col).
+// Offsets are clamped into the slice; VEC: whole 16-byte pieces, R_k a
+// multiple of 4 (only the first offset is used).
+template <int NM, bool VEC>
+struct EntSlots {
+    uint32_t lo[NM][4], mk[NM][4];
+    int len;
+    template <int RB>
+    __device__ __forceinline__ EntSlots(const tr_desc& d, int k0, int n, const EntLane<RB>& L) : len(n) {
+        int k = k0;
+#pragma unroll
+        for (int q = 0; q < NM; ++q) {
+            if (q >= n) break;
+            const int Rk = d.R[k], Rk1 = d.R[ring_next(k, d.N)];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const int r = q == 0 ? L.col : L.row4 + j, c = q == 0 ? L.row4 + j : L.col;
+                mk[q][j] = L.on && r < Rk && c < Rk1 ? ~0u : 0u;
+                const int rc = r < Rk ? r : (VEC && q > 0 ? 0 : Rk - 1), cc = c < Rk1 ? c : Rk1 - 1;
+                lo[q][j] = 4u * (uint32_t)(rc + Rk * cc);
             }
-            if (!ok) sidx[lb * N] = -1;
-            sres[lb] = resid[ps + lb] * sc;
+            k = ring_next(k, d.N);
         }
-        for (int cs = 0; cs < np; cs += SB) {
-            const int nb = min(SB, np - cs);
-            const int* cidx = sidx + cs * N;
-            __syncthreads();   // indices ready; the previous chunk is done with sl and cb
-            // (i) staging: eight loads per thread issued together per pass, at
-            // clamped positions, then stored
-            constexpr int kStagePer = 8;
-            const int tot = nb * N * RM2;
-            for (int e0 = 0; e0 < tot; e0 += kStagePer * BT) {
-                float v[kStagePer];
-                int so[kStagePer];
+    }
+    // the lane's entries of slice q of the chain, the slice at byte ``off`` of its core
+    template <typename OT>
+    __device__ __forceinline__ ef4 load(const void* __restrict__ core, OT off, int q) const {
+        const char* A = static_cast<const char*>(core);
+        if (VEC && q > 0) {
+            const float4 v = *reinterpret_cast<const float4*>(A + (OT)(off + lo[q][0]));
+            return ef4{v.x, v.y, v.z, v.w};
+        }
+        ef4 v;
 #pragma unroll
-                for (int u = 0; u < kStagePer; ++u) {
-                    const int e = e0 + u * BT + tid;
-                    const int ec = e < tot ? e : tot - 1;
-                    const int lb = ec / (N * RM2), rem = ec - lb * (N * RM2);
-                    const int kk = rem / RM2, q = rem - kk * RM2, r = q % RM, c = q / RM;
-                    const int Rk = d.R[kk], Rk1 = d.R[ring_next(kk, N)];
-                    const bool in = cidx[lb * N] >= 0 && r < Rk && c < Rk1;
-                    const gptr<float> src = lane_pick_global<float>(cores.p, kk);   // kk may differ across lanes
-                    const float a = src[in ? (int64_t)cidx[lb * N + kk] * Rk * Rk1 + r + Rk * c : 0];
-                    v[u] = in ? a : 0.f;
-                    so[u] = lb * ES + kk * SS + q;
+        for (int j = 0; j < 4; ++j) v[j] = *reinterpret_cast<const float*>(A + (OT)(off + lo[q][j]));
+        return v;
+    }
+    // exact zeros outside the slice (an infinity or NaN of one packed entry
+    // stays its own)
+    template <bool ALSO = false>
+    __device__ __forceinline__ ef4 mask(ef4 v, int q, uint32_t also = ~0u) const {
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            v[j] = __uint_as_float(__float_as_uint(v[j]) & (ALSO ? mk[q][j] & also : mk[q][j]));
+        return v;
+    }
+};
+// T^T (c, r) of a product whose last slice has Rc columns and first slice R0
+// rows: exact zeros outside.
+__device__ __forceinline__ ef4 ent_mask(ef4 v, bool in, int row4, int rows) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) v[j] = __uint_as_float(__float_as_uint(v[j]) & (in && row4 + j < rows ? ~0u : 0u));
+    return v;
+}
+__device__ __forceinline__ ef4 ent_mul(const ef4& a, const ef4& t, ef4 acc) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[j], t[j], acc, 0, 0, 0);
+    return acc;
+}
+
+// Packs whose slices a wavefront has in flight together: a pack's chain is a
+// few hundred cycles of products behind a memory round trip of several times
+// that (32 registers of slices).
+constexpr int ent_packs(int NM) { return NM <= 3 ? 4 : (NM <= 5 ? 2 : 1); }
+
+// ``iters`` rounds of ent_packs packs per wavefront; NM bounds the order, OT
+// holds a byte offset into any core.
+template <typename TX, int RB, bool VEC, int NM, typename OT>
+__global__ __launch_bounds__(kEntBlock, NM <= 5 ? 4 : 2) void k_entry_fwd(tr_desc d, Ptrs cores,
+                                                                         const int32_t* __restrict__ idx,
+                                                                         const TX* __restrict__ x, int B, int iters,
+                                                                         float* __restrict__ resid,
+                                                                         double* __restrict__ part) {
+    constexpr int P = 16 / RB, U = ent_packs(NM);
+    const EntLane<RB> L;
+    const int N = d.N, wv = threadIdx.x >> 6;
+    const EntSlots<NM, VEC> sl(d, 0, N, L);
+    const bool in0 = L.on && L.col < d.R[0];
+    double sq = 0.0;
+#pragma unroll 1
+    for (int it = 0; it < iters; ++it) {
+        const int64_t b0 = (((int64_t)blockIdx.x * iters + it) * (kEntBlock / 64) + wv) * (P * U) + L.p;
+        int ik[U][NM];
+        float xb[U];
+        bool ok[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int64_t b = b0 + P * u, bc = b < B ? b : B - 1;
+#pragma unroll
+            for (int k = 0; k < NM; ++k)
+                if (k < N) ik[u][k] = idx[bc * N + k];
+            xb[u] = (float)to_f64(x[bc]);
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            ok[u] = true;
+#pragma unroll
+            for (int k = 0; k < NM; ++k)
+                if (k < N) ok[u] = ok[u] && ik[u][k] >= 0 && ik[u][k] < d.I[k];
+        }
+        ef4 v[U][NM];
+#pragma unroll
+        for (int k = 0; k < NM; ++k) {
+            if (k >= N) break;
+            const int RR = d.R[k] * d.R[ring_next(k, N)];
+#pragma unroll
+            for (int u = 0; u < U; ++u) v[u][k] = sl.load(cores.p[k], ok[u] ? (OT)ik[u][k] * (OT)(4 * RR) : (OT)0, k);
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            ef4 T = sl.mask(v[u][0], 0);
+            float tr = 0.f;
+#pragma unroll
+            for (int k = 1; k < NM; ++k) {
+                if (k >= N) break;
+                const ef4 a = sl.mask(v[u][k], k);
+                if (k + 1 < N) {
+                    T = ent_mask(ent_mul(a, T, ef4{0.f, 0.f, 0.f, 0.f}), in0, L.row4, d.R[ring_next(k, N)]);
+                } else {
+                    // Trace(T S) = sum over (r, c) of T(r, c) S(c, r) = T^T(c, r) S(c, r)
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) tr += T[j] * a[j];
                 }
-#pragma unroll
-                for (int u = 0; u < kStagePer; ++u)
-                    if (e0 + u * BT + tid < tot) sl[so[u]] = v[u];
             }
-            __syncthreads();
-            // (ii) contributions
-            const int tc = nb * N * RM;
-            for (int e = tid; e < tc; e += BT) {
-                const int lb = e / (N * RM), rem = e - lb * (N * RM), k = rem / RM, s = rem - k * RM;
-                const int k0 = ring_next(k, N);
-                if (s >= d.R[k0] || cidx[lb * N] < 0) continue;
-                const float* base = sl + lb * ES;
-                float v[RM];
-                {
-                    const float* A = base + k0 * SS + s;
+            // the lanes of one block, in a fixed order
+            tr = L.on ? tr : 0.f;
 #pragma unroll
-                    for (int c = 0; c < RM; ++c) v[c] = A[RM * c];
+            for (int o = 1; o < RB; o <<= 1) tr += __shfl_xor(tr, o, 64);
+            if constexpr (RB >= 8) tr += __shfl_xor(tr, 16, 64);
+            if constexpr (RB == 16) tr += __shfl_xor(tr, 32, 64);
+            const int64_t b = b0 + P * u;
+            if (L.on && L.row4 == 0 && L.col == 0 && b < B) {
+                const float r = ok[u] ? tr - xb[u] : NAN;   // NaN: invalid caller index
+                resid[b] = r;
+                sq += (double)r * (double)r;
+            }
+        }
+    }
+    __shared__ double red[kEntBlock / 64];
+    const double tot = block_sum(sq, red);
+    if (threadIdx.x == 0) part[blockIdx.x] = tot;
+}
+
+// First workgroup of each mode in the backward's grid.
+struct EntGroups {
+    int64_t base[kMaxOrder + 1];
+};
+constexpr int kBwdWaves = 16;     // at most
+constexpr int64_t kBwdGrid = 1 << 22;
+// Entries of a wavefront's share scanned into its list at a time: at most
+// 4096, at least 512 (a 16 x 16 partial tile fits the list's 2-byte places).
+constexpr int kBwdWindow = 4096, kBwdWindowMin = 512;
+
+// Gradient slice (k, i), number base[k] + i (see the top of the file), one per
+// workgroup up to a grid of kBwdGrid.  An entry with an invalid index in another mode contributes nothing.
+template <int RB, bool VEC, int NM, typename OT>
+__global__ __launch_bounds__(64 * kBwdWaves) void k_entry_bwd(tr_desc d, Ptrs cores, const int32_t* __restrict__ idx,
+                                                              const float* __restrict__ resid, int B, float scale,
+                                                              const double* __restrict__ dscale, EntGroups gr,
+                                                              int window, ModeSrc only, int block, MutPtrs grads) {
+    constexpr int P = 16 / RB, U = ent_packs(NM), KI = 16;
+    extern __shared__ __align__(16) unsigned char smem_raw[];   // [wavefronts][window] 2-byte places
+    const EntLane<RB> L;
+    const int N = d.N, tid = threadIdx.x, l = tid & 63, W = blockDim.x >> 6;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    int step_mode = -1;   // block mode: only the step's core moves
+    if (block) {
+        uint64_t t;
+        resolve_mode(only, N, &t, &step_mode);
+    }
+    int k = 0;
+    for (int64_t slice = blockIdx.x; slice < gr.base[N]; slice += gridDim.x) {
+        while (k + 1 < N && slice >= gr.base[k + 1]) ++k;
+        if (block && step_mode != k) continue;   // uniform
+        const int i = (int)(slice - gr.base[k]), k0 = ring_next(k, N);
+        uint16_t* list = reinterpret_cast<uint16_t*>(smem_raw) + w * window;
+        // dL/dG_k of L = 1/(2B) sum r^2: the 1/B of the mean applied here
+        const float sc = (float)((double)scale * (dscale ? *dscale : 1.0) / (double)B);
+        const EntSlots<NM - 1, VEC> sl(d, k0, N - 1, L);
+        const bool in0 = L.on && L.col < d.R[k0];
+        ef4 acc = {0.f, 0.f, 0.f, 0.f};
+        const int64_t share = (((int64_t)B + W - 1) / W + 63) & ~63;
+        const int64_t s0 = w * share, s1 = min((int64_t)B, s0 + share);
+        for (int64_t w0 = s0; w0 < s1; w0 += window) {
+            const int len = (int)min((int64_t)window, s1 - w0);
+            int n = 0;   // uniform
+            for (int e0 = 0; e0 < len; e0 += 64 * KI) {
+                int key[KI];
+#pragma unroll
+                for (int u = 0; u < KI; ++u) {
+                    const int e = e0 + 64 * u + l;
+                    const int v = idx[(w0 + (e < len ? e : len - 1)) * N + k];
+                    key[u] = e < len ? v : -1;
                 }
+#pragma unroll
+                for (int u = 0; u < KI; ++u) {
+                    const uint64_t m = __ballot(key[u] == i);
+                    if (m) {   // uniform
+                        if (key[u] == i) list[n + __popcll(m & ((1ull << l) - 1ull))] = (uint16_t)(e0 + 64 * u + l);
+                        n += (int)__popcll(m);
+                    }
+                }
+            }
+            // this wavefront's LDS stores complete before its own reads
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            for (int q0 = 0; q0 < n; q0 += 64) {
+                int nb = min(64, n - q0);
+                const int64_t b = w0 + list[q0 + (l < nb ? l : nb - 1)];
+                float rl = resid[b] * sc;
+                OT off[NM - 1];   // this lane's entry: byte offsets of its slices of cores k+1, ..., k-1
+                bool okl = l < nb;
+                int ikk[NM - 1];
                 int kk = k0;
-                for (int q = 2; q < N; ++q) {
+#pragma unroll
+                for (int q = 0; q < NM - 1; ++q) {
+                    if (q >= N - 1) break;
+                    ikk[q] = idx[b * N + kk];
                     kk = ring_next(kk, N);
-                    const float* A = base + kk * SS;
-                    float w[RM];
+                }
+                kk = k0;
 #pragma unroll
-                    for (int c = 0; c < RM; ++c) {
-                        float acc = 0.f;
+                for (int q = 0; q < NM - 1; ++q) {
+                    if (q >= N - 1) break;
+                    okl = okl && ikk[q] >= 0 && ikk[q] < d.I[kk];
+                    off[q] = (OT)(uint32_t)ikk[q] * (OT)(4 * d.R[kk] * d.R[ring_next(kk, N)]);
+                    kk = ring_next(kk, N);
+                }
+                const uint64_t okm = __ballot(okl);
+                const int nv = (int)__popcll(okm);
+                if (nv < nb) {   // uniform, rare: close the gaps the invalid entries leave
+                    if (nv == 0) continue;
+                    if (okl) list[q0 + __popcll(okm & ((1ull << l) - 1ull))] = (uint16_t)l;
+                    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                    __builtin_amdgcn_wave_barrier();
+                    const int src = list[q0 + (l < nv ? l : nv - 1)];
+                    rl = __shfl(rl, src, 64);
 #pragma unroll
-                        for (int r = 0; r < RM; ++r) acc += v[r] * A[r + RM * c];
-                        w[c] = acc;
+                    for (int q = 0; q < NM - 1; ++q)
+                        if (q < N - 1) off[q] = (OT)__shfl(off[q], src, 64);
+                    nb = nv;
+                }
+                // U packs: every pack's loads, then every pack's products;
+                // TAIL: lanes past the batch compute on its last entry, masked
+                auto round = [&](int at, auto tail) {
+                    constexpr bool TAIL = decltype(tail)::value;
+                    ef4 v[U][NM - 1];
+                    float r[U];
+                    uint32_t on[U];
+#pragma unroll
+                    for (int u = 0; u < U; ++u) {
+                        const int a0 = at + u * P + L.p, src = TAIL && a0 >= nb ? nb - 1 : a0;
+                        on[u] = !TAIL || a0 < nb ? ~0u : 0u;
+                        r[u] = __shfl(rl, src, 64);
+                        int kc = k0;
+#pragma unroll
+                        for (int q = 0; q < NM - 1; ++q) {
+                            if (q >= N - 1) break;
+                            v[u][q] = sl.load(cores.p[kc], (OT)__shfl(off[q], src, 64), q);
+                            kc = ring_next(kc, N);
+                        }
                     }
 #pragma unroll
-                    for (int c = 0; c < RM; ++c) v[c] = w[c];
-                }
-                const float rv = sres[cs + lb];
-                float* out = cb + lb * ES + k * SS + RM * s;
+                    for (int u = 0; u < U; ++u) {
+                        ef4 T = sl.template mask<TAIL>(v[u][0] * r[u], 0, on[u]);
+                        int kc = k0;
 #pragma unroll
-                for (int c = 0; c < RM; ++c) out[c] = rv * v[c];
-            }
-            __syncthreads();
-            // (iii) ordered accumulation: each thread owns gradient positions
-            // (k, c, s) and adds the chunk's entries to them in entry order
-            for (int p = tid; p < N * RM2; p += BT) {
-                const int k = p / RM2, q = p - k * RM2, c = q % RM, s = q / RM;
-                const int Rk = d.R[k], Rk1 = d.R[ring_next(k, N)];
-                if (c >= Rk || s >= Rk1) continue;
-                int64_t go = 0;
-                for (int j = 0; j < k; ++j) go += (int64_t)d.I[j] * d.R[j] * d.R[ring_next(j, N)];
-                float* Gk = G + go + c + Rk * s;
-                const float* src = cb + k * SS + q;
-                const int RRk = Rk * Rk1;
-                for (int lb = 0; lb < nb; ++lb)
-                    if (cidx[lb * N] >= 0) Gk[(int64_t)cidx[lb * N + k] * RRk] += src[lb * ES];
+                        for (int q = 1; q < NM - 1; ++q) {
+                            if (q >= N - 1) break;
+                            kc = ring_next(kc, N);
+                            const ef4 a = sl.template mask<TAIL>(v[u][q], q, on[u]);
+                            if (q + 1 < N - 1)
+                                T = ent_mask(ent_mul(a, T, ef4{0.f, 0.f, 0.f, 0.f}), in0, L.row4,
+                                             d.R[ring_next(kc, N)]);
+                            else
+                                acc = ent_mul(a, T, acc);
+                        }
+                        if (N == 2) acc += T;
+                    }
+                };
+                int at = 0;
+#pragma unroll 1
+                for (; at + U * P <= nb; at += U * P) round(at, std::false_type{});
+                if (at < nb) round(at, std::true_type{});
             }
         }
-    }
-    if (SLICE_LDS) {
+        // the packed blocks, then the wavefronts, in a fixed order
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            if constexpr (RB == 4) acc[j] += __shfl_xor(acc[j], 20, 64);
+            if constexpr (RB <= 8) acc[j] += __shfl_xor(acc[j], 40, 64);
+        }
+        const int Rk = d.R[k], RR = Rk * d.R[k0];
+        __syncthreads();   // every list has been read
+        float* part = reinterpret_cast<float*>(smem_raw);   // [wavefronts][RB * RB]
+        if (L.on && L.p == 0) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) part[w * (RB * RB) + L.col * RB + L.row4 + j] = acc[j];
+        }
         __syncthreads();
-        for (int64_t e = tid; e < slice_len; e += BT) Gout[e] = G[e];
+        for (int e = tid; e < RR; e += blockDim.x) {
+            const float* p = part + (e / Rk) * RB + e % Rk;
+            float sum = 0.f;
+            for (int v = 0; v < W; ++v) sum += p[v * (RB * RB)];
+            static_cast<float*>(grads.p[k])[(int64_t)i * RR + e] = sum;
+        }
+        __syncthreads();   // the partial tiles have been read
     }
-}
-
-// Backward, phase 2: the block slices summed in a fixed order, in two levels
-// for parallelism.  Level 1: thread per element, grid row g sums run g of QG
-// consecutive runs of block slices.  Level 2: the run totals in run order,
-// into grads[k].
-__global__ __launch_bounds__(256) void k_entry_bwd_reduce1(const float* __restrict__ gpart, int nblocks, int QG,
-                                                           int64_t slice_len, float* __restrict__ red) {
-    const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= slice_len) return;
-    const int g = blockIdx.y;
-    const int q0 = (int)((int64_t)nblocks * g / QG), q1 = (int)((int64_t)nblocks * (g + 1) / QG);
-    float s = 0.f;
-#pragma unroll 8
-    for (int q = q0; q < q1; ++q) s += gpart[(int64_t)q * slice_len + e];
-    red[(int64_t)g * slice_len + e] = s;
-}
-
-__global__ __launch_bounds__(256) void k_entry_bwd_reduce2(tr_desc d, const float* __restrict__ red, int QG,
-                                                           int64_t slice_len, MutPtrs grads) {
-    const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= slice_len) return;
-    int k = 0;
-    int64_t base = 0;
-    for (; k < d.N; ++k) {
-        const int64_t len = (int64_t)d.I[k] * d.R[k] * d.R[ring_next(k, d.N)];
-        if (e < base + len) break;
-        base += len;
-    }
-    float s = 0.f;
-#pragma unroll 8
-    for (int g = 0; g < QG; ++g) s += red[(int64_t)g * slice_len + e];
-    static_cast<float*>(grads.p[k])[e - base] = s;
 }
 
 struct EntryPlan {
-    int fwd_blocks, bwd_blocks, bwd_threads, EPB, SB, PF, QG;
+    int fwd_blocks, fwd_iters, rb, nm, waves, window;
+    bool vec, big;   // big: a core of 4 GiB or more
     int64_t slice_len;
-    size_t part_off, gpart_off, red_off, total, bwd_shm;
-    bool slice_lds;   // the block's gradient slice fits in LDS beside the staging
+    EntGroups gr;
+    size_t part_off, total;
 };
 
-// Blocks of the backward: two per compute unit of a 256-CU device when there
-// are enough entries, fewer when the private slices would pass 64 MB.
 static EntryPlan entry_plan(const tr_desc& d, int B) {
     EntryPlan P{};
-    const int per = kEntBlock / d.R[0];
-    P.fwd_blocks = (B + per - 1) / per;
-    int64_t sl = 0;
-    for (int k = 0; k < d.N; ++k) sl += (int64_t)d.I[k] * d.R[k] * d.R[ring_next(k, d.N)];
-    P.slice_len = sl;
-    const int RM = rank_bound(d), SS = RM * RM + 1, ES = (d.N * SS) | 1;
-    const int cap_blocks = (int)std::max<int64_t>(1, std::min<int64_t>(512, ((int64_t)64 << 20) / (sl * 4)));
-    int blocks = std::min(cap_blocks, (B + 7) / 8);
-    P.EPB = (B + blocks - 1) / blocks;
-    P.bwd_blocks = (B + P.EPB - 1) / P.EPB;
-    P.PF = std::min(P.EPB, 64);
-    const size_t pf_bytes = (size_t)P.PF * (d.N + 1) * 4;
-    const size_t per_entry = (size_t)2 * ES * 4;   // staged slices + contributions
-    P.slice_lds = (size_t)sl * 4 <= 40 * 1024 && (size_t)sl * 4 + pf_bytes + per_entry + 64 <= 64 * 1024;
-    const size_t avail = 64 * 1024 - 64 - pf_bytes - (P.slice_lds ? (size_t)sl * 4 : 0);
-    int SB = 32;
-    while (SB > 1 && (size_t)SB * per_entry > avail) SB >>= 1;
-    P.SB = SB;
-    P.bwd_shm = (size_t)SB * per_entry + pf_bytes + (P.slice_lds ? (size_t)sl * 4 : 0);
-    const int pos = d.N * RM * RM;
-    P.bwd_threads = std::min(1024, std::max(256, (pos + 63) / 64 * 64));
-    P.QG = std::max(1, std::min(32, (P.bwd_blocks + 15) / 16));
+    const Shape sh = shape_of(d);
+    P.rb = sh.maxR <= 4 ? 4 : (sh.maxR <= 8 ? 8 : 16);
+    for (int k = 0; k < d.N; ++k)
+        P.big = P.big || (int64_t)d.I[k] * d.R[k] * d.R[ring_next(k, d.N)] >= ((int64_t)1 << 30);
+    P.nm = P.big ? kMaxOrder : (d.N <= 3 ? 3 : (d.N <= 5 ? 5 : kMaxOrder));
+    // one round per wavefront up to a full chip (four wavefronts per SIMD)
+    const int64_t per = (kEntBlock / 64) * (16 / P.rb) * ent_packs(P.nm), fb = ((int64_t)B + per - 1) / per;
+    P.fwd_iters = (int)std::min<int64_t>(16, (fb + 1023) / 1024);
+    P.fwd_blocks = (int)((fb + P.fwd_iters - 1) / P.fwd_iters);
+    P.vec = true;
+    for (int k = 0; k < d.N; ++k) {
+        const int64_t len = (int64_t)d.I[k] * d.R[k] * d.R[ring_next(k, d.N)];
+        P.slice_len += len;
+        P.gr.base[k + 1] = P.gr.base[k] + d.I[k];
+        P.vec = P.vec && d.R[k] % 4 == 0;
+    }
+    // at most four wavefronts per SIMD over all slices, at least 64 entries of
+    // scan each
+    P.waves = 1;
+    while (P.waves < kBwdWaves && 2 * P.gr.base[d.N] * P.waves <= 4096 && (int64_t)64 * P.waves < B) P.waves *= 2;
+    const int64_t share = (((int64_t)B + P.waves - 1) / P.waves + 63) & ~(int64_t)63;
+    P.window = (int)std::max<int64_t>(kBwdWindowMin, std::min<int64_t>(kBwdWindow, share));
     P.part_off = 0;
-    P.gpart_off = align_up((size_t)P.fwd_blocks * 8);
-    P.red_off = P.gpart_off + align_up((size_t)P.bwd_blocks * sl * 4);
-    P.total = P.red_off + align_up((size_t)P.QG * sl * 4);
+    P.total = align_up((size_t)P.fwd_blocks * 8);
     return P;
+}
+
+// 16-byte slice loads: every rank a multiple of 4 (so every slice is whole
+// pieces) and every core 16-byte aligned.
+static bool entry_vec(const tr_desc& d, const EntryPlan& P, const Ptrs& cp) {
+    bool v = P.vec;
+    for (int k = 0; k < d.N; ++k) v = v && (reinterpret_cast<uintptr_t>(cp.p[k]) & 15) == 0;
+    return v;
 }
 
 // ------------------------------------------------------------ completion --
@@ -356,14 +453,15 @@ __global__ __launch_bounds__(256) void k_completion_draw(tr_desc d, const uint64
 
 // loss = 1/(2B) sum r^2 (the forward's block partials, in block order) +
 // lambda/2 sum_k ||G_k||^2 (each strided per thread, then the block tree).
-__global__ __launch_bounds__(256) void k_completion_loss(tr_desc d, const double* __restrict__ part, int nb, int B,
-                                                         Ptrs cores, double lam, double* __restrict__ loss) {
-    __shared__ double red[4];
+__global__ __launch_bounds__(1024) void k_completion_loss(tr_desc d, const double* __restrict__ part, int nb, int B,
+                                                          Ptrs cores, double lam, double* __restrict__ loss) {
+    __shared__ double red[16];
     double s = 0.0;
     if (lam != 0.0)
         for (int k = 0; k < d.N; ++k) {
             const float* G = static_cast<const float*>(cores.p[k]);
             const int64_t len = (int64_t)d.I[k] * d.R[k] * d.R[ring_next(k, d.N)];
+#pragma unroll 8
             for (int64_t e = threadIdx.x; e < len; e += blockDim.x) s += (double)G[e] * (double)G[e];
         }
     const double ridge = block_sum(s, red);
@@ -373,71 +471,95 @@ __global__ __launch_bounds__(256) void k_completion_loss(tr_desc d, const double
     if (threadIdx.x == 0) *loss = data / (2.0 * (double)B) + 0.5 * lam * ridge;
 }
 
+// The update; its last block advances the step counter.
 __global__ __launch_bounds__(256) void k_completion_update(tr_desc d, const uint64_t* __restrict__ t_dev,
                                                            uint64_t seed, int block, MutPtrs cores, MutPtrs accum,
                                                            const float* __restrict__ grads, int64_t slice_len,
-                                                           double lam, tr_step rule, int32_t* status) {
+                                                           double lam, tr_step rule, int32_t* status, StepBump step) {
     const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= slice_len) return;
-    const uint64_t t = *t_dev;
-    int k = 0;
-    int64_t base = 0;
-    for (; k < d.N; ++k) {
-        const int64_t len = (int64_t)d.I[k] * d.R[k] * d.R[ring_next(k, d.N)];
-        if (e < base + len) break;
-        base += len;
+    const bool reads_t = block || rule.kind == 2;
+    if (e < slice_len) {
+        const uint64_t t = reads_t ? *t_dev : 0;
+        int k = 0;
+        int64_t base = 0;
+        for (; k < d.N; ++k) {
+            const int64_t len = (int64_t)d.I[k] * d.R[k] * d.R[ring_next(k, d.N)];
+            if (e < base + len) break;
+            base += len;
+        }
+        if (!block || k == pick_mode(seed, t, d.N)) {
+            float* G = static_cast<float*>(cores.p[k]);
+            float* A = static_cast<float*>(accum.p[k]);
+            const int64_t o = e - base;
+            const double p = -((double)grads[e] + lam * (double)G[o]);
+            apply_rule(G, A, o, p, rule, t, status);
+        }
     }
-    if (block && k != pick_mode(seed, t, d.N)) return;
-    float* G = static_cast<float*>(cores.p[k]);
-    float* A = static_cast<float*>(accum.p[k]);
-    const int64_t o = e - base;
-    const double p = -((double)grads[e] + lam * (double)G[o]);
-    apply_rule(G, A, o, p, rule, t, status);
+    bump_if_last(step, reads_t);
+}
+
+// F::run<RB, VEC, NM, OT>(args...) for the plan's kernel variant.
+template <typename F, int RB, bool VEC, typename... A>
+static void entry_dispatch_nm(const EntryPlan& P, A... a) {
+    // (cores of 4 GiB and more are rare enough to take the widest order's form)
+    if (P.big) F::template run<RB, VEC, kMaxOrder, uint64_t>(a...);
+    else if (P.nm == 3) F::template run<RB, VEC, 3, uint32_t>(a...);
+    else if (P.nm == 5) F::template run<RB, VEC, 5, uint32_t>(a...);
+    else F::template run<RB, VEC, kMaxOrder, uint32_t>(a...);
+}
+template <typename F, typename... A>
+static void entry_dispatch(const EntryPlan& P, bool vec, A... a) {
+    if (P.rb == 4) vec ? entry_dispatch_nm<F, 4, true>(P, a...) : entry_dispatch_nm<F, 4, false>(P, a...);
+    else if (P.rb == 8) vec ? entry_dispatch_nm<F, 8, true>(P, a...) : entry_dispatch_nm<F, 8, false>(P, a...);
+    else vec ? entry_dispatch_nm<F, 16, true>(P, a...) : entry_dispatch_nm<F, 16, false>(P, a...);
 }
 
 template <typename TX>
-static void launch_entry_fwd(const tr_desc& d, Ptrs cp, const int32_t* idx, const TX* x, int B, float* resid,
-                             double* part, int blocks, hipStream_t st) {
-    switch (rank_bound(d)) {
-        case 4: hipLaunchKernelGGL((k_entry_fwd<TX, 4>), dim3(blocks), dim3(kEntBlock), 0, st, d, cp, idx, x, B, resid,
-                                   part); break;
-        case 8: hipLaunchKernelGGL((k_entry_fwd<TX, 8>), dim3(blocks), dim3(kEntBlock), 0, st, d, cp, idx, x, B, resid,
-                                   part); break;
-        case 12: hipLaunchKernelGGL((k_entry_fwd<TX, 12>), dim3(blocks), dim3(kEntBlock), 0, st, d, cp, idx, x, B,
-                                    resid, part); break;
-        default: hipLaunchKernelGGL((k_entry_fwd<TX, 16>), dim3(blocks), dim3(kEntBlock), 0, st, d, cp, idx, x, B,
-                                    resid, part); break;
+struct FwdLaunch {
+    template <int RB, bool VEC, int NM, typename OT>
+    static void run(const tr_desc* d, const EntryPlan* P, Ptrs cp, const int32_t* idx, const TX* x, int B,
+                    float* resid, double* part, hipStream_t st) {
+        hipLaunchKernelGGL((k_entry_fwd<TX, RB, VEC, NM, OT>), dim3(P->fwd_blocks), dim3(kEntBlock), 0, st, *d, cp,
+                           idx, x, B, P->fwd_iters, resid, part);
     }
+};
+
+template <typename TX>
+static void launch_entry_fwd(const tr_desc& d, const EntryPlan& P, Ptrs cp, const int32_t* idx, const TX* x, int B,
+                             float* resid, double* part, hipStream_t st) {
+    entry_dispatch<FwdLaunch<TX>>(P, entry_vec(d, P, cp), &d, &P, cp, idx, x, B, resid, part, st);
 }
 
-static void launch_entry_bwd(const tr_desc& d, const EntryPlan& P, Ptrs cp, const int32_t* idx, const float* resid,
-                             int B, float scale, const double* scale_dev, float* gpart, float* red, MutPtrs grads,
-                             hipStream_t st) {
-#define TRK_BWD(LDS, RMV)                                                                                         \
-    hipLaunchKernelGGL((k_entry_bwd_acc<LDS, RMV>), dim3(P.bwd_blocks), dim3(P.bwd_threads), P.bwd_shm, st, d, cp, \
-                       idx, resid, B, P.EPB, P.SB, P.PF, scale, scale_dev, gpart, P.slice_len)
-    const int rm = rank_bound(d);
-    if (P.slice_lds) {
-        if (rm == 4) TRK_BWD(true, 4);
-        else if (rm == 8) TRK_BWD(true, 8);
-        else if (rm == 12) TRK_BWD(true, 12);
-        else TRK_BWD(true, 16);
-    } else {
-        if (rm == 4) TRK_BWD(false, 4);
-        else if (rm == 8) TRK_BWD(false, 8);
-        else if (rm == 12) TRK_BWD(false, 12);
-        else TRK_BWD(false, 16);
+struct BwdLaunch {
+    template <int RB, bool VEC, int NM, typename OT>
+    static void run(const tr_desc* d, const EntryPlan* P, Ptrs cp, const int32_t* idx, const float* resid, int B,
+                    float scale, const double* scale_dev, ModeSrc only, int block, MutPtrs grads, hipError_t* e,
+                    hipStream_t st) {
+        const size_t shm = (size_t)P->waves * P->window * 2;
+        if (!allow_lds(reinterpret_cast<const void*>(&k_entry_bwd<RB, VEC, NM, OT>), shm)) {
+            *e = hipErrorInvalidValue;
+            return;
+        }
+        hipLaunchKernelGGL((k_entry_bwd<RB, VEC, NM, OT>), dim3((unsigned)std::min(P->gr.base[d->N], kBwdGrid)),
+                           dim3(64 * P->waves), shm, st, *d, cp, idx, resid, B, scale, scale_dev, P->gr,
+                           P->window, only, block, grads);
+        *e = hipGetLastError();
     }
-#undef TRK_BWD
-    const unsigned eb = (unsigned)((P.slice_len + 255) / 256);
-    hipLaunchKernelGGL(k_entry_bwd_reduce1, dim3(eb, (unsigned)P.QG), dim3(256), 0, st, gpart, P.bwd_blocks, P.QG,
-                       P.slice_len, red);
-    hipLaunchKernelGGL(k_entry_bwd_reduce2, dim3(eb), dim3(256), 0, st, d, red, P.QG, P.slice_len, grads);
+};
+
+// ``block`` nonzero: only the core of ``only``'s mode.
+static hipError_t launch_entry_bwd(const tr_desc& d, const EntryPlan& P, Ptrs cp, const int32_t* idx,
+                                   const float* resid, int B, float scale, const double* scale_dev, ModeSrc only,
+                                   int block, MutPtrs grads, hipStream_t st) {
+    hipError_t e = hipSuccess;
+    entry_dispatch<BwdLaunch>(P, entry_vec(d, P, cp), &d, &P, cp, idx, resid, B, scale, scale_dev, only, block, grads,
+                              &e, st);
+    return e;
 }
 
 struct CompletionWs {
     EntryPlan P;
-    size_t bidx, bx, resid, grads, loss, total;
+    size_t bidx, bx, resid, grads, ctr, total;
 };
 
 static CompletionWs completion_layout(const tr_desc& d, int B) {
@@ -452,8 +574,8 @@ static CompletionWs completion_layout(const tr_desc& d, int B) {
     o += align_up((size_t)B * 4);
     L.grads = o;
     o += align_up((size_t)L.P.slice_len * 4);
-    L.loss = o;
-    o += align_up(8);
+    L.ctr = o;
+    o += align_up(4);
     L.total = o;
     return L;
 }
@@ -493,10 +615,10 @@ tr_status tr_entry_fwd(const tr_desc* d, const void* const* cores, const int32_t
     double* part = reinterpret_cast<double*>(static_cast<char*>(ws) + P.part_off);
     switch (d->x_dtype) {
         case TR_F32:
-            launch_entry_fwd(*d, cp, idx, static_cast<const float*>(x), B, resid, part, P.fwd_blocks, st);
+            launch_entry_fwd(*d, P, cp, idx, static_cast<const float*>(x), B, resid, part, st);
             break;
         case TR_F16:
-            launch_entry_fwd(*d, cp, idx, static_cast<const __half*>(x), B, resid, part, P.fwd_blocks, st);
+            launch_entry_fwd(*d, P, cp, idx, static_cast<const __half*>(x), B, resid, part, st);
             break;
         default:
             return TR_E_DTYPE;
@@ -526,10 +648,9 @@ tr_status tr_entry_bwd(const tr_desc* d, const void* const* cores, const int32_t
         cp.p[k] = cores[k];
         gp.p[k] = grads[k];
     }
-    char* w = static_cast<char*>(ws);
-    launch_entry_bwd(*d, P, cp, idx, resid, B, (float)scale, scale_dev, reinterpret_cast<float*>(w + P.gpart_off),
-                     reinterpret_cast<float*>(w + P.red_off), gp, st);
-    return hipGetLastError() == hipSuccess ? TR_OK : TR_E_HIP;
+    return launch_entry_bwd(*d, P, cp, idx, resid, B, (float)scale, scale_dev, ModeSrc{}, 0, gp, st) == hipSuccess
+               ? TR_OK
+               : TR_E_HIP;
 }
 
 static tr_status completion_checks(const tr_desc* d, const tr_completion_config* c) {
@@ -568,12 +689,10 @@ tr_status tr_completion_run(const tr_desc* d, void* const* cores, void* const* a
     hipStream_t st = (hipStream_t)stream;
     char* w = static_cast<char*>(ws);
     double* part = reinterpret_cast<double*>(w + L.P.part_off);
-    float* gpart = reinterpret_cast<float*>(w + L.P.gpart_off);
-    float* red = reinterpret_cast<float*>(w + L.P.red_off);
     int32_t* bidx = reinterpret_cast<int32_t*>(w + L.bidx);
     float* resid = reinterpret_cast<float*>(w + L.resid);
     float* grads = reinterpret_cast<float*>(w + L.grads);
-    double* lossw = reinterpret_cast<double*>(w + L.loss);
+    unsigned* ctr = reinterpret_cast<unsigned*>(w + L.ctr);
     Ptrs cp{};
     MutPtrs mc{}, ac{}, gp{};
     int64_t off = 0;
@@ -587,26 +706,28 @@ tr_status tr_completion_run(const tr_desc* d, void* const* cores, void* const* a
     const int B = c->B;
     const dim3 gd((unsigned)((B + 255) / 256));
     const dim3 gu((unsigned)((L.P.slice_len + 255) / 256));
+    if (launch_zero_u32(ctr, 1, st) != hipSuccess) return TR_E_HIP;
+    const ModeSrc only{t_dev, 0, -1, c->seed, nullptr, nullptr};
     for (int it = 0; it < steps; ++it) {
-        double* loss = loss_out ? loss_out + it : lossw;
         if (d->x_dtype == TR_F32) {
             float* bx = reinterpret_cast<float*>(w + L.bx);
             hipLaunchKernelGGL(k_completion_draw<float>, gd, dim3(256), 0, st, *d, t_dev, c->seed, obs_idx,
                                static_cast<const float*>(obs_x), n_obs, B, bidx, bx);
-            launch_entry_fwd(*d, cp, bidx, static_cast<const float*>(bx), B, resid, part, L.P.fwd_blocks, st);
+            launch_entry_fwd(*d, L.P, cp, bidx, static_cast<const float*>(bx), B, resid, part, st);
         } else {
             __half* bx = reinterpret_cast<__half*>(w + L.bx);
             hipLaunchKernelGGL(k_completion_draw<__half>, gd, dim3(256), 0, st, *d, t_dev, c->seed, obs_idx,
                                static_cast<const __half*>(obs_x), n_obs, B, bidx, bx);
-            launch_entry_fwd(*d, cp, bidx, static_cast<const __half*>(bx), B, resid, part, L.P.fwd_blocks, st);
+            launch_entry_fwd(*d, L.P, cp, bidx, static_cast<const __half*>(bx), B, resid, part, st);
         }
-        hipLaunchKernelGGL(k_completion_loss, dim3(1), dim3(256), 0, st, *d, part, L.P.fwd_blocks, B, cp, c->lambda,
-                           loss);
-        launch_entry_bwd(*d, L.P, cp, bidx, resid, B, 1.0f, nullptr, gpart, red, gp, st);
+        if (loss_out)
+            hipLaunchKernelGGL(k_completion_loss, dim3(1), dim3(1024), 0, st, *d, part, L.P.fwd_blocks, B, cp,
+                               c->lambda, loss_out + it);
+        if (launch_entry_bwd(*d, L.P, cp, bidx, resid, B, 1.0f, nullptr, only, (int)c->block, gp, st) != hipSuccess)
+            return TR_E_HIP;
         hipLaunchKernelGGL(k_completion_update, gu, dim3(256), 0, st, *d, t_dev, c->seed, (int)c->block, mc, ac,
-                           grads, L.P.slice_len, c->lambda, c->rule, dev_status);
+                           grads, L.P.slice_len, c->lambda, c->rule, dev_status, StepBump{t_dev, ctr});
         if (hipGetLastError() != hipSuccess) return TR_E_HIP;
-        if (launch_bump(t_dev, st) != hipSuccess) return TR_E_HIP;
     }
     return TR_OK;
 }

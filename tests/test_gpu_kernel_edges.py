@@ -4,8 +4,9 @@ import numpy as np
 import pytest
 import torch
 
-from gpu_util import DEV, TOL, problem, rel, say, unfold
-from oracle import brsgd
+import tr_inputs as ti
+from gpu_util import DEV, TOL, problem, rel, rounded, say, to_dev, unfold
+from oracle import brsgd, entry
 from paper_2303_16492_amd import _lib as L
 from paper_2303_16492_amd import api
 
@@ -111,3 +112,61 @@ def test_grad_fp32_streaming(I, R, m, xdt):
                                       brsgd.J_of(I, n))
         assert rel(g.cpu().numpy(), gref) < TOL[dtype]
         assert abs(float(loss) - lref) <= TOL[dtype] * abs(lref)
+
+
+# sampled entries: every packing of slices (rank bounds 4, 8, 16; whole 16-byte
+# slices or not), orders 2 and 8, every number of slices per workgroup (1 to
+# 16), one index holding every entry, lists around 64 entries and past one
+# window of the scan, large modes
+@pytest.mark.parametrize("N,I,R,B", [(8, [3, 2, 4, 2, 3, 2, 2, 5], [4, 3, 2, 1, 4, 2, 3, 4], 1000),
+                                     (8, [2, 3, 2, 3, 2, 3, 2, 3], [8, 5, 7, 8, 6, 8, 8, 4], 130),
+                                     (2, [1, 1], [16, 12], 1025), (2, [17, 1], [4, 4], 64), (3, [1, 30, 2], [8, 8, 8], 5000),
+                                     (3, [2048, 5, 6], [4, 4, 4], 3000), (3, [2049, 5, 6], [4, 8, 4], 17),
+                                     (2, [32768, 6], [2, 3], 2000), (2, [32769, 6], [2, 3], 2000),
+                                     (4, [9, 8, 7, 6], [12, 16, 9, 13], 40001)])
+def test_entry_packs_and_lists(N, I, R, B):
+    dtype = torch.float32
+    cores = [rounded(c, dtype) for c in ti.gaussian_cores(5, N, I, R, scale=0.6)]
+    idx = ti.entry_indices(6, I, B)
+    x = rounded(ti.standard_normal(7, B), dtype)
+    bad = np.zeros(B, dtype=bool)
+    if B > 64:   # invalid indices: NaN residual, no gradient contribution
+        bad[[3, B // 2]] = True
+        idx[3, 0], idx[B // 2, N - 1] = I[0], -1
+    ok = ~bad
+    desc = api.make_desc(I, R, dtype)
+    dc = [to_dev(unfold(c), dtype) for c in cores]
+    didx = to_dev(idx, torch.int32)
+    say("entries", N, I, R, B)
+    resid, _ = api.tr_entry_fwd(desc, dc, didx, to_dev(x, dtype), B)
+    r = resid.cpu().numpy()
+    _, rref = entry.entry_loss(cores, idx[ok], x[ok])
+    assert np.array_equal(np.isnan(r), bad) and rel(r[ok], rref) < 1e-5
+    grads = api.tr_entry_bwd(desc, dc, didx, resid, B, scale=ok.sum() and B / ok.sum())
+    again = api.tr_entry_bwd(desc, dc, didx, resid, B, scale=ok.sum() and B / ok.sum())
+    gref = entry.entry_grads(cores, idx[ok], x[ok])
+    for k in range(N):
+        assert rel(grads[k].cpu().numpy(), unfold(gref[k])) < 1e-5, k
+        assert torch.equal(grads[k], again[k])
+
+
+def test_entry_infinity_stays_with_its_entries():
+    """One slice of one core holds an infinity: the gradients of the rows that
+    no entry through it touches stay finite and exact, packed or not."""
+    N, I, R, B = 3, [8, 9, 10], [4, 4, 4], 60
+    cores = [rounded(c, torch.float32) for c in ti.gaussian_cores(8, N, I, R, scale=0.6)]
+    idx = ti.entry_indices(9, I, B)
+    x = rounded(ti.standard_normal(10, B), torch.float32)
+    keep = idx[:, 0] != 2
+    dc = [to_dev(unfold(c), torch.float32) for c in cores]
+    dc[0][2, 5] = float("inf")
+    desc = api.make_desc(I, R, torch.float32)
+    say("entries with an infinity")
+    resid, _ = api.tr_entry_fwd(desc, dc, to_dev(idx, torch.int32), to_dev(x, torch.float32), B)
+    grads = api.tr_entry_bwd(desc, dc, to_dev(idx, torch.int32), resid, B)
+    gref = entry.entry_grads(cores, idx[keep], x[keep])
+    assert np.all(np.isfinite(resid.cpu().numpy()[keep]))
+    for k in range(N):
+        clean = np.setdiff1d(np.arange(I[k]), idx[~keep][:, k])
+        got = grads[k].cpu().numpy()[clean] * B / keep.sum()
+        assert rel(got, unfold(gref[k])[clean]) < 1e-5
