@@ -5,17 +5,11 @@
 // G_{k-1}(i_{k-1}), i.e. the row of G^{!=k}_[2] at entry b (the block
 // gradient of eq:gradient restricted to sampled entries).
 //
-// Slice products run on the matrix cores (v_mfma_f32_16x16x4_f32) in
-// transposed form: with T = S_1 ... S_q, T^T sits in the result layout (lane
-// l, entry j: row 4 (l / 16) + j, column l % 16), which is also the B operand
-// of the next product T^T <- S^T T^T when K step j takes k = 4 (l / 16) + j,
-// and the A operand of that step is S(4 (l / 16) + j, l % 16): four
-// consecutive entries of the stored slice.  So a chain of slices never leaves
-// the registers and needs no LDS.  Slices of ranks <= 8 (<= 4) are packed as
-// 2 (4) diagonal blocks of one 16 x 16 operand, one entry each.
+// Slice products run on the matrix cores in transposed form, one to four
+// entries packed per operand (chain.hpp): a chain needs no LDS.
 //
-// Forward: one wavefront per pack of entries; the trace is the sum of
-// T^T S over the last slice.  Only the residuals leave the kernel.
+// Forward: a few packs of entries per wavefront; the trace is the sum of T^T S
+// over the last slice.  Only the residuals leave the kernel.
 //
 // Backward: a workgroup owns the gradient slice of one (core, index).  Each of
 // its wavefronts scans its share of the batch's indices of that mode, compacts
@@ -36,7 +30,7 @@
 #include <algorithm>
 #include <type_traits>
 
-#include "internal.hpp"
+#include "chain.hpp"
 
 namespace trk {
 
@@ -52,87 +46,7 @@ __global__ __launch_bounds__(256) void k_entry_loss(const double* __restrict__ p
     if (threadIdx.x == 0) *loss = s / (2.0 * (double)B);
 }
 
-// ------------------------------------------------ matrix-core entry kernels --
-
-typedef float ef4 __attribute__((ext_vector_type(4)));
-
-// A lane's place in a 16 x 16 operand of 16 / RB diagonal RB x RB blocks:
-// block p (off-diagonal lanes: on = false, zeros), rows row4 .. row4 + 3 and
-// column col inside the block.
-template <int RB>
-struct EntLane {
-    int p, row4, col;
-    bool on;
-    __device__ __forceinline__ EntLane() {
-        const int l = threadIdx.x & 63, lr = l & 15, lk = l >> 4;
-        p = lr / RB;
-        on = p == 4 * lk / RB;
-        row4 = (4 * lk) % RB;
-        col = lr % RB;
-    }
-};
-
-// Byte offsets inside a slice of the four entries a lane loads, and their
-// masks, for the slices of a chain of ``len`` cores from k0 (len <= NM): the
-// first slice transposed, S(col, row4 + j), the others S(row4 + j, col).
-// Offsets are clamped into the slice; VEC: whole 16-byte pieces, R_k a
-// multiple of 4 (only the first offset is used).
-template <int NM, bool VEC>
-struct EntSlots {
-    uint32_t lo[NM][4], mk[NM][4];
-    int len;
-    template <int RB>
-    __device__ __forceinline__ EntSlots(const tr_desc& d, int k0, int n, const EntLane<RB>& L) : len(n) {
-        int k = k0;
-#pragma unroll
-        for (int q = 0; q < NM; ++q) {
-            if (q >= n) break;
-            const int Rk = d.R[k], Rk1 = d.R[ring_next(k, d.N)];
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int r = q == 0 ? L.col : L.row4 + j, c = q == 0 ? L.row4 + j : L.col;
-                mk[q][j] = L.on && r < Rk && c < Rk1 ? ~0u : 0u;
-                const int rc = r < Rk ? r : (VEC && q > 0 ? 0 : Rk - 1), cc = c < Rk1 ? c : Rk1 - 1;
-                lo[q][j] = 4u * (uint32_t)(rc + Rk * cc);
-            }
-            k = ring_next(k, d.N);
-        }
-    }
-    // the lane's entries of slice q of the chain, the slice at byte ``off`` of its core
-    template <typename OT>
-    __device__ __forceinline__ ef4 load(const void* __restrict__ core, OT off, int q) const {
-        const char* A = static_cast<const char*>(core);
-        if (VEC && q > 0) {
-            const float4 v = *reinterpret_cast<const float4*>(A + (OT)(off + lo[q][0]));
-            return ef4{v.x, v.y, v.z, v.w};
-        }
-        ef4 v;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) v[j] = *reinterpret_cast<const float*>(A + (OT)(off + lo[q][j]));
-        return v;
-    }
-    // exact zeros outside the slice (an infinity or NaN of one packed entry
-    // stays its own)
-    template <bool ALSO = false>
-    __device__ __forceinline__ ef4 mask(ef4 v, int q, uint32_t also = ~0u) const {
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-            v[j] = __uint_as_float(__float_as_uint(v[j]) & (ALSO ? mk[q][j] & also : mk[q][j]));
-        return v;
-    }
-};
-// T^T (c, r) of a product whose last slice has Rc columns and first slice R0
-// rows: exact zeros outside.
-__device__ __forceinline__ ef4 ent_mask(ef4 v, bool in, int row4, int rows) {
-#pragma unroll
-    for (int j = 0; j < 4; ++j) v[j] = __uint_as_float(__float_as_uint(v[j]) & (in && row4 + j < rows ? ~0u : 0u));
-    return v;
-}
-__device__ __forceinline__ ef4 ent_mul(const ef4& a, const ef4& t, ef4 acc) {
-#pragma unroll
-    for (int j = 0; j < 4; ++j) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[j], t[j], acc, 0, 0, 0);
-    return acc;
-}
+typedef ChainVec<float>::V ef4;
 
 // Packs whose slices a wavefront has in flight together: a pack's chain is a
 // few hundred cycles of products behind a memory round trip of several times
@@ -148,10 +62,10 @@ __global__ __launch_bounds__(kEntBlock, NM <= 5 ? 4 : 2) void k_entry_fwd(tr_des
                                                                          float* __restrict__ resid,
                                                                          double* __restrict__ part) {
     constexpr int P = 16 / RB, U = ent_packs(NM);
-    const EntLane<RB> L;
+    const ChainLane<float, RB> L;
     const int N = d.N, wv = threadIdx.x >> 6;
-    const EntSlots<NM, VEC> sl(d, 0, N, L);
-    const bool in0 = L.on && L.col < d.R[0];
+    const ChainSlots<float, NM, VEC> sl(d, 0, N, L);
+    const bool in0 = L.col < d.R[0];
     double sq = 0.0;
 #pragma unroll 1
     for (int it = 0; it < iters; ++it) {
@@ -191,7 +105,7 @@ __global__ __launch_bounds__(kEntBlock, NM <= 5 ? 4 : 2) void k_entry_fwd(tr_des
                 if (k >= N) break;
                 const ef4 a = sl.mask(v[u][k], k);
                 if (k + 1 < N) {
-                    T = ent_mask(ent_mul(a, T, ef4{0.f, 0.f, 0.f, 0.f}), in0, L.row4, d.R[ring_next(k, N)]);
+                    T = chain_mask(chain_mul(a, T, ef4{0.f, 0.f, 0.f, 0.f}), L, in0, d.R[ring_next(k, N)]);
                 } else {
                     // Trace(T S) = sum over (r, c) of T(r, c) S(c, r) = T^T(c, r) S(c, r)
 #pragma unroll
@@ -199,13 +113,13 @@ __global__ __launch_bounds__(kEntBlock, NM <= 5 ? 4 : 2) void k_entry_fwd(tr_des
                 }
             }
             // the lanes of one block, in a fixed order
-            tr = L.on ? tr : 0.f;
+            tr = L.on[0] ? tr : 0.f;
 #pragma unroll
             for (int o = 1; o < RB; o <<= 1) tr += __shfl_xor(tr, o, 64);
             if constexpr (RB >= 8) tr += __shfl_xor(tr, 16, 64);
             if constexpr (RB == 16) tr += __shfl_xor(tr, 32, 64);
             const int64_t b = b0 + P * u;
-            if (L.on && L.row4 == 0 && L.col == 0 && b < B) {
+            if (L.on[0] && L.row[0] == 0 && L.col == 0 && b < B) {
                 const float r = ok[u] ? tr - xb[u] : NAN;   // NaN: invalid caller index
                 resid[b] = r;
                 sq += (double)r * (double)r;
@@ -236,7 +150,7 @@ __global__ __launch_bounds__(64 * kBwdWaves) void k_entry_bwd(tr_desc d, Ptrs co
                                                               int window, ModeSrc only, int block, MutPtrs grads) {
     constexpr int P = 16 / RB, U = ent_packs(NM), KI = 16;
     extern __shared__ __align__(16) unsigned char smem_raw[];   // [wavefronts][window] 2-byte places
-    const EntLane<RB> L;
+    const ChainLane<float, RB> L;
     const int N = d.N, tid = threadIdx.x, l = tid & 63, W = blockDim.x >> 6;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     int step_mode = -1;   // block mode: only the step's core moves
@@ -252,8 +166,8 @@ __global__ __launch_bounds__(64 * kBwdWaves) void k_entry_bwd(tr_desc d, Ptrs co
         uint16_t* list = reinterpret_cast<uint16_t*>(smem_raw) + w * window;
         // dL/dG_k of L = 1/(2B) sum r^2: the 1/B of the mean applied here
         const float sc = (float)((double)scale * (dscale ? *dscale : 1.0) / (double)B);
-        const EntSlots<NM - 1, VEC> sl(d, k0, N - 1, L);
-        const bool in0 = L.on && L.col < d.R[k0];
+        const ChainSlots<float, NM - 1, VEC> sl(d, k0, N - 1, L);
+        const bool in0 = L.col < d.R[k0];
         ef4 acc = {0.f, 0.f, 0.f, 0.f};
         const int64_t share = (((int64_t)B + W - 1) / W + 63) & ~63;
         const int64_t s0 = w * share, s1 = min((int64_t)B, s0 + share);
@@ -346,10 +260,10 @@ __global__ __launch_bounds__(64 * kBwdWaves) void k_entry_bwd(tr_desc d, Ptrs co
                             kc = ring_next(kc, N);
                             const ef4 a = sl.template mask<TAIL>(v[u][q], q, on[u]);
                             if (q + 1 < N - 1)
-                                T = ent_mask(ent_mul(a, T, ef4{0.f, 0.f, 0.f, 0.f}), in0, L.row4,
-                                             d.R[ring_next(kc, N)]);
+                                T = chain_mask(chain_mul(a, T, ef4{0.f, 0.f, 0.f, 0.f}), L, in0,
+                                               d.R[ring_next(kc, N)]);
                             else
-                                acc = ent_mul(a, T, acc);
+                                acc = chain_mul(a, T, acc);
                         }
                         if (N == 2) acc += T;
                     }
@@ -369,9 +283,9 @@ __global__ __launch_bounds__(64 * kBwdWaves) void k_entry_bwd(tr_desc d, Ptrs co
         const int Rk = d.R[k], RR = Rk * d.R[k0];
         __syncthreads();   // every list has been read
         float* part = reinterpret_cast<float*>(smem_raw);   // [wavefronts][RB * RB]
-        if (L.on && L.p == 0) {
+        if (L.on[0] && L.p == 0) {
 #pragma unroll
-            for (int j = 0; j < 4; ++j) part[w * (RB * RB) + L.col * RB + L.row4 + j] = acc[j];
+            for (int j = 0; j < 4; ++j) part[w * (RB * RB) + L.col * RB + L.row[j]] = acc[j];
         }
         __syncthreads();
         for (int e = tid; e < RR; e += blockDim.x) {

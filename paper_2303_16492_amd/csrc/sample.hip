@@ -3,7 +3,7 @@
 //
 // S[f][r + R_n s] = M_f(s, r) with M_f = G_{n+1}(i_{n+1}) ... G_{n-1}(i_{n-1})
 // (the product of slices of the subchain, Section 3.2).
-#include "internal.hpp"
+#include "chain.hpp"
 
 namespace trk {
 
@@ -17,18 +17,37 @@ namespace trk {
 // step's own mode is dropped.
 // do_sample == 2 enumerates instead: sample f is column j = f of X_[n]
 // (every column once, m = J_n), decoded in the cyclic order, p = 1/J_n.
-// Phase 2: the N-1 core slices of every sample are copied to LDS in one
-// batch (a slice G_k(i) is row i of G_k(2): R_k R_{k+1} contiguous values).
-// Phase 3: the chain products M <- M G_k(i_k), the last product written
-// straight to S[f][r + R_n s] = M_f(s, r): for FP32 cores one wavefront per
-// sample on the matrix cores; for FP64 one output entry per thread at a time
-// (consecutive threads, consecutive columns), accumulated in FP64 with the
+// Phase 2, FP32 cores: the chain products of every sample's slices on the
+// matrix cores (chain.hpp), each wavefront its packs of samples, every slice
+// of a group of packs requested before the first product; the last product is
+// written straight to S[f][r + R_n s] = M_f(s, r).  No LDS beyond the draws and
+// no barrier after them.
+// Phase 2, FP64 cores: the N-1 slices of every sample are copied to LDS in one
+// batch; the chain products M <- M G_k(i_k) take one output entry per thread at
+// a time (consecutive threads, consecutive columns), accumulated with the
 // inner index ascending.
+//
+// Bound: latency (the draws' generator chain, then one round of slice loads).
+// FP32 per launch, with the slices copied to LDS and one product per barrier
+// before: 64^4, ranks 5, m 512, leverage law 11.7 -> 7.3 us; 400^3,
+// ranks 10, m 4096 8.2 -> 7.0 us; 101 x 57 x 83 x 44, ranks 12/11/9/14, m 2048
+// 12.3 -> 10.0 us.
+constexpr int kSampleBlock = 16;   // samples of a block
+
+// Packs whose slices a wavefront has in flight together (at most 64 registers
+// of slices), NM - 1 slices a sample.
 template <typename TC>
-__global__ __launch_bounds__(256) void k_sample_subchain(tr_desc d, ModeSrc ms, int m, int SB, CdfPtrs cdf,
+constexpr int sample_packs(int NM) {
+    const int u = 64 / ((NM - 1) * 4 * (int)(sizeof(TC) / 4));
+    return u >= 4 ? 4 : (u >= 2 ? 2 : 1);
+}
+
+template <typename TC, int RB, bool VEC, int NM, typename OT>
+__global__ __launch_bounds__(256) void k_sample_subchain(tr_desc d, ModeSrc ms, int m, int SBf, CdfPtrs cdf,
                                                          const uint64_t* __restrict__ cdf_J, int stream_tag,
                                                          Ptrs cores, int32_t* __restrict__ idx, double* __restrict__ pF,
                                                          TC* __restrict__ S, int do_sample, int do_subchain) {
+    const int SB = sizeof(TC) == 4 ? kSampleBlock : SBf;
     const int N = d.N, tid = threadIdx.x;
     const int f0 = blockIdx.x * SB;
     const int nb = min(SB, m - f0);
@@ -69,26 +88,9 @@ __global__ __launch_bounds__(256) void k_sample_subchain(tr_desc d, ModeSrc ms, 
     if (ms.n_pub && blockIdx.x == 0 && threadIdx.x == 0) *ms.n_pub = n;
     const int n1 = ring_next(n, N);
     const int Rn = d.R[n], Rn1 = d.R[n1], RR = Rn * Rn1;
-    extern __shared__ __align__(16) unsigned char smem_raw[];
-    int* sidx = reinterpret_cast<int*>(smem_raw);                   // [SB][kMaxOrder]
-    double* sp = reinterpret_cast<double*>(sidx + SB * kMaxOrder);  // [SB][kMaxOrder], order of the chain
-    int* sok = reinterpret_cast<int*>(sp + SB * kMaxOrder);         // [SB]
-    TC* sl = reinterpret_cast<TC*>(sok + ((SB + 3) & ~3));          // slices, then two product buffers
-
-    // chain order n+1, ..., n-1: stage q is mode (n + 1 + q) mod N; its
-    // slice starts at soff[q] within a sample's slices
-    __shared__ int soff[kMaxOrder + 1];
-    if (tid == 0) {
-        int o = 0;
-        for (int q = 0; q < N - 1; ++q) {
-            soff[q] = o;
-            const int k = (n + 1 + q) % N;
-            o += d.R[k] * d.R[ring_next(k, N)];
-        }
-        soff[N - 1] = o;
-    }
-    int mr = 0;   // largest rank: stride of the product buffers
-    for (int k = 0; k < N; ++k) mr = max(mr, d.R[k]);
+    __shared__ int sidx[kSampleBlock * kMaxOrder];
+    __shared__ double sp[kSampleBlock * kMaxOrder];   // order of the chain
+    __shared__ int sok[kSampleBlock];
     if (do_sample == 2) {
         const int64_t J = J_of(d, n);
         for (int fl = tid; fl < nb; fl += blockDim.x) {
@@ -105,27 +107,64 @@ __global__ __launch_bounds__(256) void k_sample_subchain(tr_desc d, ModeSrc ms, 
         __syncthreads();
     } else if (do_sample) {
         if (cdf_J) {
-            for (int fl = tid; fl < nb; fl += blockDim.x) {
-                const int64_t f = f0 + fl;
-                const int64_t J = J_of(d, n);
-                const uint64_t r = draw_word(ms.seed, t, (uint64_t)f, (uint64_t)n, (uint64_t)stream_tag);
-                const uint64_t W = cdf_J[J - 1];
-                const uint64_t u = mulhi64(r, W);
-                int64_t lo = 0, hi = J - 1;   // first j with cdf_J[j] > u
-                while (lo < hi) {
-                    const int64_t mid = (lo + hi) >> 1;
-                    if (cdf_J[mid] > u) hi = mid; else lo = mid + 1;
+            // A wavefront searches for four samples at once, 64 probes a
+            // sample and round: every lane draws the word of sample l % 4 of
+            // its wavefront, then the probes of all four go out together.
+            // (One thread per sample halving the range is a dependent round
+            // trip per bit of J_n.)
+            const int wv = tid >> 6, l = tid & 63;
+            const int64_t J = J_of(d, n);
+            const int fw = wv + 4 * (l & 3);   // wavefront w: samples w, w + 4, w + 8, w + 12
+            const uint64_t W = cdf_J[J - 1];
+            const uint64_t uw = mulhi64(draw_word(ms.seed, t, (uint64_t)(f0 + fw), (uint64_t)n, (uint64_t)stream_tag), W);
+            uint64_t u[4], before[4], at[4];
+            int64_t lo[4], hi[4];
+            bool more = J > 1;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                u[q] = (uint64_t)__shfl((unsigned long long)uw, q, 64);
+                lo[q] = 0;
+                hi[q] = J - 1;
+                before[q] = 0;
+                at[q] = W;
+            }
+            while (more) {   // uniform: first j with cdf_J[j] > u
+                uint64_t v[4];
+                int64_t step[4];
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    step[q] = (hi[q] - lo[q] + 64) >> 6;
+                    const int64_t pos = lo[q] + (l + 1) * step[q] - 1;
+                    v[q] = cdf_J[pos < hi[q] ? pos : hi[q]];
                 }
-                const uint64_t prev = lo > 0 ? cdf_J[lo - 1] : 0ull;
-                sp[fl * kMaxOrder] = (double)(cdf_J[lo] - prev) / (double)W;
-                int64_t j = lo;
-                for (int q = 0; q < N - 1; ++q) {
-                    const int k = (n + 1 + q) % N;
-                    sidx[fl * kMaxOrder + k] = (int)(j % d.I[k]);
-                    j /= d.I[k];
+                more = false;
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const int64_t pos = lo[q] + (l + 1) * step[q] - 1;
+                    const int below = (int)__popcll(__ballot(pos < hi[q] && v[q] <= u[q]));   // a prefix of the lanes
+                    const uint64_t vb = (uint64_t)__shfl((unsigned long long)v[q], below > 0 ? below - 1 : 0, 64);
+                    const uint64_t va = (uint64_t)__shfl((unsigned long long)v[q], below < 64 ? below : 63, 64);
+                    before[q] = below > 0 ? vb : before[q];
+                    if (lo[q] + (below + 1) * step[q] - 1 < hi[q]) at[q] = va;
+                    lo[q] += below * step[q];
+                    hi[q] = lo[q] + step[q] - 1 < hi[q] ? lo[q] + step[q] - 1 : hi[q];
+                    more = more || lo[q] < hi[q];
                 }
-                sidx[fl * kMaxOrder + n] = -1;
-                sok[fl] = 1;
+            }
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int fl = wv + 4 * q;
+                if (l == q && fl < nb) {
+                    sp[fl * kMaxOrder] = (double)(at[q] - before[q]) / (double)W;
+                    int64_t j = lo[q];
+                    for (int c = 0; c < N - 1; ++c) {
+                        const int k = (n + 1 + c) % N;
+                        sidx[fl * kMaxOrder + k] = (int)(j % d.I[k]);
+                        j /= d.I[k];
+                    }
+                    sidx[fl * kMaxOrder + n] = -1;
+                    sok[fl] = 1;
+                }
             }
         } else if (early_draws) {
             // thread (sample fl, mode k): its draw at chain position q
@@ -198,183 +237,160 @@ __global__ __launch_bounds__(256) void k_sample_subchain(tr_desc d, ModeSrc ms, 
         return;
     }
 
-    // Phase 2: slices of every sample, all loads in flight together.  Thread
-    // w of a pass owns value w of every sample's slices (its slice q, mode k
-    // and offset are the same for all samples), so the loads of the pass
-    // are one per sample at a row taken from LDS: the row is clamped to 0
-    // for a rejected caller index and the value masked afterwards, so no
-    // load sits behind a branch.
-    const int per = soff[N - 1];   // slice values per sample
-    for (int w0 = 0; w0 < per; w0 += 256) {
-        const int w = w0 + tid, wc = w < per ? w : per - 1;
-        int q = 0;
-        while (q + 1 < N - 1 && wc >= soff[q + 1]) ++q;
-        const int k = (n + 1 + q) % N;
-        const int len = soff[q + 1] - soff[q], off = wc - soff[q];
-        const gptr<TC> src = lane_pick_global<TC>(cores.p, k);   // k differs across lanes
-        constexpr int kSB = 16;   // samples per block at most
-        int row[kSB];
-        bool ok[kSB];
-#pragma unroll
-        for (int fl = 0; fl < kSB; ++fl) {   // sample indices clamped into the block's own
-            const int fc = fl < nb ? fl : nb - 1;
-            const int i = sidx[fc * kMaxOrder + k];
-            ok[fl] = sok[fc] != 0;
-            row[fl] = ok[fl] ? i : 0;
-        }
-        TC v[kSB];
-#pragma unroll
-        for (int fl = 0; fl < kSB; ++fl) v[fl] = src[(int64_t)row[fl] * len + off];
-        if (w0 == 0 && do_sample) write_draws();   // while the loads above are in flight
-#pragma unroll
-        for (int fl = 0; fl < kSB; ++fl)
-            if (fl < nb && w < per) sl[(size_t)fl * per + w] = ok[fl] ? v[fl] : TC(0);
-    }
-    __syncthreads();
-
-    // Phase 3: M (R_{n+1} x R_{k+1}, row-major per sample, stride mr^2)
-    // through the chain; slice q of sample fl holds (r, c) at
-    // sl[fl * per + soff[q] + r + R_k c].  The last product goes to S.
-    const size_t P2 = (size_t)mr * mr;
-    TC* bufA = sl + (size_t)SB * per;
-    TC* bufB = bufA + (size_t)SB * P2;
-    if (N == 2) {
-        for (int e = tid; e < nb * RR; e += blockDim.x) {
-            const int fl = e / RR, w = e - fl * RR;
-            const int s = w / Rn, r = w - s * Rn;
-            S[(int64_t)(f0 + fl) * RR + w] = sok[fl] ? sl[(size_t)fl * per + s + Rn1 * r] : TC(NAN);
-        }
-        return;
-    }
     if constexpr (sizeof(TC) == 4) {
-        // FP32: one wavefront per sample (samples wv, wv + 4, ...): M <- M A_q
-        // as a zero-padded 16 x 16 tile on the matrix cores (K = R_k in four
-        // steps of 4); an intermediate M goes back through the wavefront's
-        // LDS tile to become the next A operand.  Operand layouts of
-        // v_mfma_f32_16x16x4_f32 (lane l): A[l % 16][l / 16], B[l / 16][l % 16],
-        // D[4 (l / 16) + j][l % 16].
-        typedef float sf4 __attribute__((ext_vector_type(4)));
-        const int wv = tid >> 6, l = tid & 63, lr = l & 15, lk = l >> 4;
-        // product tiles after the slices (and after the FP64 path's product
-        // buffers, which exist for N > 3 only)
-        float* Mw = reinterpret_cast<float*>(bufA + (N > 3 ? 2 * (size_t)SB * P2 : 0)) + wv * 256;
-        if (N == 3) {
-            // One product per sample, M = A_0 A_1; the wavefront's samples
-            // wv, wv + 4, wv + 8, wv + 12 (SB <= 16) side by side, operands
-            // read at clamped indices and masked.
-            const int k = (n + 2) % N, Rk = d.R[k], Rk1 = d.R[ring_next(k, N)];
-            const int lrA = lr < Rn1 ? lr : Rn1 - 1, lrB = lr < Rk1 ? lr : Rk1 - 1;
-            float a[4][4], b[4][4];
+        // FP32.  Wavefront w takes packs w, w + 4, ... of P samples.
+        using V = typename ChainVec<TC>::V;
+        constexpr int P = 16 / RB, NPK = kSampleBlock / P, PW = (NPK + 3) / 4, UP = sample_packs<TC>(NM), U = UP < PW ? UP : PW;
+        const ChainLane<TC, RB> L;
+        const ChainSlots<TC, NM - 1, VEC> sl(d, n1, N - 1, L);
+        const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+        const bool in0 = L.col < Rn1;
+        bool wrote = !do_sample;
+#pragma unroll 1
+        for (int g = 0; g < PW; g += U) {
+            V v[U][NM - 1];
+            int fl[U], ok[U];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const int fl = wv + 4 * u;
-                const float* base = reinterpret_cast<const float*>(sl) + (size_t)(fl < nb ? fl : 0) * per;
+            for (int u = 0; u < U; ++u) {
+                const int pk = wv + 4 * (g + u);
+                fl[u] = pk * P + L.p;
+                // a sample past the end computes on the block's last one; a rejected
+                // caller index reads slice 0 and gives a row of NaN
+                const int fc = fl[u] < nb ? fl[u] : nb - 1;
+                ok[u] = sok[fc];
+                int k = n1;
 #pragma unroll
-                for (int ks = 0; ks < 4; ++ks) {
-                    const int kk = 4 * ks + lk, kc = kk < Rk ? kk : Rk - 1;
-                    // the masks multiply (a select would become a branch around
-                    // each LDS read); a clamped entry is one of the sample's own
-                    // and feeds the same outputs, so non-finite values propagate
-                    // exactly as with zero padding
-                    const float av = base[lrA + Rn1 * kc], bv = base[soff[1] + kc + Rk * lrB];
-                    a[u][ks] = av * ((lr < Rn1 && kk < Rk) ? 1.f : 0.f);
-                    b[u][ks] = bv * ((kk < Rk && lr < Rk1) ? 1.f : 0.f);
+                for (int q = 0; q < NM - 1; ++q) {
+                    if (q >= N - 1) break;
+                    const int i = ok[u] ? sidx[fc * kMaxOrder + k] : 0;
+                    const uint32_t len = (uint32_t)(d.R[k] * d.R[ring_next(k, N)]) * (uint32_t)sizeof(TC);
+                    v[u][q] = sl.load(cores.p[k], (OT)(uint32_t)i * (OT)len, q);
+                    k = ring_next(k, N);
                 }
             }
-            sf4 acc[4];
+            if (!wrote) write_draws();   // while the loads above are in flight
+            wrote = true;
 #pragma unroll
-            for (int u = 0; u < 4; ++u) acc[u] = sf4{0.f, 0.f, 0.f, 0.f};
+            for (int u = 0; u < U; ++u) {
+                V T = sl.mask(v[u][0], 0);
+                int k = n1;
 #pragma unroll
-            for (int ks = 0; ks < 4; ++ks)
-#pragma unroll
-                for (int u = 0; u < 4; ++u) acc[u] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[u][ks], b[u][ks], acc[u], 0, 0, 0);
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const int fl = wv + 4 * u;
-                if (fl < nb) {   // uniform
-                    const bool ok = sok[fl] != 0;
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) {   // S(f, r + R_n s) = M_f(s, r), s = 4 lk + j, r = lr
-                        const int srow = 4 * lk + j;
-                        if (srow < Rn1 && lr < Rn)
-                            S[(int64_t)(f0 + fl) * RR + lr + Rn * srow] = ok ? (TC)acc[u][j] : TC(NAN);
-                    }
+                for (int q = 1; q < NM - 1; ++q) {
+                    if (q >= N - 1) break;
+                    k = ring_next(k, N);
+                    T = chain_mul(sl.mask(v[u][q], q), T, V{TC(0), TC(0), TC(0), TC(0)});
+                    if (q + 1 < N - 1) T = chain_mask(T, L, in0, d.R[ring_next(k, N)]);
                 }
+                if (fl[u] < nb && in0) {   // S(f, r + R_n s) = M_f(s, r), s = the lane's column, r = its rows
+                    TC* out = S + (int64_t)(f0 + fl[u]) * RR + Rn * L.col;
+#pragma unroll
+                    for (int j = 0; j < 4; ++j)
+                        if (L.on[j] && L.row[j] < Rn) out[L.row[j]] = ok[u] ? T[j] : TC(NAN);
+                }
+            }
+        }
+        return;
+    } else {
+        // chain order n+1, ..., n-1: stage q is mode (n + 1 + q) mod N; its
+        // slice starts at soff[q] within a sample's slices
+        extern __shared__ __align__(16) unsigned char smem_raw[];
+        TC* sl = reinterpret_cast<TC*>(smem_raw);   // slices, then two product buffers
+        __shared__ int soff[kMaxOrder + 1];
+        if (tid == 0) {
+            int o = 0;
+            for (int q = 0; q < N - 1; ++q) {
+                soff[q] = o;
+                const int k = (n + 1 + q) % N;
+                o += d.R[k] * d.R[ring_next(k, N)];
+            }
+            soff[N - 1] = o;
+        }
+        __syncthreads();
+        int mr = 0;   // largest rank: stride of the product buffers
+        for (int k = 0; k < N; ++k) mr = max(mr, d.R[k]);
+        // FP64.  Slices of every sample, all loads in flight together.  Thread
+        // w of a pass owns value w of every sample's slices (its slice q, mode k
+        // and offset are the same for all samples), so the loads of the pass
+        // are one per sample at a row taken from LDS: the row is clamped to 0
+        // for a rejected caller index and the value masked afterwards, so no
+        // load sits behind a branch.
+        const int per = soff[N - 1];   // slice values per sample
+        for (int w0 = 0; w0 < per; w0 += 256) {
+            const int w = w0 + tid, wc = w < per ? w : per - 1;
+            int q = 0;
+            while (q + 1 < N - 1 && wc >= soff[q + 1]) ++q;
+            const int k = (n + 1 + q) % N;
+            const int len = soff[q + 1] - soff[q], off = wc - soff[q];
+            const gptr<TC> src = lane_pick_global<TC>(cores.p, k);   // k differs across lanes
+            constexpr int kSB = 16;   // samples per block at most
+            int row[kSB];
+            bool ok[kSB];
+#pragma unroll
+            for (int fl = 0; fl < kSB; ++fl) {   // sample indices clamped into the block's own
+                const int fc = fl < nb ? fl : nb - 1;
+                const int i = sidx[fc * kMaxOrder + k];
+                ok[fl] = sok[fc] != 0;
+                row[fl] = ok[fl] ? i : 0;
+            }
+            TC v[kSB];
+#pragma unroll
+            for (int fl = 0; fl < kSB; ++fl) v[fl] = src[(int64_t)row[fl] * len + off];
+            if (w0 == 0 && do_sample) write_draws();   // while the loads above are in flight
+#pragma unroll
+            for (int fl = 0; fl < kSB; ++fl)
+                if (fl < nb && w < per) sl[(size_t)fl * per + w] = ok[fl] ? v[fl] : TC(0);
+        }
+        __syncthreads();
+
+        // M (R_{n+1} x R_{k+1}, row-major per sample, stride mr^2)
+        // through the chain; slice q of sample fl holds (r, c) at
+        // sl[fl * per + soff[q] + r + R_k c].  The last product goes to S.
+        const size_t P2 = (size_t)mr * mr;
+        TC* bufA = sl + (size_t)SB * per;
+        TC* bufB = bufA + (size_t)SB * P2;
+        if (N == 2) {
+            for (int e = tid; e < nb * RR; e += blockDim.x) {
+                const int fl = e / RR, w = e - fl * RR;
+                const int s = w / Rn, r = w - s * Rn;
+                S[(int64_t)(f0 + fl) * RR + w] = sok[fl] ? sl[(size_t)fl * per + s + Rn1 * r] : TC(NAN);
             }
             return;
         }
-        for (int fl = wv; fl < nb; fl += (int)(blockDim.x >> 6)) {
-            const float* base = reinterpret_cast<const float*>(sl) + (size_t)fl * per;
-            sf4 mv = {0.f, 0.f, 0.f, 0.f};
-            for (int q = 1; q < N - 1; ++q) {
-                const int k = (n + 1 + q) % N, Rk = d.R[k], Rk1 = d.R[ring_next(k, N)];
-                const float* Aq = base + soff[q];
-                sf4 acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                for (int ks = 0; ks < 4; ++ks) {
-                    const int kk = 4 * ks + lk;
-                    float a;
-                    if (q == 1) a = (lr < Rn1 && kk < Rk) ? base[lr + Rn1 * kk] : 0.f;   // first slice, row lr
-                    else a = Mw[lr * 16 + kk];
-                    const float b = (kk < Rk && lr < Rk1) ? Aq[kk + Rk * lr] : 0.f;
-                    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, acc, 0, 0, 0);
+        const TC* Mc = nullptr;     // current product; null: the first slice
+        int cols = d.R[ring_next(n1, N)];
+        for (int q = 1; q < N - 1; ++q) {
+            const int k = (n + 1 + q) % N, Rk = d.R[k], Rk1 = d.R[ring_next(k, N)];
+            const bool last = q == N - 2;   // then Rk1 == R_n
+            TC* Mo = (q & 1) ? bufA : bufB;
+            for (int e = tid; e < nb * Rn1 * Rk1; e += blockDim.x) {
+                const int fl = e / (Rn1 * Rk1), w = e - fl * (Rn1 * Rk1);
+                const int s = w / Rk1, c = w - s * Rk1;
+                const TC* A = sl + (size_t)fl * per + soff[q];
+                TC acc = TC(0);
+                for (int r = 0; r < Rk; ++r) {
+                    const TC mv = Mc ? Mc[(size_t)fl * P2 + s * cols + r] : sl[(size_t)fl * per + s + Rn1 * r];
+                    acc += mv * A[r + Rk * c];
                 }
-                mv = acc;
-                if (q + 1 < N - 1) {   // D rows 4 lk + j, column lr
-                    __builtin_amdgcn_wave_barrier();
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) Mw[(4 * lk + j) * 16 + lr] = mv[j];
-                    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-                    __builtin_amdgcn_s_waitcnt(0xc07f);
-                    __builtin_amdgcn_wave_barrier();
-                    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-                }
+                if (last)
+                    S[(int64_t)(f0 + fl) * RR + w] = sok[fl] ? acc : TC(NAN);
+                else
+                    Mo[(size_t)fl * P2 + s * Rk1 + c] = acc;
             }
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {   // S(f, r + R_n s) = M_f(s, r), s = 4 lk + j, r = lr
-                const int srow = 4 * lk + j;
-                if (srow < Rn1 && lr < Rn)
-                    S[(int64_t)(f0 + fl) * RR + lr + Rn * srow] = sok[fl] ? (TC)mv[j] : TC(NAN);
-            }
+            if (!last) __syncthreads();
+            Mc = Mo;
+            cols = Rk1;
         }
-        return;
-    }
-    const TC* Mc = nullptr;     // current product; null: the first slice
-    int cols = d.R[ring_next(n1, N)];
-    for (int q = 1; q < N - 1; ++q) {
-        const int k = (n + 1 + q) % N, Rk = d.R[k], Rk1 = d.R[ring_next(k, N)];
-        const bool last = q == N - 2;   // then Rk1 == R_n
-        TC* Mo = (q & 1) ? bufA : bufB;
-        for (int e = tid; e < nb * Rn1 * Rk1; e += blockDim.x) {
-            const int fl = e / (Rn1 * Rk1), w = e - fl * (Rn1 * Rk1);
-            const int s = w / Rk1, c = w - s * Rk1;
-            const TC* A = sl + (size_t)fl * per + soff[q];
-            TC acc = TC(0);
-            for (int r = 0; r < Rk; ++r) {
-                const TC mv = Mc ? Mc[(size_t)fl * P2 + s * cols + r] : sl[(size_t)fl * per + s + Rn1 * r];
-                acc += mv * A[r + Rk * c];
-            }
-            if (last)
-                S[(int64_t)(f0 + fl) * RR + w] = sok[fl] ? acc : TC(NAN);
-            else
-                Mo[(size_t)fl * P2 + s * Rk1 + c] = acc;
-        }
-        if (!last) __syncthreads();
-        Mc = Mo;
-        cols = Rk1;
     }
 }
 
-// Samples per block: the slices of all of them and two product buffers fit
-// in 48 KiB of LDS.
-static int sample_block(const tr_desc& d, const Shape& sh, size_t es, size_t* lds) {
+// FP64: samples per block, so that the slices of all of them and two product
+// buffers fit in 48 KiB of LDS.
+static int sample_block(const tr_desc& d, const Shape& sh, size_t* lds) {
     const size_t per = (size_t)(d.N - 1) * sh.maxR * sh.maxR;
     const size_t prod = d.N > 3 ? 2 * (size_t)sh.maxR * sh.maxR : 0;   // product buffers
-    const size_t need = (per + prod) * es + kMaxOrder * 12 + 4;
-    int SB = (int)((48 * 1024) / need);
-    SB = SB < 1 ? 1 : (SB > 16 ? 16 : SB);   // the kernel's slice loads assume SB <= 16
-    *lds = (size_t)SB * kMaxOrder * 12 + (size_t)((SB + 3) & ~3) * 4 + 16 +
-           ((size_t)SB * per + (size_t)SB * prod) * es + (es == 4 ? 4 * 256 * 4 : 0);   // FP32: product tiles
+    int SB = (int)((48 * 1024) / ((per + prod) * sizeof(double)));
+    SB = SB < 1 ? 1 : (SB > kSampleBlock ? kSampleBlock : SB);
+    *lds = (size_t)SB * (per + prod) * sizeof(double);
     return SB;
 }
 
@@ -392,18 +408,43 @@ hipError_t launch_sample_subchain_mode(const tr_desc& d, ModeSrc ms, int m, CdfP
                                        bool do_subchain, hipStream_t st) {
     if (m <= 0) return hipSuccess;
     const Shape sh = shape_of(d);
-    const size_t es = d.core_dtype == TR_F64 ? 8 : 4;
-    size_t lds = 0;
-    const int SB = sample_block(d, sh, es, &lds);
-    const dim3 grid((unsigned)((m + SB - 1) / SB));
-    if (d.core_dtype == TR_F64)
-        hipLaunchKernelGGL(k_sample_subchain<double>, grid, dim3(256), lds, st, d, ms, m, SB, cdf, cdf_J,
-                           stream_tag, cores, idx, pF, static_cast<double*>(S), sample_mode,
-                           (int)do_subchain);
-    else
-        hipLaunchKernelGGL(k_sample_subchain<float>, grid, dim3(256), lds, st, d, ms, m, SB, cdf, cdf_J,
-                           stream_tag, cores, idx, pF, static_cast<float*>(S), sample_mode,
-                           (int)do_subchain);
+    if (d.core_dtype == TR_F64) {
+        size_t lds = 0;
+        const int SB = sample_block(d, sh, &lds);
+        hipLaunchKernelGGL((k_sample_subchain<double, 16, false, 3, uint32_t>), dim3((unsigned)((m + SB - 1) / SB)),
+                           dim3(256), do_subchain ? lds : 0, st, d, ms, m, SB, cdf, cdf_J, stream_tag, cores, idx, pF,
+                           static_cast<double*>(S), sample_mode, (int)do_subchain);
+        return hipGetLastError();
+    }
+    const dim3 grid((unsigned)((m + kSampleBlock - 1) / kSampleBlock));
+    // 16-byte slice loads need whole pieces at aligned cores; cores of 4 GiB
+    // and more need 64-bit offsets (and take the widest order's form)
+    bool vec = do_subchain, big = false;
+    for (int k = 0; k < d.N; ++k) {
+        vec = vec && d.R[k] % 4 == 0 && (reinterpret_cast<uintptr_t>(cores.p[k]) & 15) == 0;
+        big = big || (int64_t)d.I[k] * d.R[k] * d.R[ring_next(k, d.N)] >= ((int64_t)1 << 30);
+    }
+#define TRK_SMP(RB, VEC, NM, OT)                                                                                    \
+    hipLaunchKernelGGL((k_sample_subchain<float, RB, VEC, NM, OT>), grid, dim3(256), 0, st, d, ms, m, kSampleBlock, \
+                       cdf, cdf_J, stream_tag, cores, idx, pF, static_cast<float*>(S), sample_mode, (int)do_subchain)
+#define TRK_SMP_NM(RB, VEC)                                     \
+    do {                                                        \
+        if (big) TRK_SMP(RB, VEC, kMaxOrder, uint64_t);         \
+        else if (d.N <= 3) TRK_SMP(RB, VEC, 3, uint32_t);       \
+        else if (d.N <= 5) TRK_SMP(RB, VEC, 5, uint32_t);       \
+        else TRK_SMP(RB, VEC, kMaxOrder, uint32_t);             \
+    } while (0)
+#define TRK_SMP_RB(RB)                   \
+    do {                                 \
+        if (vec) TRK_SMP_NM(RB, true);   \
+        else TRK_SMP_NM(RB, false);      \
+    } while (0)
+    if (sh.maxR <= 4) TRK_SMP_RB(4);
+    else if (sh.maxR <= 8) TRK_SMP_RB(8);
+    else TRK_SMP_RB(16);
+#undef TRK_SMP_RB
+#undef TRK_SMP_NM
+#undef TRK_SMP
     return hipGetLastError();
 }
 

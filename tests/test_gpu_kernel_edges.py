@@ -6,7 +6,7 @@ import torch
 
 import tr_inputs as ti
 from gpu_util import DEV, TOL, problem, rel, rounded, say, to_dev, unfold
-from oracle import brsgd, entry
+from oracle import brsgd, entry, sampling
 from paper_2303_16492_amd import _lib as L
 from paper_2303_16492_amd import api
 
@@ -170,3 +170,67 @@ def test_entry_infinity_stays_with_its_entries():
         clean = np.setdiff1d(np.arange(I[k]), idx[~keep][:, k])
         got = grads[k].cpu().numpy()[clean] * B / keep.sum()
         assert rel(got, unfold(gref[k])[clean]) < 1e-5
+
+
+# ranks <= 4, 8, 16 (samples packed 4, 2 and 1 to an operand), whole 16-byte
+# slices or not, orders 2 to 8, rank 1, sample counts around one block of 16
+@pytest.mark.parametrize("I,R", [([5, 6], [4, 4]), ([5, 6], [3, 16]), ([5, 6, 7], [1, 4, 2]), ([5, 6, 7], [8, 4, 8]),
+                                 ([5, 6, 7], [12, 16, 4]), ([5, 6, 7], [7, 1, 8]), ([3, 4, 5, 6], [5, 5, 5, 5]),
+                                 ([3, 4, 5, 6, 2], [13, 2, 16, 9, 1]), ([2, 3, 2, 3, 2, 3], [4, 3, 2, 1, 4, 3]),
+                                 ([2, 3, 2, 3, 2, 3, 2, 3], [8, 4, 8, 8, 4, 8, 8, 8]),
+                                 ([2, 3, 2, 3, 2, 3, 2, 3], [6, 9, 16, 3, 11, 2, 7, 5])])
+def test_subchain_chains_fp32(I, R):
+    N = len(I)
+    cores = [rounded(c, torch.float32) for c in ti.gaussian_cores(12, N, I, R, scale=0.7)]
+    desc = api.make_desc(I, R, torch.float32)
+    dc = [to_dev(unfold(c), torch.float32) for c in cores]
+    rng = np.random.default_rng(2)
+    for n in range(N):
+        for m in (1, 15, 17, 70):
+            idx = np.stack([rng.integers(0, i, m) for i in I], axis=1).astype(np.int32)
+            say("subchain chains", I, R, "mode", n, "m", m)
+            ref = brsgd.subchain_rows(cores, n, idx)
+            mag = brsgd.subchain_rows([np.abs(c) for c in cores], n, idx)
+            bad = np.zeros(m, dtype=bool)
+            inf = np.zeros(m, dtype=bool)
+            k = (n + 1) % N
+            core = dc[k].clone()
+            if m > 2:   # a rejected index: a row of NaN; an infinity: nobody else's
+                bad[m // 2] = True
+                idx[m // 2, (n + N - 1) % N] = I[(n + N - 1) % N]
+                core[0, 0] = float("inf")
+                inf = idx[:, k] == 0
+            S = api.tr_subchain(desc, n, [core if j == k else c for j, c in enumerate(dc)], to_dev(idx, torch.int32),
+                                m).cpu().numpy()
+            ok = ~bad & ~inf
+            assert np.all(np.isnan(S[bad])) and np.all(np.isfinite(S[ok]))
+            # N - 2 products of R_k terms, each term and sum rounded once
+            assert np.all(np.abs(S - ref)[ok] <= (2.0 ** -24 * sum(R) * 2 * mag)[ok])
+
+
+# range ends, one to several rounds of the eight-way and of the 64-way search,
+# laws with nearly all their mass in one entry (first, last or neither)
+@pytest.mark.parametrize("I", [[1, 2, 7], [8, 9, 63], [64, 65, 3], [4097, 5, 512], [70001, 1, 1]])
+@pytest.mark.parametrize("dtype", [torch.float32, torch.float64])
+def test_cdf_draws(I, dtype):
+    N, m = 3, 333
+    desc = api.make_desc(I, [3, 2, 4], dtype)
+    rng = np.random.default_rng(6)
+    for heavy in (None, 0, -1):
+        w = [rng.integers(1, 1 << 20, i).astype(np.uint64) for i in I]
+        if heavy is not None:
+            for v in w:
+                v[heavy] = 1 << 36
+        up = lambda a: torch.from_numpy(np.cumsum(a, dtype=np.uint64).astype(np.int64)).to(DEV)
+        for n in range(N):
+            say("cdf draws", I, "mode", n, "heavy", heavy, dtype)
+            idx, pF = api.tr_sample(desc, 4, 9, n, m, cdf=[up(a) for a in w])
+            iref, pref = sampling.draw(4, 9, n, m, I, w_modes=w)
+            assert np.array_equal(idx.cpu().numpy(), iref) and np.array_equal(pF.cpu().numpy(), pref)
+            J = int(np.prod([s for k, s in enumerate(I) if k != n]))
+            wJ = rng.integers(1, 1 << 12, J).astype(np.uint64)
+            if heavy is not None:
+                wJ[heavy] = 1 << 30
+            idx, pF = api.tr_sample(desc, 4, 9, n, m, cdf_J=up(wJ))
+            iref, pref = sampling.draw(4, 9, n, m, I, w_J=wJ)
+            assert np.array_equal(idx.cpu().numpy(), iref) and np.array_equal(pF.cpu().numpy(), pref)
