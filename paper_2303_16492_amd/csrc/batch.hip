@@ -12,7 +12,7 @@
 //   the sign of the direction folded in) and the step rule on the core.
 // The loss estimate of the step is written in FP64.  The chunk size and the
 // number of wavefronts are template parameters picked by the host tuner.
-#include "internal.hpp"
+#include "chain.hpp"
 
 namespace trk {
 
@@ -21,11 +21,7 @@ typedef _Float16 h8 __attribute__((ext_vector_type(8)));
 
 constexpr int kBatchMaxI = 128;     // I_n
 constexpr int kBatchMaxRR = 160;    // R_n R_{n+1} <= 144, padded to the K step (32)
-constexpr int kBatchRank = 12;      // R_n
-constexpr int kBatchGroup = 16;     // samples whose core slices are staged together
 constexpr int kBatchMaxN = 5;       // order (slices per sample: N - 1)
-// the FP32 slices of a group, each padded to 12 x 12
-constexpr int kBatchSliceFloats = kBatchGroup * (kBatchMaxN - 1) * 12 * 12;
 
 template <int CH>
 struct BatchLds {
@@ -34,9 +30,7 @@ struct BatchLds {
     static constexpr size_t s_off = 0;
     static constexpr size_t t_off = s_off + (size_t)CH * SP * 2;
     static constexpr size_t e_off = t_off + (size_t)kBatchMaxRR * TP * 2;
-    static constexpr size_t c_off = e_off + (size_t)kBatchMaxI * TP * 2;     // staged slices (FP32)
-    static constexpr size_t m_off = c_off + (size_t)kBatchSliceFloats * 4;   // per-wavefront 16 x 16 product tile
-    static constexpr size_t a_off = m_off + (size_t)16 * 256 * 4;           // G_n rows (FP16), pitch SP
+    static constexpr size_t a_off = e_off + (size_t)kBatchMaxI * TP * 2;     // G_n rows (FP16), pitch SP
     static constexpr size_t i_off = a_off + (size_t)kBatchMaxI * SP * 2;     // sample indices [CH][8]
     static constexpr size_t w_off = i_off + (size_t)CH * kMaxOrder * 4;      // weights [CH] float
     static constexpr size_t o_off = w_off + (size_t)CH * 4;                  // fiber offsets [CH] int64
@@ -77,14 +71,12 @@ __global__ __launch_bounds__(64 * WAVES) void k_batch_steps(const tr_batch_item*
     _Float16* sS = reinterpret_cast<_Float16*>(smem_raw + Lz::s_off);
     _Float16* sT = reinterpret_cast<_Float16*>(smem_raw + Lz::t_off);
     _Float16* sE = reinterpret_cast<_Float16*>(smem_raw + Lz::e_off);
-    float* sC = reinterpret_cast<float*>(smem_raw + Lz::c_off);
     _Float16* sA = reinterpret_cast<_Float16*>(smem_raw + Lz::a_off);
-    float* sM = reinterpret_cast<float*>(smem_raw + Lz::m_off);
     int* sidx = reinterpret_cast<int*>(smem_raw + Lz::i_off);
     float* sw = reinterpret_cast<float*>(smem_raw + Lz::w_off);
     int64_t* soff = reinterpret_cast<int64_t*>(smem_raw + Lz::o_off);
     __shared__ double red[WAVES];
-    __shared__ int qoff[kMaxOrder + 1];   // slice offsets of the chain stages within a sample
+    const ChainLane<float, 16> L;
 
     uint64_t t = *it.t_dev;
     const int m = it.m;
@@ -104,16 +96,6 @@ __global__ __launch_bounds__(64 * WAVES) void k_batch_steps(const tr_batch_item*
                 xs[k] = s;
                 s *= d.I[k];
             }
-        }
-        __syncthreads();   // the previous step is done with qoff
-        if (tid == 0) {
-            int o = 0;
-            for (int q = 0; q < N - 1; ++q) {
-                qoff[q] = o;
-                const int k = (n + 1 + q) % N;
-                o += d.R[k] * d.R[ring_next(k, N)];
-            }
-            qoff[N - 1] = o;
         }
         const float* Gn = static_cast<const float*>(it.cores[n]);
         const _Float16* X = static_cast<const _Float16*>(it.Xrep[n]);
@@ -149,7 +131,7 @@ __global__ __launch_bounds__(64 * WAVES) void k_batch_steps(const tr_batch_item*
         }
         for (int f0 = fbeg; f0 < fend; f0 += CH) {
             const int nb = min(CH, m - f0);
-            __syncthreads();   // previous chunk done with S, E, indices; qoff written
+            __syncthreads();   // previous chunk done with S, E, indices
             for (int w = tid; w < nb * (N - 1); w += NT) {
                 const int fl = w / (N - 1), q = w - fl * (N - 1);
                 const int k = (n + 1 + q) % N;
@@ -172,102 +154,59 @@ __global__ __launch_bounds__(64 * WAVES) void k_batch_steps(const tr_batch_item*
                 sw[fl] = ws;
                 soff[fl] = off;
             }
-            // Rows of M_f = G_{n+1}(i) ... G_{n-1}(i), S(f, r + R_n s) = M_f(s, r),
-            // kBatchGroup samples at a time: each slice is staged in LDS
-            // zero-padded to 12 x 12 (element (r, c) at r + 12 c), every load
-            // of the group in flight together; then one thread per (sample,
-            // row s) carries row s of M_f through the chain in registers with
-            // unrolled 12 x 12 products (the padding multiplies zeros).  FP32
-            // throughout, rounded to FP16 once.
-            constexpr int PS = kBatchRank * kBatchRank;                 // padded slice
-            constexpr int PW = (kBatchGroup * (kBatchMaxN - 1) + WAVES - 1) / WAVES;   // slices per wave
-            for (int g0 = 0; g0 < CH; g0 += kBatchGroup) {
-                const int gn = min(kBatchGroup, CH - g0);
-                float v[PW][3];
+            // Rows of M_f = G_{n+1}(i) ... G_{n-1}(i), S(f, r + R_n s) = M_f(s, r):
+            // slice chains on the FP32 matrix cores, in registers (chain.hpp),
+            // rounded to FP16 once.  Wavefront wv takes samples wv, wv + WAVES,
+            // ..., U at a time with all of their slices in flight.  Bound by
+            // the latency of the slice loads; 64 uneven problems, m 1024,
+            // over 4 workgroups each, chunks of 64, 8 wavefronts: 111 us a
+            // launch with the slices staged in LDS and a barrier per group,
+            // 91 so.
+            // (The lane's offsets and masks are formed anew for every chunk:
+            // kept across the products below they would spill.)
+            constexpr int U = WAVES > 4 ? 2 : 4;   // what the registers of the wavefronts hold
+            int k0 = n1;
+            asm volatile("" : "+v"(k0));
+            const ChainSlots<float, kBatchMaxN - 1, false> sl(d, k0, N - 1, L);
+#pragma unroll 1
+            for (int g = wv; g < CH; g += U * WAVES) {
+                ChainVec<float>::V v[U][kBatchMaxN - 1];
 #pragma unroll
-                for (int j = 0; j < PW; ++j) {
-                    const int pr = wv + WAVES * j;                       // (sample, stage) pair
-                    const int fl = pr / (N - 1), q = pr - fl * (N - 1);
-                    int k = n + 1 + q;
-                    k = k >= N ? k - N : k;
-                    k = k >= N ? k - N : k;
-                    const bool ok = pr < gn * (N - 1) && g0 + fl < nb;
-                    const int Rk = d.R[k], Rk1 = d.R[k + 1 == N ? 0 : k + 1];
-                    const float* src = static_cast<const float*>(it.cores[k]) +
-                                       (int64_t)(ok ? sidx[(g0 + fl) * kMaxOrder + k] : 0) * Rk * Rk1;
+                for (int u = 0; u < U; ++u) {
+                    const int f = g + u * WAVES, fc = f < nb ? f : nb - 1;
+                    int k = n1;
 #pragma unroll
-                    for (int u = 0; u < 3; ++u) {
-                        const int pidx = l + 64 * u, r = pidx % kBatchRank, c = pidx / kBatchRank;
-                        v[j][u] = src[(r < Rk ? r : Rk - 1) + Rk * (c < Rk1 ? c : Rk1 - 1)];
-                    }
-#pragma unroll
-                    for (int u = 0; u < 3; ++u) {
-                        const int pidx = l + 64 * u, r = pidx % kBatchRank, c = pidx / kBatchRank;
-                        if (!(ok && pidx < PS && r < Rk && c < Rk1)) v[j][u] = 0.f;
+                    for (int q = 0; q < kBatchMaxN - 1; ++q) {
+                        if (q >= N - 1) break;
+                        const uint32_t len = 4u * (uint32_t)(d.R[k] * d.R[ring_next(k, N)]);
+                        v[u][q] = sl.load(it.cores[k], (uint32_t)sidx[fc * kMaxOrder + k] * len, q);
+                        k = ring_next(k, N);
                     }
                 }
 #pragma unroll
-                for (int j = 0; j < PW; ++j) {
-                    const int pr = wv + WAVES * j;
-                    if (pr < gn * (N - 1)) {
+                for (int u = 0; u < U; ++u) {
+                    const int f = g + u * WAVES;
+                    ChainVec<float>::V T = sl.mask(v[u][0], 0);
+                    int k = n1;
 #pragma unroll
-                        for (int u = 0; u < 3; ++u)
-                            if (l + 64 * u < PS) sC[(size_t)pr * PS + l + 64 * u] = v[j][u];
+                    for (int q = 1; q < kBatchMaxN - 1; ++q) {
+                        if (q >= N - 1) break;
+                        k = ring_next(k, N);
+                        T = chain_mul(sl.mask(v[u][q], q), T, ChainVec<float>::V{0.f, 0.f, 0.f, 0.f});
+                        if (q + 1 < N - 1) T = chain_mask(T, L, L.col < Rn1, d.R[ring_next(k, N)]);
                     }
-                }
-                __syncthreads();
-                // chain products on FP32 matrix cores, one wavefront per
-                // sample: M_q = M_{q-1} A_q as a 16 x 16 (zero-padded) tile,
-                // K = 12 in three steps of 4; M_q goes back through this
-                // wavefront's LDS tile to become the next A operand.
-                float* Mw = sM + wv * 256;   // 16 x 16, row-major
-                for (int fl = wv; fl < gn; fl += WAVES) {
-                    const float* base = sC + (size_t)fl * (N - 1) * PS;
-                    f32x4b m = {0.f, 0.f, 0.f, 0.f};
-                    for (int q = 1; q < N - 1; ++q) {
-                        const float* Aq = base + q * PS;
-                        f32x4b acc = {0.f, 0.f, 0.f, 0.f};
+                    if (L.col < Rn1) {   // s = the lane's column, r = its rows
 #pragma unroll
-                        for (int ks = 0; ks < 3; ++ks) {
-                            const int kk = 4 * ks + lk;   // K index of this lane
-                            // operands read at clamped indices and masked by a factor
-                            // (a select would put each LDS read behind a branch)
-                            const int lrc = lr < kBatchRank ? lr : kBatchRank - 1;
-                            const float msk = lr < kBatchRank ? 1.f : 0.f;
-                            float a;
-                            if (q == 1) a = base[lrc + kBatchRank * kk] * msk;   // slice 0 (row lr)
-                            else a = Mw[lr * 16 + kk];
-                            const float b = Aq[kk + kBatchRank * lrc] * msk;
-                            acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, acc, 0, 0, 0);
-                        }
-                        m = acc;
-                        if (q + 1 < N - 1) {   // D rows 4 lk + j, column lr
-                            __builtin_amdgcn_wave_barrier();
-#pragma unroll
-                            for (int j = 0; j < 4; ++j) Mw[(4 * lk + j) * 16 + lr] = m[j];
-                            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-                            __builtin_amdgcn_s_waitcnt(0xc07f);
-                            __builtin_amdgcn_wave_barrier();
-                            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-                        }
-                    }
-                    const int f = g0 + fl;
-                    if (N == 2) {   // M_f is slice 0
-#pragma unroll
-                        for (int j = 0; j < 4; ++j) m[j] = (4 * lk + j < kBatchRank && lr < kBatchRank)
-                                                               ? base[(4 * lk + j) + kBatchRank * lr] : 0.f;
-                    }
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) {
-                        const int srow = 4 * lk + j, r = lr;   // M_f(srow, r) -> S(f, r + R_n srow)
-                        if (srow < Rn1 && r < Rn) {
-                            const _Float16 h = (_Float16)(f < nb ? m[j] : 0.f);
-                            sS[f * Lz::SP + r + Rn * srow] = h;
-                            sT[(r + Rn * srow) * Lz::TP + f] = h;
+                        for (int j = 0; j < 4; ++j) {
+                            if (L.row[j] < Rn) {
+                                const int c = L.row[j] + Rn * L.col;
+                                const _Float16 h = (_Float16)(f < nb ? T[j] : 0.f);
+                                sS[f * Lz::SP + c] = h;
+                                sT[c * Lz::TP + f] = h;
+                            }
                         }
                     }
                 }
-                __syncthreads();   // slices consumed before the next group overwrites them
             }
             for (int w = tid; w < CH * (kBatchMaxRR - RR); w += NT) {   // K padding of S rows
                 const int fl = w / (kBatchMaxRR - RR), c = RR + w % (kBatchMaxRR - RR);
