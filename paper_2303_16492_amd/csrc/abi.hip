@@ -226,7 +226,7 @@ tr_status tr_dist(const tr_desc* d, int32_t k, int32_t law, const void* core_k, 
     uint64_t* outs[kMaxOrder] = {};
     outs[k] = cdf_k;
     ModeSrc ms{nullptr, 0, k, 0};
-    return hip_status(launch_dist(*d, ms, false, k, law, cores, outs, dev_status, ws, (hipStream_t)stream));
+    return hip_status(launch_dist(*d, ms, kLawCore, k, law, cores, outs, dev_status, ws, (hipStream_t)stream));
 }
 
 size_t tr_dist_optimal_workspace_size(const tr_desc* d, int32_t n) {
@@ -485,9 +485,8 @@ tr_status tr_run_ex(const tr_problem* p, const tr_config* c, uint64_t* t_dev, in
     const StepBump fused = refresh ? StepBump{} : StepBump{t_dev, ctr};
     if (!refresh) e = launch_zero_u32(ctr, 1, st);
     if (refresh)
-        for (int k = 0; k < d.N && e == hipSuccess; ++k)
-            e = launch_dist(d, ModeSrc{nullptr, 0, k, 0}, false, k, c->law, cores, p->cdf, dev_status,
-                            w + L.dist, st);
+        e = launch_dist(d, ModeSrc{nullptr, 0, 0, 0}, kLawEveryMode, 0, c->law, cores, p->cdf, dev_status, w + L.dist,
+                        st);
     // The Gram, its reduction and the inverse use the mode only for R_n R_{n+1}
     // and J_n; when every mode has the same ones they take mode 0 and skip
     // the dependent read of the step counter.
@@ -577,7 +576,7 @@ tr_status tr_run_ex(const tr_problem* p, const tr_config* c, uint64_t* t_dev, in
                                        dev_status, st, fused);
         }
         if (e == hipSuccess && refresh)   // the law's last kernel also advances the step counter
-            e = launch_dist(d, ms, true, 0, c->law, cores, p->cdf, dev_status, w + L.dist, st, t_dev);
+            e = launch_dist(d, ms, kLawStepMode, 0, c->law, cores, p->cdf, dev_status, w + L.dist, st, t_dev);
     }
     return hip_status(e);
 }
@@ -649,8 +648,7 @@ tr_status tr_sweep_run(const tr_problem* p, const tr_sweep_config* c, uint64_t* 
     }
     hipError_t e = hipSuccess;
     if (refresh)
-        for (int k = 0; k < d.N && e == hipSuccess; ++k)
-            e = launch_dist(d, ModeSrc{nullptr, 0, k, 0}, false, k, c->law, live, p->cdf, dev_status, w + L.dist, st);
+        e = launch_dist(d, ModeSrc{nullptr, 0, 0, 0}, kLawEveryMode, 0, c->law, live, p->cdf, dev_status, w + L.dist, st);
     for (int sw = 0; sw < sweeps && e == hipSuccess; ++sw) {
         if (jacobi)   // the iterate every block of this sweep is computed from
             for (int k = 0; k < d.N && e == hipSuccess; ++k)
@@ -685,7 +683,7 @@ tr_status tr_sweep_run(const tr_problem* p, const tr_sweep_config* c, uint64_t* 
             }
             if (e == hipSuccess) e = launch_bump(t_dev, st);
             if (e == hipSuccess && refresh)
-                e = launch_dist(d, ModeSrc{nullptr, 0, n, 0}, false, n, c->law, live, p->cdf, dev_status, w + L.dist,
+                e = launch_dist(d, ModeSrc{nullptr, 0, n, 0}, kLawCore, n, c->law, live, p->cdf, dev_status, w + L.dist,
                                 st);
         }
     }

@@ -11,74 +11,9 @@
 //                              over the J_n columns, FP64.
 // Weights w = floor(p 2^40) + 1 and their inclusive prefix sums are exact
 // integers: the sampler's choice depends only on them.
-#include "internal.hpp"
+#include "law.hpp"
 
 namespace trk {
-
-constexpr double kTwo40 = 1099511627776.0;
-
-typedef double dbl4 __attribute__((ext_vector_type(4)));
-
-// Inclusive scan of a[0..len) (uint64) by one block, in place: each thread
-// scans a contiguous segment, the segment sums are scanned across lanes with
-// shuffles and across wavefronts through LDS, and each segment adds its
-// offset.  Integer sums: the result does not depend on the grouping.
-__device__ inline void block_scan_u64(uint64_t* a, int64_t len) {
-    __shared__ uint64_t wtot[16];
-    const int T = blockDim.x, lane = threadIdx.x & 63, wid = threadIdx.x >> 6, nw = (T + 63) >> 6;
-    const int64_t per = (len + T - 1) / T;
-    const int64_t b = threadIdx.x * per, e = min(len, b + per);
-    uint64_t s = 0;
-    for (int64_t i = b; i < e; ++i) {
-        s += a[i];
-        a[i] = s;
-    }
-    uint64_t incl = s;   // inclusive scan of the segment sums within the wavefront
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const uint64_t y = __shfl_up(incl, (unsigned)o, 64);
-        if (lane >= o) incl += y;
-    }
-    if (lane == 63) wtot[wid] = incl;
-    __syncthreads();
-    if (wid == 0) {   // exclusive scan of the wavefront totals
-        const uint64_t v = lane < nw ? wtot[lane] : 0ull;
-        uint64_t x = v;
-#pragma unroll
-        for (int o = 1; o < 16; o <<= 1) {
-            const uint64_t y = __shfl_up(x, (unsigned)o, 64);
-            if (lane >= o) x += y;
-        }
-        if (lane < nw) wtot[lane] = x - v;
-    }
-    __syncthreads();
-    const uint64_t off = wtot[wid] + incl - s;
-    for (int64_t i = b; i < e; ++i) a[i] += off;
-    __syncthreads();
-}
-
-__device__ inline uint64_t quantize(double p) { return (uint64_t)floor(p * kTwo40) + 1ull; }
-
-__device__ inline void write_uniform_weights(uint64_t* w, int64_t len) {
-    const uint64_t wu = quantize(1.0 / (double)len);
-    for (int64_t i = threadIdx.x; i < len; i += blockDim.x) w[i] = wu;
-    __syncthreads();
-}
-
-// Weights staged in LDS when every core has at most this many rows (the
-// launch then passes lds_rows = max I_k, else 0).
-constexpr int kLdsRows = 8192;
-constexpr int kLevLdsRows = 4096;
-
-// w (Ik weights, in LDS or global memory) -> inclusive CDF in cdf; the
-// step counter advances afterwards when ``bump`` is set (every thread of
-// the block read it before the block's first barrier).
-__device__ inline void finish_cdf(uint64_t* w, uint64_t* cdf, int Ik, uint64_t* bump) {
-    block_scan_u64(w, Ik);
-    if (w != cdf)
-        for (int i = threadIdx.x; i < Ik; i += blockDim.x) cdf[i] = w[i];
-    if (bump && threadIdx.x == 0) atomicAdd(reinterpret_cast<unsigned long long*>(bump), 1ull);
-}
 
 // Euclidean law of core k in two launches: the row norms ||g_i||^2 across
 // the GPU (a wavefront takes four rows, its lanes across the row, coalesced,
@@ -86,46 +21,56 @@ __device__ inline void finish_cdf(uint64_t* w, uint64_t* cdf, int Ik, uint64_t* 
 // total, weights, CDF and (inside a step) the counter advance in one block.
 constexpr int kEucRows = 16;
 
+// Norms of rows i0 to i0 + NR - 1 (NR a power of two) by one wavefront, NP passes
+// of 64 columns.
+template <int NR, int NP, typename TC>
+__device__ __forceinline__ void euc_rows(const TC* __restrict__ G, int Ik, int RR, int i0, double* rn) {
+    const int lane = threadIdx.x & 63;
+    if (i0 >= Ik) return;
+    double s[NR];
+#pragma unroll
+    for (int r = 0; r < NR; ++r) {
+        const int i = i0 + r < Ik ? i0 + r : Ik - 1;
+        s[r] = 0.0;
+#pragma unroll
+        for (int pa = 0; pa < NP; ++pa) {
+            const int c = lane + 64 * pa;
+            const double v = (double)G[(int64_t)i * RR + (c < RR ? c : RR - 1)];
+            s[r] += c < RR ? v * v : 0.0;
+        }
+    }
+    // The tree of wave_sum for all rows at once: a lane keeps half of its rows
+    // and hands the other half over at each of the first log2(NR) levels (a
+    // full tree per row is 6 exchanges a row, NR + 2 to NR + 5 here).
+    int o = 32;
+#pragma unroll
+    for (int h = NR / 2; h >= 1; h >>= 1, o >>= 1) {
+        const bool up = lane & o;
+#pragma unroll
+        for (int r = 0; r < h; ++r) {
+            const double keep = up ? s[r + h] : s[r], give = up ? s[r] : s[r + h];
+            s[r] = keep + __shfl_xor(give, o, 64);
+        }
+    }
+#pragma unroll
+    for (; o >= 1; o >>= 1) s[0] += __shfl_xor(s[0], o, 64);
+    const int r = lane / (64 / NR);
+    if (lane % (64 / NR) == 0 && i0 + r < Ik) rn[i0 + r] = s[0];
+}
+
 template <typename TC>
 __global__ __launch_bounds__(256) void k_euc_rows(tr_desc d, ModeSrc ms, int use_mode, int k_fixed, Ptrs cores,
                                                   double* __restrict__ rn) {
     uint64_t t;
     int k = k_fixed;
     if (use_mode) resolve_mode(ms, d.N, &t, &k);
-    const int Ik = d.I[k];
-    const int RR = d.R[k] * d.R[ring_next(k, d.N)];
-    const int i0 = blockIdx.x * kEucRows + 4 * (threadIdx.x >> 6), lane = threadIdx.x & 63;
-    if (i0 >= Ik) return;
-    const TC* G = static_cast<const TC*>(cores.p[k]);
-    double s[4];
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-        const int i = i0 + r < Ik ? i0 + r : Ik - 1;
-        s[r] = 0.0;
-#pragma unroll
-        for (int pa = 0; pa < 4; ++pa) {
-            const int c = lane + 64 * pa;
-            const double v = (double)G[(int64_t)i * RR + (c < RR ? c : RR - 1)];
-            s[r] += c < RR ? v * v : 0.0;
-        }
-    }
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-        const double tr = wave_sum(s[r]);
-        if (lane == 0 && i0 + r < Ik) rn[i0 + r] = tr;
-    }
+    euc_rows<4, 4>(static_cast<const TC*>(cores.p[k]), d.I[k], d.R[k] * d.R[ring_next(k, d.N)],
+                   blockIdx.x * kEucRows + 4 * (threadIdx.x >> 6), rn);
 }
 
-__global__ __launch_bounds__(1024) void k_euc_cdf(tr_desc d, ModeSrc ms, int use_mode, int k_fixed,
-                                                  const double* __restrict__ rn, MutPtrs cdf_out, int32_t* status,
-                                                  uint64_t* bump, int lds_rows) {
-    uint64_t t;
-    int k = k_fixed;
-    if (use_mode) resolve_mode(ms, d.N, &t, &k);
-    const int Ik = d.I[k];
-    uint64_t* cdf = static_cast<uint64_t*>(cdf_out.p[k]);
-    extern __shared__ __align__(16) unsigned char smem_raw[];
-    uint64_t* w = Ik <= lds_rows ? reinterpret_cast<uint64_t*>(smem_raw) : cdf;
+// Total, weights and CDF from the row norms.
+__device__ __forceinline__ void euc_cdf_block(const double* rn, uint64_t* w, uint64_t* cdf, int Ik, int32_t* status,
+                                              uint64_t* bump) {
     double loc = 0.0;
     for (int i = threadIdx.x; i < Ik; i += blockDim.x) loc += rn[i];
     __shared__ double red[16];
@@ -140,347 +85,87 @@ __global__ __launch_bounds__(1024) void k_euc_cdf(tr_desc d, ModeSrc ms, int use
     finish_cdf(w, cdf, Ik, bump);
 }
 
-// ----------------------------------------------------- rank-revealing law --
-//
-// Leverage law of a core whose unfolding may be rank deficient (Lemma
-// lev_est divides the scores of Definition "Leverage Scores" by the rank):
-// Cholesky with diagonal pivoting on the Gram B = G^T G of G = G_{k(2)}
-// (the largest remaining pivot first), stopped once no remaining pivot
-// exceeds RR 2^-52 max_i B_ii; r = the steps taken is the rank.  The chosen
-// columns P of G span its column space, so with L the r x r factor of B_PP
-//     l_i = g_i[P]^T (G_P^T G_P)^{-1} g_i[P] = ||L^{-1} g_i[P]||^2,
-// and r = I_k (full row rank, possible only when I_k <= RR) gives l_i = 1.
-// One block of 1024 threads.  Bm: RR x RR doubles of device scratch
-// (row-major) holding G^T G on entry, overwritten.  Writes the weights
-// floor(l_i / r 2^40) + 1 into w (r = 0, a zero core: the uniform law and
-// TR_DEV_ZERO_DIST).
-// Pivot test that sends the fast path here: 2^-43 of the largest diagonal
-// entry, a few times the rounding of a Gram summed over a few hundred rows
-// (so a pivot of a dependent column is caught) while an ill-conditioned core
-// of full rank (sigma_min / sigma_max above about 3.4e-7) stays on the fast
-// path; both Gram routes carry the same kappa^2 u error on such a core.
-constexpr double kLevTrigger = 1.0 / 8796093022208.0;
-
-template <typename TC>
-__device__ void leverage_pivoted(const TC* __restrict__ G, int Ik, int RR, double* __restrict__ Bm,
-                                 uint64_t* __restrict__ w, int32_t* status) {
-    __shared__ int perm[kMaxRR];
-    __shared__ double dinv[kMaxRR];
-    __shared__ double xw[8][kMaxRR];   // rows are scored by the first eight wavefronts
-    __shared__ double rv[16];
-    __shared__ int ri[16];
-    __shared__ double red[16];
-    const int tid = threadIdx.x, T = blockDim.x, lane = tid & 63, wid = tid >> 6, nw = T >> 6;
-    const int nB = RR;
-    for (int i = tid; i < nB; i += T) perm[i] = i;
-    __syncthreads();
-    double mx = 0.0;
-    for (int i = tid; i < nB; i += T) mx = fmax(mx, Bm[(int64_t)i * nB + i]);
-    for (int o = 32; o > 0; o >>= 1) mx = fmax(mx, __shfl_xor(mx, o, 64));
-    if (lane == 0) red[wid] = mx;
-    __syncthreads();
-    mx = 0.0;
-    for (int q = 0; q < nw; ++q) mx = fmax(mx, red[q]);
-    const double tol = (double)nB * 2.220446049250313e-16 * mx;
-    int r = 0;
-    for (int j = 0; j < nB; ++j) {
-        // largest remaining pivot (ties: the smallest index)
-        double bv = -1.0;
-        int bi = nB;
-        for (int i = j + tid; i < nB; i += T) {
-            const double v = Bm[(int64_t)i * nB + i];
-            if (v > bv) { bv = v; bi = i; }
-        }
-        for (int o = 32; o > 0; o >>= 1) {
-            const double ov = __shfl_xor(bv, o, 64);
-            const int oi = __shfl_xor(bi, o, 64);
-            if (ov > bv || (ov == bv && oi < bi)) { bv = ov; bi = oi; }
-        }
-        if (lane == 0) { rv[wid] = bv; ri[wid] = bi; }
-        __syncthreads();
-        bv = rv[0];
-        bi = ri[0];
-        for (int q = 1; q < nw; ++q)
-            if (rv[q] > bv || (rv[q] == bv && ri[q] < bi)) { bv = rv[q]; bi = ri[q]; }
-        __syncthreads();
-        if (!(bv > tol) || !isfinite(bv)) break;   // the same verdict in every thread
-        r = j + 1;
-        if (bi != j) {   // symmetric exchange of j and bi: rows (all columns), then columns of the trailing rows
-            for (int c = tid; c < nB; c += T) {
-                const double a = Bm[(int64_t)j * nB + c];
-                Bm[(int64_t)j * nB + c] = Bm[(int64_t)bi * nB + c];
-                Bm[(int64_t)bi * nB + c] = a;
-            }
-            __syncthreads();
-            for (int i = j + tid; i < nB; i += T) {
-                const double a = Bm[(int64_t)i * nB + j];
-                Bm[(int64_t)i * nB + j] = Bm[(int64_t)i * nB + bi];
-                Bm[(int64_t)i * nB + bi] = a;
-            }
-            if (tid == 0) {
-                const int a = perm[j];
-                perm[j] = perm[bi];
-                perm[bi] = a;
-            }
-            __syncthreads();
-        }
-        const double ljj = sqrt(Bm[(int64_t)j * nB + j]);
-        __syncthreads();
-        for (int i = j + 1 + tid; i < nB; i += T) Bm[(int64_t)i * nB + j] /= ljj;
-        if (tid == 0) Bm[(int64_t)j * nB + j] = ljj;
-        __syncthreads();
-        const int wd = nB - j - 1;
-        for (int e = tid; e < wd * wd; e += T) {
-            const int i = j + 1 + e / wd, c = j + 1 + e % wd;
-            Bm[(int64_t)i * nB + c] -= Bm[(int64_t)i * nB + j] * Bm[(int64_t)c * nB + j];
-        }
-        __syncthreads();
-    }
-    if (r == 0 || r == Ik) {   // zero core, or full row rank: every score 0 or 1
-        if (r == 0 && tid == 0) set_status(status, TR_DEV_ZERO_DIST);
-        write_uniform_weights(w, Ik);
-        return;
-    }
-    // L^{-1}: column c by thread c; its diagonal in dinv, the rest in the
-    // free upper triangle (entry (jj, c) of L^{-1} at Bm[c][jj]).
-    for (int c = tid; c < r; c += T) {
-        const double yc = 1.0 / Bm[(int64_t)c * nB + c];
-        dinv[c] = yc;
-        for (int jj = c + 1; jj < r; ++jj) {
-            double acc = Bm[(int64_t)jj * nB + c] * yc;
-            for (int k = c + 1; k < jj; ++k) acc += Bm[(int64_t)jj * nB + k] * Bm[(int64_t)c * nB + k];
-            Bm[(int64_t)c * nB + jj] = -acc / Bm[(int64_t)jj * nB + jj];
-        }
-    }
-    __syncthreads();
-    // l_i, one row per wavefront: x = g_i[P] staged in LDS, then z = L^{-1} x
-    // with the lanes over the entries of z.
-    double* x = xw[wid & 7];
-    for (int i = wid; i < Ik && wid < 8; i += 8) {
-        for (int c = lane; c < r; c += 64) x[c] = (double)G[(int64_t)i * RR + perm[c]];
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        double acc = 0.0;
-        for (int jj = lane; jj < r; jj += 64) {
-            double z = dinv[jj] * x[jj];
-            for (int c = 0; c < jj; ++c) z += Bm[(int64_t)c * nB + jj] * x[c];
-            acc += z * z;
-        }
-        acc = wave_sum(acc);
-        if (lane == 0) w[i] = quantize(acc / (double)r);
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    }
-    __syncthreads();
-}
-
-// Leverage law of core k in four launches across the GPU: the
-// FP64 Gram of G_{k(2)} (the sampled-Gram kernels on the core's own rows),
-// -(G^T G)^{-1} by the one-workgroup sweep, then
-//     l_i = g_i^T (G^T G)^{-1} g_i = -g_i . (g_i (-(G^T G)^{-1}))
-// for every row on the FP64 matrix cores, then the weights, CDF and
-// (inside a step) the counter advance in one block.
-
-constexpr int kLevRows = 16;
-
-// l_i for 16 rows per block: wavefront w owns output columns 16 n.., n = w,
-// w + 4, ... (K = RR <= RB in steps of 4), each lane's partial dot products
-// are added across its 16 lanes, then across the four wavefronts in a fixed
-// order.  Loads at clamped indices, masked afterwards; up to RB = 128 both
-// column blocks' loads are in flight together, above it one block's.
-template <typename TC, int RB>
-__global__ __launch_bounds__(256) void k_lev_rows(tr_desc d, ModeSrc ms, int use_mode, int k_fixed, Ptrs cores,
-                                                  const double* __restrict__ hm, double* __restrict__ lev) {
-    uint64_t t;
-    int k = k_fixed;
-    if (use_mode) resolve_mode(ms, d.N, &t, &k);
-    const int Ik = d.I[k];
-    const int RR = d.R[k] * d.R[ring_next(k, d.N)];
-    const int r0 = blockIdx.x * kLevRows;
-    if (r0 >= Ik) return;
-    const TC* G = static_cast<const TC*>(cores.p[k]);
-    const int tid = threadIdx.x, l = tid & 63, lr = l & 15, lk = l >> 4, w = tid >> 6;
-    constexpr int KS = RB / 4, U = RB <= 128 ? RB / 64 : 1;
-    const int row = r0 + lr, rowc = row < Ik ? row : Ik - 1;
-    TC ga[KS];
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) {
-        const int kk = 4 * ks + lk, kc = kk < RR ? kk : RR - 1;
-        ga[ks] = TC(0);
-        if (4 * ks < RR) ga[ks] = G[(int64_t)rowc * RR + kc];   // uniform
-    }
-    double part[4] = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll 1
-    for (int u0 = 0; u0 < RB / 64; u0 += U) {
-        if (16 * (w + 4 * u0) >= RR) break;   // uniform
-        double hb[U][KS];
-        TC gd[U][4];   // G[r0 + 4 j + lk][c], the entries this lane's outputs pair with
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks) {
-            const int kk = 4 * ks + lk, kc = kk < RR ? kk : RR - 1;
-            if (4 * ks < RR) {   // uniform
-#pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    const int c = 16 * (w + 4 * (u0 + u)) + lr, cc = c < RR ? c : RR - 1;
-                    hb[u][ks] = hm[(int64_t)kc * RR + cc];
-                }
-            }
-        }
-#pragma unroll
-        for (int u = 0; u < U; ++u)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int r = r0 + 4 * j + lk, rc = r < Ik ? r : Ik - 1;
-                const int c = 16 * (w + 4 * (u0 + u)) + lr, cc = c < RR ? c : RR - 1;
-                gd[u][j] = G[(int64_t)rc * RR + cc];
-            }
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int c = 16 * (w + 4 * (u0 + u)) + lr;
-            dbl4 acc = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-            for (int ks = 0; ks < KS; ++ks)
-                if (4 * ks < RR) {
-                    const int kk = 4 * ks + lk;
-                    const double a = (row < Ik && kk < RR) ? (double)ga[ks] : 0.0;
-                    const double b = (kk < RR && c < RR) ? hb[u][ks] : 0.0;
-                    acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, acc, 0, 0, 0);
-                }
-#pragma unroll
-            for (int j = 0; j < 4; ++j) part[j] += c < RR ? (double)gd[u][j] * acc[j] : 0.0;
-        }
-    }
-    __shared__ double sp[4][kLevRows];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        double v = part[j];
-#pragma unroll
-        for (int o = 1; o < 16; o <<= 1) v += __shfl_xor(v, o, 64);   // the 16 lanes of one row
-        if (lr == 0) sp[w][4 * j + lk] = v;
-    }
-    __syncthreads();
-    if (tid < kLevRows && r0 + tid < Ik)
-        lev[r0 + tid] = -(((sp[0][tid] + sp[1][tid]) + sp[2][tid]) + sp[3][tid]);
-}
-
-// Weights floor(l_i / RR 2^40) + 1 and their CDF (one block).  When the
-// sweep found a pivot at or below 2^-43 max_i h_ii (the Gram is singular or
-// close to it), or when I_k <= RR, the scores come from the rank-revealing
-// route instead (it overwrites the Gram ``gram``).
-template <typename TC>
-__global__ __launch_bounds__(1024) void k_lev_cdf(tr_desc d, ModeSrc ms, int use_mode, int k_fixed, Ptrs cores,
-                                                  double* __restrict__ gram, const double* __restrict__ lev,
-                                                  const int* __restrict__ flag, MutPtrs cdf_out, int32_t* status,
+__global__ __launch_bounds__(1024) void k_euc_cdf(tr_desc d, ModeSrc ms, int use_mode, int k_fixed,
+                                                  const double* __restrict__ rn, MutPtrs cdf_out, int32_t* status,
                                                   uint64_t* bump, int lds_rows) {
     uint64_t t;
     int k = k_fixed;
     if (use_mode) resolve_mode(ms, d.N, &t, &k);
     const int Ik = d.I[k];
-    const int RR = d.R[k] * d.R[ring_next(k, d.N)];
     uint64_t* cdf = static_cast<uint64_t*>(cdf_out.p[k]);
     extern __shared__ __align__(16) unsigned char smem_raw[];
-    uint64_t* w = Ik <= lds_rows ? reinterpret_cast<uint64_t*>(smem_raw) : cdf;
-    if (Ik <= RR || *flag != 0) {
-        leverage_pivoted(static_cast<const TC*>(cores.p[k]), Ik, RR, gram, w, status);
-    } else {
-        for (int i = threadIdx.x; i < Ik; i += blockDim.x) w[i] = quantize(lev[i] / (double)RR);
-        __syncthreads();
-    }
-    finish_cdf(w, cdf, Ik, bump);
-}
-
-struct LevWs {
-    GramWs g;
-    size_t gram_off, upd_off, lev_off, total;
-    UpdWs u;
-};
-
-static LevWs lev_ws_layout(const tr_desc& d) {
-    const Shape sh = shape_of(d);
-    LevWs L{};
-    L.g = gram_ws_layout(d, sh.maxI);
-    L.gram_off = L.g.total;
-    L.upd_off = L.gram_off + align_up((size_t)sh.maxRR * sh.maxRR * 8);
-    L.u = UpdWs{};
-    L.u.L_off = 0;
-    L.u.flag_off = align_up((size_t)sh.maxRR * sh.maxRR * 8);
-    L.u.total = L.u.flag_off + 256;
-    L.lev_off = L.upd_off + L.u.total;
-    L.total = L.lev_off + align_up((size_t)sh.maxI * 8);
-    return L;
+    euc_cdf_block(rn, Ik <= lds_rows ? reinterpret_cast<uint64_t*>(smem_raw) : cdf, cdf, Ik, status, bump);
 }
 
 size_t dist_ws_bytes(const tr_desc& d, int law) {
     const Shape sh = shape_of(d);
     if (law == TR_LAW_EUCLID) return align_up((size_t)sh.maxI * 8);   // row norms
     if (law != TR_LAW_LEVERAGE) return 256;
-    return lev_ws_layout(d).total;
+    return lev_ws_bytes(d);
 }
 
-hipError_t launch_dist(const tr_desc& d, ModeSrc ms, bool use_mode, int k, int law, Ptrs cores,
+// The Euclidean law in one launch: the same row norms (in the same order),
+// total, weights and CDF by one block, everything after the loads in LDS.
+// Taken when every core's rows are one round of the block: there it saves a
+// launch, past it the exchanges of the row sums on one CU cost more than that
+// (five refreshes and three first ones per pass, whole pass in us, two launches
+// against one: 64^3 ranks 10 186, 173; 128^3 ranks 10 188, 182; 160^3 ranks 5 154, 177).
+constexpr int kEucSmallRows = 128;
+
+template <typename TC>
+__global__ __launch_bounds__(1024) void k_euc_small(tr_desc d, ModeSrc ms, int mode_src, int k_fixed, Ptrs cores,
+                                                    MutPtrs cdf_out, int32_t* status, uint64_t* bump) {
+    uint64_t t;
+    int k = mode_src == kLawEveryMode ? (int)blockIdx.x : k_fixed;
+    if (mode_src == kLawStepMode) resolve_mode(ms, d.N, &t, &k);
+    const int Ik = d.I[k], RR = d.R[k] * d.R[ring_next(k, d.N)];
+    __shared__ double rn[kEucSmallRows];
+    __shared__ uint64_t w[kEucSmallRows];
+    const TC* G = static_cast<const TC*>(cores.p[k]);
+    const int i0 = 8 * (threadIdx.x >> 6);   // 16 wavefronts, eight rows each, 8 to 32 loads a lane in flight
+    if (RR <= 64) euc_rows<8, 1>(G, Ik, RR, i0, rn);
+    else if (RR <= 128) euc_rows<8, 2>(G, Ik, RR, i0, rn);
+    else euc_rows<8, 4>(G, Ik, RR, i0, rn);
+    __syncthreads();
+    euc_cdf_block(rn, w, static_cast<uint64_t*>(cdf_out.p[k]), Ik, status, bump);
+}
+
+hipError_t launch_dist(const tr_desc& d, ModeSrc ms, int mode_src, int k, int law, Ptrs cores,
                        uint64_t* const* cdf_out, int32_t* status, void* ws, hipStream_t st, uint64_t* bump) {
     MutPtrs out{};
     for (int q = 0; q < d.N; ++q) out.p[q] = cdf_out[q];
+    if (law == TR_LAW_LEVERAGE) return launch_leverage(d, ms, mode_src, k, cores, out, status, ws, st, bump);
+    if (law != TR_LAW_EUCLID) return hipErrorInvalidValue;
     const bool f64 = d.core_dtype == TR_F64;
     const Shape sh = shape_of(d);
+    if (sh.maxI <= kEucSmallRows) {
+        const dim3 grid(mode_src == kLawEveryMode ? d.N : 1);
+        if (f64)
+            hipLaunchKernelGGL(k_euc_small<double>, grid, dim3(1024), 0, st, d, ms, mode_src, k,
+                               cores, out, status, bump);
+        else
+            hipLaunchKernelGGL(k_euc_small<float>, grid, dim3(1024), 0, st, d, ms, mode_src, k,
+                               cores, out, status, bump);
+        return hipGetLastError();
+    }
+    const int first = mode_src == kLawEveryMode ? 0 : k, last = mode_src == kLawEveryMode ? d.N : k + 1;
+    const int use_mode = mode_src == kLawStepMode;
     const int lds_rows = sh.maxI <= kLdsRows ? sh.maxI : 0;
     const size_t lds = (size_t)lds_rows * 8;
-    if (law == TR_LAW_EUCLID) {
-        double* rn = static_cast<double*>(ws);
-        const dim3 grid((sh.maxI + kEucRows - 1) / kEucRows);
+    double* rn = static_cast<double*>(ws);
+    const dim3 grid((sh.maxI + kEucRows - 1) / kEucRows);
+    for (int q = first; q < last; ++q) {
         if (f64)
-            hipLaunchKernelGGL(k_euc_rows<double>, grid, dim3(256), 0, st, d, ms, (int)use_mode, k, cores, rn);
+            hipLaunchKernelGGL(k_euc_rows<double>, grid, dim3(256), 0, st, d, ms, use_mode, q, cores, rn);
         else
-            hipLaunchKernelGGL(k_euc_rows<float>, grid, dim3(256), 0, st, d, ms, (int)use_mode, k, cores, rn);
+            hipLaunchKernelGGL(k_euc_rows<float>, grid, dim3(256), 0, st, d, ms, use_mode, q, cores, rn);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(k_euc_cdf, dim3(1), dim3(1024), lds, st, d, ms, (int)use_mode, k, rn, out, status, bump,
+        hipLaunchKernelGGL(k_euc_cdf, dim3(1), dim3(1024), lds, st, d, ms, use_mode, q, rn, out, status, bump,
                            lds_rows);
-    } else if (law == TR_LAW_LEVERAGE) {
-        // the mode source of the Gram, the inverse and the scores: the step's
-        // mode, or core k
-        const ModeSrc mk = use_mode ? ms : ModeSrc{nullptr, 0, k, 0};
-        const LevWs L = lev_ws_layout(d);
-        char* w = static_cast<char*>(ws);
-        double* gram = reinterpret_cast<double*>(w + L.gram_off);
-        hipError_t e = launch_gram(d, mk, nullptr, nullptr, sh.maxI, gram, w, L.g, st, nullptr, cores);
-        if (e != hipSuccess) return e;
-        // no status from the inverse and no damping ladder: a pivot at or
-        // below 2^-43 of the largest diagonal entry sends the CDF kernel to
-        // the rank-revealing route
-        e = launch_sweep_inverse(d, mk, gram, 0.0, L.u, w + L.upd_off, nullptr, st, kLevTrigger);
-        if (e != hipSuccess) return e;
-        const double* hm = reinterpret_cast<const double*>(w + L.upd_off + L.u.L_off);
-        const int* flag = reinterpret_cast<const int*>(w + L.upd_off + L.u.flag_off);
-        double* lev = reinterpret_cast<double*>(w + L.lev_off);
-        const dim3 grid((sh.maxI + kLevRows - 1) / kLevRows);
-        // the CDF kernel's static LDS (rank-revealing route, about 20 KB)
-        // plus the staged weights stay within 64 KB
-        const int lev_lds_rows = sh.maxI <= kLevLdsRows ? sh.maxI : 0;
-        const size_t lev_lds = (size_t)lev_lds_rows * 8;
-#define TRK_LEV_ROWS(TC, RB) \
-    hipLaunchKernelGGL((k_lev_rows<TC, RB>), grid, dim3(256), 0, st, d, ms, (int)use_mode, k, cores, hm, lev)
-        if (f64) {
-            if (sh.maxRR <= 128) TRK_LEV_ROWS(double, 128);
-            else TRK_LEV_ROWS(double, 256);
-        } else {
-            if (sh.maxRR <= 128) TRK_LEV_ROWS(float, 128);
-            else TRK_LEV_ROWS(float, 256);
-        }
-#undef TRK_LEV_ROWS
         if ((e = hipGetLastError()) != hipSuccess) return e;
-        if (f64)
-            hipLaunchKernelGGL(k_lev_cdf<double>, dim3(1), dim3(1024), lev_lds, st, d, ms, (int)use_mode, k, cores,
-                               gram, lev, flag, out, status, bump, lev_lds_rows);
-        else
-            hipLaunchKernelGGL(k_lev_cdf<float>, dim3(1), dim3(1024), lev_lds, st, d, ms, (int)use_mode, k, cores,
-                               gram, lev, flag, out, status, bump, lev_lds_rows);
-    } else {
-        return hipErrorInvalidValue;
     }
-    return hipGetLastError();
+    return hipSuccess;
 }
 
 // -------------------------------------------------------------- optimal --

@@ -171,11 +171,19 @@ __global__ __launch_bounds__(256) void k_gram_partial(tr_desc d, ModeSrc ms, con
     uint64_t t;
     int n;
     resolve_mode(ms, d.N, &t, &n);
-    const int RR = d.R[n] * d.R[ring_next(n, d.N)];
-    // S null: the rows are those of G_{n(2)} itself (I_n of them), unweighted
+    int RR = d.R[n] * d.R[ring_next(n, d.N)];   // columns of the result
+    int64_t sf = RR, sc = 1;                    // entry (f, c) at f sf + c sc
+    // S null: the rows are those of G_{n(2)} itself (I_n of them), unweighted,
+    // or its columns where there are no fewer of them
     if (!S) {
         S = static_cast<const TC*>(rows.p[n]);
         m = d.I[n];
+        if (m <= RR) {
+            m = RR;
+            RR = d.I[n];
+            sf = 1;
+            sc = m;
+        }
     }
     const int tpd = (RR + kGramT - 1) / kGramT;
     int tile, grp;
@@ -223,8 +231,8 @@ __global__ __launch_bounds__(256) void k_gram_partial(tr_desc d, ModeSrc ms, con
 #pragma unroll
             for (int v = h * VH; v < (h + 1) * VH; ++v) {
                 const int f = f0 + fo + 8 * v, fr = f < fe ? f : fe - 1;
-                av[v] = S[(int64_t)fr * RR + cA];
-                bv[v] = S[(int64_t)fr * RR + cB];
+                av[v] = S[fr * sf + cA * sc];
+                bv[v] = S[fr * sf + cB * sc];
             }
             __builtin_amdgcn_sched_barrier(0);
         }
@@ -260,11 +268,12 @@ __global__ __launch_bounds__(256) void k_gram_partial(tr_desc d, ModeSrc ms, con
 // gram = sum of the group partials in group order; entries above the
 // diagonal come from their mirror (only lower tiles are computed).
 __global__ void k_gram_reduce(tr_desc d, ModeSrc ms, const double* __restrict__ part, int groups, int maxRR2,
-                              double* __restrict__ gram) {
+                              int core_rows, double* __restrict__ gram) {
     uint64_t t;
     int n;
     resolve_mode(ms, d.N, &t, &n);
-    const int RR = d.R[n] * d.R[ring_next(n, d.N)];
+    int RR = d.R[n] * d.R[ring_next(n, d.N)];
+    if (core_rows && d.I[n] < RR) RR = d.I[n];
     const int e = blockIdx.x * blockDim.x + threadIdx.x;
     if (e >= RR * RR) return;
     const int r = e / RR, c = e - r * RR;
@@ -326,7 +335,7 @@ hipError_t launch_gram(const tr_desc& d, ModeSrc ms, const void* S, const double
     // one wavefront per block: the partials' reads spread over as many CUs
     // as there are blocks of 64 entries
     hipLaunchKernelGGL(k_gram_reduce, dim3((maxRR2 + 63) / 64), dim3(64), 0, st, d, ms, part, L.groups, maxRR2,
-                       gram);
+                       S == nullptr, gram);
     return hipGetLastError();
 }
 

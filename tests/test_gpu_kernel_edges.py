@@ -5,10 +5,11 @@ import pytest
 import torch
 
 import tr_inputs as ti
-from gpu_util import DEV, TOL, problem, rel, rounded, say, to_dev, unfold
+from gpu_util import DEV, TOL, fold, problem, rel, rounded, say, to_dev, unfold
 from oracle import brsgd, entry, sampling
 from paper_2303_16492_amd import _lib as L
 from paper_2303_16492_amd import api
+from paper_2303_16492_amd.driver import TRSolver
 
 pytestmark = pytest.mark.gpu
 
@@ -234,3 +235,68 @@ def test_cdf_draws(I, dtype):
             idx, pF = api.tr_sample(desc, 4, 9, n, m, cdf_J=up(wJ))
             iref, pref = sampling.draw(4, 9, n, m, I, w_J=wJ)
             assert np.array_equal(idx.cpu().numpy(), iref) and np.array_equal(pF.cpu().numpy(), pref)
+
+
+def _weights(cdf):
+    return np.diff(np.concatenate([[0], cdf.cpu().numpy()])).astype(np.int64)
+
+
+# the one-launch law with 1 to 4 tile columns (full and partial), tall, square
+# and wide cores, row counts around batches of K steps and tiles, its largest
+# I_k and the first past it; wide cores above 64 rows and above 128
+@pytest.mark.parametrize("I,R", [([1, 2, 16], [4, 4, 1]), ([4096, 17, 15], [4, 4, 4]), ([4097, 17, 33], [4, 4, 4]),
+                                 ([33, 32, 1000], [5, 5, 6]), ([1024, 9, 31], [8, 4, 1]), ([1025, 9, 31], [8, 4, 1]),
+                                 ([455, 47, 49], [6, 8, 5]), ([256, 64, 63], [8, 8, 8]), ([257, 64, 63], [8, 8, 8]),
+                                 ([60, 30, 64], [16, 16, 16]), ([66, 65, 100], [10, 10, 10]),
+                                 ([150, 129, 40], [12, 13, 12]), ([256, 255, 257], [16, 16, 16])])
+@pytest.mark.parametrize("dtype", [torch.float32, torch.float64])
+def test_leverage_forms(I, R, dtype):
+    cores = [rounded(c, dtype) for c in ti.gaussian_cores(41, 3, I, R, scale=0.7)]
+    desc = api.make_desc(I, R, dtype)
+    for k in range(3):
+        G = unfold(cores[k])
+        s = np.linalg.svd(G, compute_uv=False)
+        if s[-1] < 1e-5 * s[0]:   # near the rank test: covered by exact deficiency below
+            continue
+        say("leverage forms", I, R, dtype, "core", k)
+        cdf, st = api.tr_dist(desc, k, L.TR_LAW_LEVERAGE, to_dev(G, dtype))
+        wref = sampling.quantize(sampling.dist_leverage(cores[k])).astype(np.int64)
+        # 64 units, and the squared condition of the Gram's rounding
+        assert int(st) == 0 and np.max(np.abs(_weights(cdf) - wref)) <= 64 + 2.0 ** -10 * (s[0] / s[-1]) ** 2
+        if G.shape[0] > 2:   # rows of lower rank, exactly
+            H = G.copy()
+            H[-1] = H[0]
+            if G.shape[1] > 1:
+                H[:, -1] = H[:, 0]
+            say("leverage forms", I, R, dtype, "core", k, "deficient")
+            cdf, st = api.tr_dist(desc, k, L.TR_LAW_LEVERAGE, to_dev(H, dtype))
+            wref = sampling.quantize(sampling.dist_leverage(fold_core(H, R, k))).astype(np.int64)
+            sd = np.linalg.svd(H, compute_uv=False)
+            sd = sd[sd > 1e-10 * sd[0]]
+            assert int(st) == 0 and np.max(np.abs(_weights(cdf) - wref)) <= 64 + 2.0 ** -10 * (sd[0] / sd[-1]) ** 2
+
+
+def fold_core(G, R, k):
+    return fold(G, R[k], R[(k + 1) % len(R)])
+
+
+# every core's law in the first launch and the step's core after each step:
+# one-launch forms and the forms of several launches
+@pytest.mark.parametrize("law,I,R", [("L", [20, 30, 25], [3, 4, 5]), ("L", [90, 30, 80], [10, 9, 8]),
+                                     ("E", [20, 30, 25], [3, 4, 5]), ("E", [300, 260, 40], [16, 16, 14])])
+@pytest.mark.parametrize("prec", ["f32", "f64"])
+def test_laws_follow_the_cores(law, I, R, prec):
+    dtype = torch.float64 if prec == "f64" else torch.float32
+    I, R, cores, X, dcores, dX = problem(43, 3, I, R, dtype)
+    desc = api.make_desc(I, R, dtype)
+    solver = TRSolver(dcores, dX, I, R, 64, law=law, prec=prec, rule=api.step_rule("fixed", alpha=1e-3), seed=5)
+    code = L.TR_LAW_LEVERAGE if law == "L" else L.TR_LAW_EUCLID
+    for steps in (1, 3):
+        say("laws follow", law, I, R, prec, steps)
+        solver.run(steps)
+        for k in range(3):
+            assert torch.equal(solver.cdf[k], api.tr_dist(desc, k, code, dcores[k])[0])
+            pref = (sampling.dist_leverage if law == "L" else lambda c: sampling.dist_euclid(c)[0])(
+                fold_core(dcores[k].double().cpu().numpy(), R, k))
+            assert np.max(np.abs(_weights(solver.cdf[k]) - sampling.quantize(pref).astype(np.int64))) <= 1024
+    assert int(solver.status.item()) == 0
