@@ -26,7 +26,7 @@ class TRContract(torch.autograd.Function):
     def backward(ctx, gloss):
         idx, resid, *cores = ctx.saved_tensors
         B = idx.shape[0]
-        g = gloss.detach().to(torch.float64).contiguous()
+        g = gloss if gloss.dtype == torch.float64 else gloss.to(torch.float64)   # a scalar: always contiguous
         grads = api.tr_entry_bwd(ctx.desc, cores, idx, resid, B, scale_dev=g)
         return (None, None, None, *grads)
 
