@@ -87,9 +87,10 @@ __global__ __launch_bounds__(256) void k_sweep(tr_desc d, ModeSrc ms, const doub
 // passes Z = B V~ of its columns to its tiles through its own LDS slots.
 //
 // Measured (order 4, 101 x 57 x 83 x 44, ranks 12, 11, 9, 14: RR 99 to 168,
-// m 2048, Euclidean law, eager): 137 us per scaled step; 749 us with a blocked
-// Cholesky from global memory (475 us) and two triangular solves per row (117
-// us) on one stream.
+// m 2048, Euclidean law, eager): 46 us for the sweep (54 with every slot's
+// coordinates compared in every step, see SlotMasks), 116 us per scaled step;
+// 749 us with a blocked Cholesky from global memory (475 us) and two triangular
+// solves per row (117 us) on one stream.  RR = 256: 192 us with its apply (233).
 constexpr int kWideUpd = 6;                         // update wavefronts
 constexpr int kWideThreads = 64 * (kWideUpd + 1);
 constexpr int kWideCols = 5;   // tile columns a wavefront's run of tiles touches (NT <= 16)
@@ -133,6 +134,21 @@ struct WideShared {
     int good[2];
 };
 
+// Which slots of an update wavefront a block step publishes: lane t holds, for
+// tile row t, the slots in it (row), those below its diagonal tile in its
+// column (col) and its diagonal tile's slot (diag), so that a step finds its
+// slots with three lane reads.  (Comparing every slot's coordinates took some
+// 220 cycles a slot and step, half of the wide sweep's step.)
+struct SlotMasks {
+    int row = 0, col = 0, diag = 0;
+    __device__ __forceinline__ void add(int k, int rt, int ct) {
+        const int t = threadIdx.x & 15, bit = 1 << k;
+        row |= rt == t ? bit : 0;
+        col |= ct == t && rt > t ? bit : 0;
+        diag |= rt == t && ct == t ? bit : 0;
+    }
+};
+
 // The tiles of update wavefront uw: slot k is tile (rt, ct) of the wavefront's
 // column number m; unused slots have rt = ct = 255 and compute on tile row 15
 // and column 0 without being stored or published.  Everything is uniform and
@@ -142,6 +158,7 @@ struct WideShared {
 template <int K>
 struct WideTiles {
     int pk[K], cols, n, ncol;   // pk: rt | ct << 8 | m << 16; cols: four bits per column
+    SlotMasks M;
     __device__ __forceinline__ static int fresh(int v) {
         asm volatile("" : "+s"(v));
         return v;
@@ -163,6 +180,7 @@ struct WideTiles {
             const int c = wide_col(p, NT), h = NT - c;
             pk[k] = __builtin_amdgcn_readfirstlane(in ? (c + (s - at)) | c << 8 | (p - p0) << 16 : 0xffff);
             if (in) {
+                M.add(k, c + (s - at), c);
                 nc = p - p0 + 1;
                 cs |= c << (4 * (p - p0));
             }
@@ -178,26 +196,39 @@ struct WideTiles {
     }
 };
 
-template <int NTB, int K, int HQ>
-__device__ __forceinline__ void wide_publish(const dbl4 (&acc)[K], const WideTiles<K>& T, int q, double* Vt) {
-    constexpr int NP = vt_pitch<NTB>();
+// One tile's part of the pivot rows (see publish_rows): a tile of the pivot
+// tile row, or one of the column below its diagonal tile.
+template <int NP, int HQ>
+__device__ __forceinline__ void publish_row_tile(const dbl4& a, int ct, int tq, double* Vt) {
     const int l = threadIdx.x & 63, lr = l >> 4, lc = l & 15;
-    const int tq = q >> 1;
 #pragma unroll
-    for (int k = 0; k < K; ++k) {
-        const int pk = T.fresh(T.pk[k]), rt = pk & 255, ct = pk >> 8 & 255;
-        if (rt == tq) {
+    for (int jj = 0; jj < 2; ++jj) {
+        const double v = a[2 * HQ + jj];
+        const int u = 4 * jj + lr, c = 16 * ct + lc;
+        // the selector lies in the diagonal tile only: c == 8q + u there is lc == 8 HQ + u
+        Vt[u * NP + c] = ct == tq ? v - (lc == 8 * HQ + u ? 1.0 : 0.0) : v;
+    }
+}
+template <int NP, int HQ>
+__device__ __forceinline__ void publish_col_tile(const dbl4& a, int rt, double* Vt) {
+    const int l = threadIdx.x & 63, lr = l >> 4, lc = l & 15;
+    if ((lc >> 3) == HQ) {
 #pragma unroll
-            for (int jj = 0; jj < 2; ++jj) {
-                const double v = acc[k][2 * HQ + jj];
-                const int u = 4 * jj + lr;
-                Vt[u * NP + 16 * ct + lc] = ct == tq ? v - (lc == 8 * HQ + u ? 1.0 : 0.0) : v;
-            }
-        } else if (ct == tq && (lc >> 3) == HQ) {
-            const int u = lc - 8 * HQ;
+        for (int j = 0; j < 4; ++j) Vt[(lc - 8 * HQ) * NP + 16 * rt + 4 * j + lr] = a[j];
+    }
+}
+
+// Slots g to g + 3's part of the pivot rows of block q (row, col: SlotMasks of
+// its tile row).
+template <int NTB, int K, int HQ>
+__device__ __forceinline__ void wide_publish(const dbl4 (&acc)[K], const WideTiles<K>& T, int g, int q, int row, int col,
+                                             double* Vt) {
+    constexpr int NP = vt_pitch<NTB>();
+    if (!((row | col) >> g & 15)) return;
 #pragma unroll
-            for (int j = 0; j < 4; ++j) Vt[u * NP + 16 * rt + 4 * j + lr] = acc[k][j];
-        }
+    for (int k = g; k < g + 4 && k < K; ++k) {
+        if (row >> k & 1) publish_row_tile<NP, HQ>(acc[k], T.fresh(T.pk[k]) >> 8 & 255, q >> 1, Vt);
+        else if (col >> k & 1) publish_col_tile<NP, HQ>(acc[k], T.fresh(T.pk[k]) & 255, Vt);
     }
 }
 
@@ -234,9 +265,16 @@ __device__ __forceinline__ bool wide_update_step(dbl4 (&acc)[K], const WideTiles
     __builtin_amdgcn_s_waitcnt(0xc07f);
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    // The pivot rows of the next step go out one group of four tiles behind the
+    // products, so that the stores run while the matrix cores do.
+    int row = 0, col = 0;
+    if (more) {
+        row = __builtin_amdgcn_readlane(T.M.row, (q + 1) >> 1);
+        col = __builtin_amdgcn_readlane(T.M.col, (q + 1) >> 1);
+    }
 #pragma unroll
-    for (int g = 0; g < K; g += 4) {
-        if (g < T.n) {   // uniform; four tiles' operands in flight together
+    for (int g = 0; g < K + 4; g += 4) {
+        if (g < K && g < T.n) {   // uniform; four tiles' operands in flight together
             double u0[4], u1[4], z0[4], z1[4];
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
@@ -255,13 +293,13 @@ __device__ __forceinline__ bool wide_update_step(dbl4 (&acc)[K], const WideTiles
             for (int i = 0; i < 4 && g + i < K; ++i)
                 acc[g + i] = __builtin_amdgcn_mfma_f64_16x16x4f64(u1[i], z1[i], acc[g + i], 0, 0, 0);
         }
+        if (g > 0) wide_publish<NTB, K, HQ ^ 1>(acc, T, g - 4, q + 1, row, col, sh.Vt[HQ ^ 1]);
     }
-    if (more) wide_publish<NTB, K, HQ ^ 1>(acc, T, q + 1, sh.Vt[HQ ^ 1]);
     if (q + 2 < npiv) {
-        const int t2 = (q + 2) >> 1;
+        const int diag = __builtin_amdgcn_readlane(T.M.diag, (q + 2) >> 1);
 #pragma unroll
         for (int k = 0; k < K; ++k)
-            if ((T.fresh(T.pk[k]) & 0xffff) == (t2 | t2 << 8)) publish_d8<HQ>(acc[k], sh.D8[HQ]);
+            if (diag && diag >> k & 1) publish_d8<HQ>(acc[k], sh.D8[HQ]);
     }
     __syncthreads();
     return more ? sh.good[HQ ^ 1] != 0 : true;
@@ -391,7 +429,9 @@ __device__ __forceinline__ int wide_update_wave(int uw, const double* __restrict
                 acc[k][j] = in ? (acc[k][j] + (r == c ? eta : 0.0)) * sc : (r == c ? 1.0 : 0.0);
             }
         }
-        wide_publish<NTB, K, 0>(acc, T, 0, sh.Vt[0]);
+        const int row = __builtin_amdgcn_readlane(T.M.row, 0), col = __builtin_amdgcn_readlane(T.M.col, 0);
+#pragma unroll
+        for (int g = 0; g < K; g += 4) wide_publish<NTB, K, 0>(acc, T, g, 0, row, col, sh.Vt[0]);
         __syncthreads();
         bool good = sh.good[0] != 0;
         for (int q = 0; q < npiv && good; q += 2) {
