@@ -240,24 +240,31 @@ __global__ __launch_bounds__(kOptBlock) void k_opt_terms(tr_desc d, ModeSrc ms, 
 // The same terms read from the mode-major replica of X, where the fiber
 // X_[n](:,j) is contiguous at j I_n (columns in the ring order n+1, n+2, ...
 // with the first fastest, as above).  A block takes kOptCols consecutive
-// columns.  It forms s_j of every column in LDS (one thread per (column,
-// row s of the chain product), the slices read from the cores in global
-// memory, which stay in cache), and each wavefront then takes kOptCols / 4
-// consecutive columns:
+// columns.  It forms s_j of every column in LDS: the columns share their
+// indices past the first but for a few steps, so the product of the slices of
+// cores n+2, ..., n-1 is formed once per such step (one thread per row of it)
+// and one thread per (column, row s of the chain product) multiplies the row of
+// the column's first slice into it; where a block has more than kOptOuter such
+// steps (I_{n+1} < 8) or there is no second slice, that thread walks the whole
+// chain.  Each wavefront then takes kOptCols / 4 consecutive columns:
 // the predictions G_{n(2)} s_j of its 16 columns are 16 x 16 tiles of FP64
 // matrix-core products (its fiber entries requested, in the products'
 // result layout, before any arithmetic), and the squared residuals of a
 // column are added over its rows in a fixed order.  Needs I_n <= 64 Q,
-// R_n R_{n+1} <= kOptRRMax, every rank <= kOptRank and J_n < 2^31.  (At the
-// order-4 workload, staging the other cores in LDS measured the same, 98 us;
-// all N cores 120 us and G_{n(2)} alone 102 us.)
+// R_n R_{n+1} <= RM, every rank <= kOptRank and J_n < 2^31.  bs (optional): the
+// sum of the block's terms.
+//
+// Bound: the loads of the slices and of the fibers (45 MB at the size below).
+// 50 x 47 x 53 x 45, ranks 5, FP64: 48.5 us with the whole chain walked per
+// column (55 slice loads a thread), 35.8 so; with the fibers or the A operands
+// requested earlier 38 to 40 (fewer wavefronts per SIMD).
 constexpr int kOptCols = 64;
-constexpr int kOptRRMax = 32;
 constexpr int kOptRank = 8;                   // every R_k
+constexpr int kOptOuter = 9;                  // runs of columns with the same indices past the first
 
-template <typename TC, typename TX, int Q>
+template <typename TC, typename TX, int Q, int RM>
 __global__ __launch_bounds__(256) void k_opt_terms_rep(tr_desc d, ModeSrc ms, Ptrs cores, XSrc xs,
-                                                       double* __restrict__ a) {
+                                                       double* __restrict__ a, double* __restrict__ bs) {
     uint64_t t;
     int n;
     resolve_mode(ms, d.N, &t, &n);
@@ -269,29 +276,23 @@ __global__ __launch_bounds__(256) void k_opt_terms_rep(tr_desc d, ModeSrc ms, Pt
     const int64_t J = J_of(d, n);
     const int64_t j0 = (int64_t)blockIdx.x * kOptCols;
     if (j0 >= J) return;   // the whole block
-    __shared__ double sS[kOptCols][kOptRRMax + 1];
+    __shared__ double sS[kOptCols][RM + 1];
     __shared__ double sN[kOptCols];
+    __shared__ double sP[kOptOuter][kOptRank][kOptRank];   // product of the slices past the first, per run
     const int tid = threadIdx.x;
-    for (int e = tid; e < kOptCols * (kOptRRMax + 1); e += 256) (&sS[0][0])[e] = 0.0;
-    __syncthreads();
-    // Row s of the chain product of column j: the slices of cores n+1, ...,
-    // n-1 at the column's indices (decoded in that order, the first
-    // fastest), every loop bounded by kOptRank at compile time so that the
-    // row stays in registers and a stage's LDS reads issue together.
-    for (int w = tid; w < kOptCols * Rn1; w += 256) {
-        const int c = w / Rn1, s = w - c * Rn1;
-        if (j0 + c >= J) continue;
-        uint32_t rem = (uint32_t)(j0 + c);
-        int k = n1;
+    for (int e = tid; e < kOptCols * (RM + 1); e += 256) (&sS[0][0])[e] = 0.0;
+    // Row s of the product of the slices of cores k, ..., n-1 at the indices
+    // that rem decodes to (in that order, the first fastest), every loop
+    // bounded by kOptRank at compile time so that the row stays in registers
+    // and a stage's loads issue together.
+    auto chain_row = [&](int k, uint32_t rem, int s, double (&v)[kOptRank]) {
         int Rk = d.R[k], Rk1 = d.R[ring_next(k, N)];
         uint32_t ik = rem % (uint32_t)d.I[k];
         rem /= (uint32_t)d.I[k];
         const TC* A = static_cast<const TC*>(cores.p[k]) + ik * Rk * Rk1;
-        double v[kOptRank];
 #pragma unroll
         for (int cc = 0; cc < kOptRank; ++cc) v[cc] = cc < Rk1 ? (double)A[s + Rk * cc] : 0.0;
-        for (int q = 2; q < N; ++q) {
-            k = ring_next(k, N);
+        for (k = ring_next(k, N); k != n; k = ring_next(k, N)) {
             Rk = d.R[k];
             Rk1 = d.R[ring_next(k, N)];
             ik = rem % (uint32_t)d.I[k];
@@ -311,9 +312,54 @@ __global__ __launch_bounds__(256) void k_opt_terms_rep(tr_desc d, ModeSrc ms, Pt
 #pragma unroll
             for (int cc = 0; cc < kOptRank; ++cc) v[cc] = nv[cc];
         }
+    };
+    const int n2 = ring_next(n1, N), Rn2 = d.R[n2];
+    const uint32_t I1 = (uint32_t)d.I[n1], jf = (uint32_t)j0, o0 = jf / I1, i10 = jf - o0 * I1;
+    const uint32_t jl = (uint32_t)(j0 + kOptCols < J ? j0 + kOptCols : J) - 1;
+    const int runs = (int)(jl / I1 - o0) + 1;
+    if (N > 2 && runs <= kOptOuter) {   // uniform
+        if (tid < runs * Rn2) {
+            const int o = tid / Rn2, s = tid - o * Rn2;
+            double v[kOptRank];
+            chain_row(n2, o0 + o, s, v);
 #pragma unroll
-        for (int r = 0; r < kOptRank; ++r)
-            if (r < Rn) sS[c][r + Rn * s] = v[r];
+            for (int r = 0; r < kOptRank; ++r) sP[o][s][r] = v[r];
+        }
+        __syncthreads();
+        const TC* G1 = static_cast<const TC*>(cores.p[n1]);
+        for (int w = tid; w < kOptCols * Rn1; w += 256) {
+            const int c = w / Rn1, s = w - c * Rn1;
+            if (j0 + c >= J) continue;
+            const uint32_t p = i10 + (uint32_t)c, o = p / I1, i1 = p - o * I1;
+            const TC* A = G1 + i1 * Rn1 * Rn2;
+            TC av[kOptRank];
+            double v[kOptRank];
+#pragma unroll
+            for (int q = 0; q < kOptRank; ++q) av[q] = A[s + Rn1 * (q < Rn2 ? q : 0)];
+#pragma unroll
+            for (int r = 0; r < kOptRank; ++r) v[r] = 0.0;
+#pragma unroll
+            for (int q = 0; q < kOptRank; ++q) {
+                if (q < Rn2) {
+#pragma unroll
+                    for (int r = 0; r < kOptRank; ++r) v[r] += (double)av[q] * sP[o][q][r];
+                }
+            }
+#pragma unroll
+            for (int r = 0; r < kOptRank; ++r)
+                if (r < Rn) sS[c][r + Rn * s] = v[r];
+        }
+    } else {
+        __syncthreads();
+        for (int w = tid; w < kOptCols * Rn1; w += 256) {
+            const int c = w / Rn1, s = w - c * Rn1;
+            if (j0 + c >= J) continue;
+            double v[kOptRank];
+            chain_row(n1, jf + (uint32_t)c, s, v);
+#pragma unroll
+            for (int r = 0; r < kOptRank; ++r)
+                if (r < Rn) sS[c][r + Rn * s] = v[r];
+        }
     }
     // Wavefront w takes the block's columns 16 w .. 16 w + 15.  Its fiber
     // entries are requested before the barrier, in the layout of the matrix
@@ -347,9 +393,9 @@ __global__ __launch_bounds__(256) void k_opt_terms_rep(tr_desc d, ModeSrc ms, Pt
     // extra registers cut the wavefronts per SIMD from 6 to 3.)
     typedef double od4 __attribute__((ext_vector_type(4)));
     const TC* Gn = static_cast<const TC*>(cores.p[n]);
-    double bv[kOptRRMax / 4];
+    double bv[RM / 4];
 #pragma unroll
-    for (int ks = 0; ks < kOptRRMax / 4; ++ks) bv[ks] = sS[c][4 * ks + lk];
+    for (int ks = 0; ks < RM / 4; ++ks) bv[ks] = sS[c][4 * ks + lk];
     double rr = 0.0;
 #pragma unroll
     for (int rt = 0; rt < 4 * Q; ++rt) {
@@ -357,7 +403,7 @@ __global__ __launch_bounds__(256) void k_opt_terms_rep(tr_desc d, ModeSrc ms, Pt
             od4 acc = {0.0, 0.0, 0.0, 0.0};
             const int gi = 16 * rt + lc;
 #pragma unroll
-            for (int ks = 0; ks < kOptRRMax / 4; ++ks) {
+            for (int ks = 0; ks < RM / 4; ++ks) {
                 if (ks < KS) {
                     const int gk = 4 * ks + lk;
                     const double av = (gi < In && gk < RR) ? (double)Gn[gi * RR + gk] : 0.0;
@@ -376,9 +422,18 @@ __global__ __launch_bounds__(256) void k_opt_terms_rep(tr_desc d, ModeSrc ms, Pt
     rr += __shfl_xor(rr, 16, 64);
     rr += __shfl_xor(rr, 32, 64);
     __syncthreads();
-    if (lk == 0 && colok) a[jc] = sqrt(rr) * sqrt(sN[c]);
+    const double term = colok ? sqrt(rr) * sqrt(sN[c]) : 0.0;
+    if (lk == 0 && colok) a[jc] = term;
+    if (bs) {   // the block's columns in a fixed order: 16 lanes of a wavefront, then the four
+        double v = term;
+#pragma unroll
+        for (int o = 8; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+        __shared__ double sB[4];
+        if (lane == 0) sB[wv] = v;
+        __syncthreads();
+        if (tid == 0) bs[blockIdx.x] = ((sB[0] + sB[1]) + sB[2]) + sB[3];
+    }
 }
-
 
 // Per-block FP64 sums of a (fixed order within a block).
 __global__ __launch_bounds__(kOptBlock) void k_opt_blocksum(tr_desc d, ModeSrc ms, const double* __restrict__ a,
@@ -396,10 +451,11 @@ __global__ __launch_bounds__(kOptBlock) void k_opt_blocksum(tr_desc d, ModeSrc m
     if (threadIdx.x == 0) bs[blockIdx.x] = s;
 }
 
-// Total, quantisation and per-block weight sums; then the block offsets.
+// Total, quantisation, per-block inclusive sums and totals of the weights.
 __global__ __launch_bounds__(kOptBlock) void k_opt_quantize(tr_desc d, ModeSrc ms, const double* __restrict__ a,
-                                                           const double* __restrict__ bs, uint64_t* __restrict__ w,
-                                                           uint64_t* __restrict__ wbs, int32_t* status) {
+                                                           const double* __restrict__ bs, int bcols,
+                                                           uint64_t* __restrict__ w, uint64_t* __restrict__ wbs,
+                                                           int32_t* status) {
     uint64_t t;
     int n;
     resolve_mode(ms, d.N, &t, &n);
@@ -407,31 +463,33 @@ __global__ __launch_bounds__(kOptBlock) void k_opt_quantize(tr_desc d, ModeSrc m
     const int64_t J = J_of(d, n);
     const int64_t nb = (J + kOptBlock - 1) / kOptBlock;
     if (blockIdx.x >= nb) return;
-    // the total of the block sums, the same fixed order in every block
+    // the total of the sums of bcols columns each, the same fixed order in
+    // every block, with the block's own terms in flight beside it
+    const int64_t j = (int64_t)blockIdx.x * kOptBlock + threadIdx.x;
+    const double aj = a[j < J ? j : J - 1];
+    const int64_t ns = (J + bcols - 1) / bcols;
     double part = 0.0;
-    for (int64_t b = threadIdx.x; b < nb; b += kOptBlock) part += bs[b];
+    for (int64_t b = threadIdx.x; b < ns; b += kOptBlock) part += bs[b];
     __shared__ double red[kOptBlock / 64];
     const double tot = block_sum(part, red);
     const bool zero = !(tot > 0.0) || !isfinite(tot);
     if (zero && blockIdx.x == 0 && threadIdx.x == 0) set_status(status, TR_DEV_ZERO_DIST);
-    const int64_t j = (int64_t)blockIdx.x * kOptBlock + threadIdx.x;
     uint64_t wv = 0;
-    if (j < J) {
-        wv = zero ? quantize(1.0 / (double)J) : quantize(a[j] / tot);
-        w[j] = wv;
+    if (j < J) wv = zero ? quantize(1.0 / (double)J) : quantize(aj / tot);
+    // inclusive scan inside the block: shuffles within a wavefront, then the
+    // wavefronts' totals
+    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const uint64_t y = __shfl_up((unsigned long long)wv, (unsigned)o, 64);
+        if (lane >= o) wv += y;
     }
-    // Inclusive scan inside the block (Hillis-Steele over 256 entries).
-    __shared__ uint64_t sc[kOptBlock];
-    sc[threadIdx.x] = wv;
+    __shared__ uint64_t sc[kOptBlock / 64];
+    if (lane == 63) sc[wid] = wv;
     __syncthreads();
-    for (int o = 1; o < kOptBlock; o <<= 1) {
-        const uint64_t v = (int)threadIdx.x >= o ? sc[threadIdx.x - o] : 0ull;
-        __syncthreads();
-        sc[threadIdx.x] += v;
-        __syncthreads();
-    }
-    if (j < J) w[j] = sc[threadIdx.x];
-    if (threadIdx.x == kOptBlock - 1) wbs[blockIdx.x] = sc[threadIdx.x];
+    for (int q = 0; q < wid; ++q) wv += sc[q];
+    if (j < J) w[j] = wv;
+    if (threadIdx.x == kOptBlock - 1) wbs[blockIdx.x] = wv;
 }
 
 __global__ __launch_bounds__(1024) void k_opt_offsets(tr_desc d, ModeSrc ms, uint64_t* __restrict__ wbs) {
@@ -455,6 +513,9 @@ __global__ __launch_bounds__(1024) void k_opt_offsets(tr_desc d, ModeSrc ms, uin
     if (b < nb) wbs[b] = prev;
 }
 
+// Each block's offset added to its part of the CDF: the sum of the totals
+// before it (SUM), or the entry that k_opt_offsets put there.
+template <bool SUM>
 __global__ __launch_bounds__(kOptBlock) void k_opt_apply(tr_desc d, ModeSrc ms, const uint64_t* __restrict__ wbs,
                                                         uint64_t* __restrict__ w) {
     uint64_t t;
@@ -463,43 +524,68 @@ __global__ __launch_bounds__(kOptBlock) void k_opt_apply(tr_desc d, ModeSrc ms, 
     n = __builtin_amdgcn_readfirstlane(n);   // uniform: its table reads stay scalar
     const int64_t J = J_of(d, n);
     const int64_t j = (int64_t)blockIdx.x * kOptBlock + threadIdx.x;
-    if (j < J) w[j] += wbs[blockIdx.x];
+    if ((int64_t)blockIdx.x * kOptBlock >= J) return;   // the whole block
+    uint64_t off;
+    if constexpr (SUM) {
+        const uint64_t wj = w[j < J ? j : J - 1];
+        unsigned long long part = 0;
+        for (int b = threadIdx.x; b < (int)blockIdx.x; b += kOptBlock) part += wbs[b];
+        __shared__ unsigned long long red[kOptBlock / 64];
+        off = block_sum(part, red);
+        if (j < J) w[j] = wj + off;
+    } else {
+        off = wbs[blockIdx.x];
+        if (j < J) w[j] += off;
+    }
 }
+
+// Up to this many partial sums every block adds them itself (16 loads a thread);
+// above it a launch forms the sums of 256 terms or the offsets once.  At
+// J = 112 K (441 blocks) the four launches after the terms took 21 us, the two
+// left 12.
+constexpr int64_t kOptSums = 4096;
 
 size_t dist_opt_ws_bytes(const tr_desc& d) {
     const Shape sh = shape_of(d);
     const int64_t nb = (sh.maxJ + kOptBlock - 1) / kOptBlock;
-    return align_up((size_t)sh.maxJ * 8) + 2 * align_up((size_t)nb * 8);
+    // sums: one per block of 256, or one per kOptCols columns
+    const int64_t ns = (sh.maxJ + kOptCols - 1) / kOptCols;
+    return align_up((size_t)sh.maxJ * 8) + align_up((size_t)(ns <= kOptSums ? ns : nb) * 8) + align_up((size_t)nb * 8);
 }
 
 hipError_t launch_dist_optimal(const tr_desc& d, ModeSrc ms, Ptrs cores, XSrc xs, uint64_t* cdf_J, int32_t* status,
                                void* ws, hipStream_t st) {
     const Shape sh = shape_of(d);
-    const int64_t nb = (sh.maxJ + kOptBlock - 1) / kOptBlock;
+    const int64_t nb = (sh.maxJ + kOptBlock - 1) / kOptBlock, ns = (sh.maxJ + kOptCols - 1) / kOptCols;
     char* w = static_cast<char*>(ws);
     double* a = reinterpret_cast<double*>(w);
     double* bs = reinterpret_cast<double*>(w + align_up((size_t)sh.maxJ * 8));
-    uint64_t* wbs = reinterpret_cast<uint64_t*>(w + align_up((size_t)sh.maxJ * 8) + align_up((size_t)nb * 8));
+    uint64_t* wbs = reinterpret_cast<uint64_t*>(reinterpret_cast<char*>(bs) +
+                                                align_up((size_t)(ns <= kOptSums ? ns : nb) * 8));
     const dim3 grid((unsigned)nb);
     const bool f64 = d.core_dtype == TR_F64;
-    bool reps = true;
+    bool reps = true, summed = false;
     for (int k = 0; k < d.N; ++k) reps = reps && xs.rep[k] != nullptr;
-    if (reps && sh.maxI <= 128 && sh.maxRR <= kOptRRMax && sh.maxR <= kOptRank &&
-        sh.maxJ < ((int64_t)1 << 31)) {
-        const dim3 gr((unsigned)((sh.maxJ + kOptCols - 1) / kOptCols));
-        const bool one = sh.maxI <= 64;
-        if (f64 && d.x_dtype == TR_F64) {
-            if (one) hipLaunchKernelGGL((k_opt_terms_rep<double, double, 1>), gr, dim3(256), 0, st, d, ms, cores, xs, a);
-            else hipLaunchKernelGGL((k_opt_terms_rep<double, double, 2>), gr, dim3(256), 0, st, d, ms, cores, xs, a);
-        } else if (!f64 && d.x_dtype == TR_F32) {
-            if (one) hipLaunchKernelGGL((k_opt_terms_rep<float, float, 1>), gr, dim3(256), 0, st, d, ms, cores, xs, a);
-            else hipLaunchKernelGGL((k_opt_terms_rep<float, float, 2>), gr, dim3(256), 0, st, d, ms, cores, xs, a);
-        } else if (!f64 && d.x_dtype == TR_F16) {
-            if (one) hipLaunchKernelGGL((k_opt_terms_rep<float, __half, 1>), gr, dim3(256), 0, st, d, ms, cores, xs, a);
-            else hipLaunchKernelGGL((k_opt_terms_rep<float, __half, 2>), gr, dim3(256), 0, st, d, ms, cores, xs, a);
-        } else {
-            return hipErrorInvalidValue;
-        }
+    if (reps && sh.maxI <= 128 && sh.maxR <= kOptRank && sh.maxJ < ((int64_t)1 << 31)) {
+        const dim3 gr((unsigned)ns);
+        summed = ns <= kOptSums;
+        double* sums = summed ? bs : nullptr;
+#define TRK_OPT_Q(TC, TX, Q)                                                                                              \
+    do {                                                                                                                  \
+        if (sh.maxRR <= 32) hipLaunchKernelGGL((k_opt_terms_rep<TC, TX, Q, 32>), gr, dim3(256), 0, st, d, ms, cores, xs, a, sums); \
+        else hipLaunchKernelGGL((k_opt_terms_rep<TC, TX, Q, 64>), gr, dim3(256), 0, st, d, ms, cores, xs, a, sums);        \
+    } while (0)
+#define TRK_OPT(TC, TX)                            \
+    do {                                           \
+        if (sh.maxI <= 64) TRK_OPT_Q(TC, TX, 1);   \
+        else TRK_OPT_Q(TC, TX, 2);                 \
+    } while (0)
+        if (f64 && d.x_dtype == TR_F64) TRK_OPT(double, double);
+        else if (!f64 && d.x_dtype == TR_F32) TRK_OPT(float, float);
+        else if (!f64 && d.x_dtype == TR_F16) TRK_OPT(float, __half);
+        else return hipErrorInvalidValue;
+#undef TRK_OPT
+#undef TRK_OPT_Q
     } else if (f64 && d.x_dtype == TR_F64)
         hipLaunchKernelGGL((k_opt_terms<double, double>), grid, dim3(kOptBlock), 0, st, d, ms, cores, xs, a);
     else if (!f64 && d.x_dtype == TR_F32)
@@ -510,10 +596,15 @@ hipError_t launch_dist_optimal(const tr_desc& d, ModeSrc ms, Ptrs cores, XSrc xs
         return hipErrorInvalidValue;
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_opt_blocksum, grid, dim3(kOptBlock), 0, st, d, ms, a, bs);
-    hipLaunchKernelGGL(k_opt_quantize, grid, dim3(kOptBlock), 0, st, d, ms, a, bs, cdf_J, wbs, status);
-    hipLaunchKernelGGL(k_opt_offsets, dim3(1), dim3(1024), 0, st, d, ms, wbs);
-    hipLaunchKernelGGL(k_opt_apply, grid, dim3(kOptBlock), 0, st, d, ms, wbs, cdf_J);
+    if (!summed) hipLaunchKernelGGL(k_opt_blocksum, grid, dim3(kOptBlock), 0, st, d, ms, a, bs);
+    hipLaunchKernelGGL(k_opt_quantize, grid, dim3(kOptBlock), 0, st, d, ms, a, bs, summed ? kOptCols : kOptBlock, cdf_J, wbs,
+                       status);
+    if (nb <= kOptSums) {
+        hipLaunchKernelGGL(k_opt_apply<true>, grid, dim3(kOptBlock), 0, st, d, ms, wbs, cdf_J);
+    } else {
+        hipLaunchKernelGGL(k_opt_offsets, dim3(1), dim3(1024), 0, st, d, ms, wbs);
+        hipLaunchKernelGGL(k_opt_apply<false>, grid, dim3(kOptBlock), 0, st, d, ms, wbs, cdf_J);
+    }
     return hipGetLastError();
 }
 

@@ -300,3 +300,28 @@ def test_laws_follow_the_cores(law, I, R, prec):
                 fold_core(dcores[k].double().cpu().numpy(), R, k))
             assert np.max(np.abs(_weights(solver.cdf[k]) - sampling.quantize(pref).astype(np.int64))) <= 1024
     assert int(solver.status.item()) == 0
+
+
+# the optimal law's terms from the replicas: runs of columns up to and past
+# kOptOuter a block (I_{n+1} from 1), orders 2 to 5, R_n R_{n+1} up to 32, past it
+# and 64, I_n up to 64 and past it; J below one block of columns, and past the
+# sums that every block adds itself
+@pytest.mark.parametrize("I,R", [([5, 3], [4, 8]), ([70, 66], [8, 8]), ([1, 2, 40], [3, 5, 8]), ([9, 8, 7], [6, 6, 6]),
+                                 ([64, 65, 11], [4, 8, 4]), ([6, 5, 4, 9], [5, 6, 7, 8]), ([30, 7, 9, 8], [5, 5, 5, 5]),
+                                 ([3, 8, 2, 9, 4], [8, 1, 8, 4, 8]), ([100, 90, 80, 41], [3, 2, 3, 2])])
+@pytest.mark.parametrize("prec", ["f32", "f64"])
+def test_optimal_law_from_replicas(I, R, prec):
+    dtype = torch.float64 if prec == "f64" else torch.float32
+    I, R, cores, X, dcores, dX = problem(47, len(I), I, R, dtype)
+    start = [c.clone() for c in dcores]
+    for seed in (1, 2, 3, 4):
+        solver = TRSolver([c.clone() for c in start], dX, I, R, 32, law="O", prec=prec,
+                          rule=api.step_rule("fixed", alpha=1e-4), seed=seed)
+        n = api.tr_mode(seed, 0, len(I))
+        say("optimal law from replicas", I, R, prec, "mode", n)
+        solver.run(1)
+        J = int(np.prod([s for k, s in enumerate(I) if k != n]))
+        q, _ = sampling.dist_optimal(cores, X, n)
+        w = _weights(solver.cdf_J[:J])
+        assert int(solver.status.item()) == 0
+        assert np.max(np.abs(w - sampling.quantize(q).astype(np.int64))) <= 64 + 16 * np.max(q)
