@@ -17,7 +17,9 @@
 // Other cases (FP64, larger ranks) take k_recon: every thread takes rows
 // i_1 = tid, tid + 256, ... and forms TJ dot products with s_j broadcast
 // from LDS.  Per-block FP64 partial sums are added in a fixed order.
-#include "internal.hpp"
+#include <type_traits>
+
+#include "chain.hpp"
 
 namespace trk {
 
@@ -229,9 +231,58 @@ __global__ __launch_bounds__(256) void k_recon_pack_h3(tr_desc d, const float* _
     if (tid == 0) escale[it] = e;
 }
 
-// Order 3 builds a block's rows from LDS when its columns touch at most this
-// many slices of the last core (true whenever I_2 >= 32).
-constexpr int kRmMaxOuter = 8;
+// Subchain rows of the block's kRmCols columns into sS (row pitch SP): the chain
+// products of the columns' slices on the FP32 matrix cores, in registers
+// (chain.hpp; NM slices at most), 32 columns a wavefront, 16 / RB of them to an
+// operand.  sidx: the columns' indices.
+//
+// Against one thread per (column, row of the product), with the outer slice in
+// LDS at order 3 and loaded anew by every thread above it, and 64-bit entry
+// offsets (whole call of the error, us, before and so): 400^3 ranks 10 145, 141;
+// 400 x 300 x 200 ranks 11 83, 74; 64^4 ranks 5 109, 85; 30^4 x 20 ranks 7 395, 182.
+template <int RB, int NM>
+__device__ __forceinline__ void recon_rows(const tr_desc& d, const Ptrs& cores, const int* sidx, float* sS, int SP) {
+    constexpr int P = 16 / RB, PK = 32 / P, UM = NM > 4 ? 1 : (NM > 2 ? 2 : 8), U = UM < PK ? UM : PK;
+    const int N = d.N, k0 = ring_next(0, N), R0 = d.R[0], R1 = d.R[k0];
+    const ChainLane<float, RB> L;
+    const ChainSlots<float, NM, false> sl(d, k0, N - 1, L);
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const bool in0 = L.col < R1;
+#pragma unroll 1
+    for (int g = 0; g < PK; g += U) {
+        ChainVec<float>::V v[U][NM];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int* ix = sidx + (32 * w + (g + u) * P + L.p) * kMaxOrder;
+            int k = k0;
+#pragma unroll
+            for (int q = 0; q < NM; ++q) {
+                if (q >= N - 1) break;
+                const uint32_t len = (uint32_t)(d.R[k] * d.R[ring_next(k, N)]) * 4u;
+                v[u][q] = sl.load(cores.p[k], (uint64_t)(uint32_t)ix[k] * len, q);
+                k = ring_next(k, N);
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            ChainVec<float>::V T = sl.mask(v[u][0], 0);
+            int k = k0;
+#pragma unroll
+            for (int q = 1; q < NM; ++q) {
+                if (q >= N - 1) break;
+                k = ring_next(k, N);
+                T = chain_mul(sl.mask(v[u][q], q), T, ChainVec<float>::V{0.f, 0.f, 0.f, 0.f});
+                if (q + 1 < N - 1) T = chain_mask(T, L, in0, d.R[ring_next(k, N)]);
+            }
+            if (in0) {   // M(s, r): s = the lane's column, r = its rows
+                float* out = sS + (32 * w + (g + u) * P + L.p) * SP + R0 * L.col;
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    if (L.on[j] && L.row[j] < R0) out[L.row[j]] = T[j];
+            }
+        }
+    }
+}
 
 // MODE 0: per-block sums of (X_hat - X_true)^2 and X_true^2 into part, on
 // the split FP16 products with KT = 8 K16, the B operand from
@@ -247,7 +298,7 @@ template <typename TX, int KT, int MODE>
 __global__ __launch_bounds__(256) void k_recon_mfma(tr_desc d, Ptrs cores, const TX* __restrict__ Xt,
                                                     TX* __restrict__ Xo, double* __restrict__ part,
                                                     const _Float16* __restrict__ Bh, const _Float16* __restrict__ Bl,
-                                                    const int* __restrict__ escale) {
+                                                    const int* __restrict__ escale, int rb, int off32) {
     static_assert(MODE == 1 || KT % 8 == 0, "split products: K in steps of 16");
     constexpr int SP = 2 * KT + 1;          // LDS row pitch of the subchain rows
     const int N = d.N;
@@ -260,139 +311,33 @@ __global__ __launch_bounds__(256) void k_recon_mfma(tr_desc d, Ptrs cores, const
     extern __shared__ __align__(16) unsigned char smem_raw[];
     int64_t* sOff = reinterpret_cast<int64_t*>(smem_raw);          // [kRmCols], -1 past J
     float* sS = reinterpret_cast<float*>(sOff + kRmCols);          // [kRmCols][SP]
-    float* sP = sS + kRmCols * SP;                                  // order 3: slices of the last core
+    int* sidx = reinterpret_cast<int*>(sS + kRmCols * SP);         // [kRmCols][kMaxOrder]
+    __shared__ __align__(16) uint32_t sOff32[kRmCols];             // byte offsets (off32)
     const int tid = threadIdx.x;
-
-    // Order 3: column j = i_2 + I_2 i_3 has subchain row M_j = G_2(i_2) G_3(i_3);
-    // the block's columns span few i_3, whose slices are staged in LDS, and
-    // each item (column, row s of M_j) loads one row of G_2(i_2).
-    const int I1 = d.I[1 % N];
-    const int64_t jl = (j0 + kRmCols < J ? j0 + kRmCols : J) - 1;
-    const int o_lo = N == 3 ? (int)(j0 / I1) : 0;
-    const int n_outer = N == 3 && j0 < J ? (int)(jl / I1) - o_lo + 1 : 0;
-    const bool staged = N == 3 && n_outer <= kRmMaxOuter;
-    if (staged) {
-        const int R2 = d.R[2];                       // slices of core 3: R_3 x R_1 (R_{N+1} = R_1)
-        const int RR2 = R2 * R0;
-        const float* G2 = static_cast<const float*>(cores.p[2]);
-        {   // the slices of core 3, all loads of a thread in flight (clamped, masked after)
-            constexpr int UB = (kRmMaxOuter * kMaxRR + 255) / 256;
-            const int tot = n_outer * RR2;
-            float pv[UB];
-#pragma unroll
-            for (int u = 0; u < UB; ++u) {
-                const int e = u * 256 + tid;
-                pv[u] = G2[(int64_t)o_lo * RR2 + (e < tot ? e : tot - 1)];
-            }
-#pragma unroll
-            for (int u = 0; u < UB; ++u)
-                if (u * 256 + tid < tot) sP[u * 256 + tid] = pv[u];
+    if (tid < kRmCols) {   // a column past the end computes on the last one; its offset marks it
+        const int64_t j = j0 + tid;
+        int64_t rem = j < J ? j : J - 1, off = 0;
+        for (int k = 1; k < N; ++k) {
+            const int64_t q = rem < ((int64_t)1 << 32) ? (int64_t)((uint32_t)rem / (uint32_t)d.I[k]) : rem / d.I[k];
+            const int ik = (int)(rem - q * d.I[k]);
+            rem = q;
+            sidx[tid * kMaxOrder + k] = ik;
+            off += (int64_t)ik * d.x_stride[k];
         }
-        // column jj of the block: i_2 = (i2_0 + jj) mod I_2, i_3 = i3_0 + (i2_0 + jj) div I_2 (32-bit)
-        const int i2_0 = (int)(j0 % I1), i3_0 = (int)(j0 / I1);
-        int* sI2 = reinterpret_cast<int*>(sP + kRmMaxOuter * kMaxRR);   // [kRmCols]
-        int* sI3 = sI2 + kRmCols;                                         // [kRmCols], relative to o_lo
-        for (int e = tid; e < kRmCols; e += blockDim.x) {
-            const int64_t j = j0 + e;
-            const int q = (i2_0 + e) / I1;
-            const int i2 = i2_0 + e - q * I1, i3 = i3_0 + q;
-            sI2[e] = i2;
-            sI3[e] = i3 - o_lo;
-            sOff[e] = j < J ? (int64_t)i2 * d.x_stride[1] + (int64_t)i3 * d.x_stride[2] : -1;
-        }
-        __syncthreads();
-        const float* G1 = static_cast<const float*>(cores.p[1]);
-        const int RR1 = R1 * R2, last = RR1 - 1;
-        const int total = kRmCols * R1;
-        auto load_row = [&](int e, float (&v)[kMaxRank]) {   // row s of G_2(i_2), clamped in bounds
-            const int jj = e / R1, s = e - jj * R1;
-            const float* A = G1 + (int64_t)sI2[jj] * RR1;
-#pragma unroll
-            for (int c = 0; c < kMaxRank; ++c) v[c] = A[min(s + R1 * c, last)];
-#pragma unroll
-            for (int c = 0; c < kMaxRank; ++c) v[c] = c < R2 ? v[c] : 0.f;   // uniform mask
-        };
-        float v[kMaxRank];
-        if (tid < total) load_row(tid, v);
-        for (int e = tid; e < total; e += blockDim.x) {
-            float vn[kMaxRank];
-            if (e + (int)blockDim.x < total) load_row(e + blockDim.x, vn);   // next item's row in flight
-            const int jj = e / R1, s = e - jj * R1;
-            const int64_t j = j0 + jj;
-            float* out = sS + jj * SP + R0 * s;
-            if (j >= J) {
-                for (int r = 0; r < R0; ++r) out[r] = 0.f;
-            } else {
-                // every LDS read of a row issued together: no read behind a
-                // branch (entries past R_3 multiply the zeros of v)
-                const float* P = sP + sI3[jj] * R2 * R0;
-                for (int r = 0; r < R0; ++r) {
-                    const float* Pr = P + R2 * r;
-                    float acc = 0.f;
-#pragma unroll
-                    for (int c = 0; c < kMaxRank; ++c) acc += v[c] * Pr[c < R2 ? c : R2 - 1];
-                    out[r] = acc;
-                }
-            }
-#pragma unroll
-            for (int c = 0; c < kMaxRank; ++c) v[c] = vn[c];
-        }
+        sOff[tid] = j < J ? off : -1;
+        if (MODE == 0) sOff32[tid] = (uint32_t)off * (uint32_t)sizeof(TX);
+    }
+    __syncthreads();
+    if (N <= 3) {
+        if (rb == 4) recon_rows<4, 2>(d, cores, sidx, sS, SP);
+        else if (rb == 8) recon_rows<8, 2>(d, cores, sidx, sS, SP);
+        else recon_rows<16, 2>(d, cores, sidx, sS, SP);
+    } else if (N <= 5) {
+        if (rb == 4) recon_rows<4, 4>(d, cores, sidx, sS, SP);
+        else if (rb == 8) recon_rows<8, 4>(d, cores, sidx, sS, SP);
+        else recon_rows<16, 4>(d, cores, sidx, sS, SP);
     } else {
-        // any order: thread item (column, row s of M_j) through the chain of
-        // slice products.  Loads are unconditional (indices clamped into the
-        // slice) so that a whole slice row or column is in flight at once;
-        // entries past the ranks are masked after the load.
-        for (int e = tid; e < kRmCols * R1; e += blockDim.x) {
-            const int jj = e / R1, s = e - jj * R1;
-            const int64_t j = j0 + jj;
-            float* out = sS + jj * SP + R0 * s;
-            if (j >= J) {
-                for (int r = 0; r < R0; ++r) out[r] = 0.f;
-                if (s == 0) sOff[jj] = -1;
-                continue;
-            }
-            int ik[kMaxOrder];
-            int64_t rem = j, off = 0;
-            for (int k = 1; k < N; ++k) {
-                ik[k] = (int)(rem % d.I[k]);
-                rem /= d.I[k];
-                off += (int64_t)ik[k] * d.x_stride[k];
-            }
-            if (s == 0) sOff[jj] = off;
-            float v[kMaxRank];
-            {
-                const int Rk = d.R[1 % N], Rk1 = d.R[ring_next(1 % N, N)];
-                const float* A = static_cast<const float*>(cores.p[1 % N]) + (int64_t)ik[1] * Rk * Rk1;
-                const int last = Rk * Rk1 - 1;
-#pragma unroll
-                for (int c = 0; c < kMaxRank; ++c) {
-                    const float a = A[min(s + Rk * c, last)];
-                    v[c] = c < Rk1 ? a : 0.f;
-                }
-            }
-            for (int k = 2; k < N; ++k) {
-                const int Rk = d.R[k], Rk1 = d.R[ring_next(k, N)];
-                const float* A = static_cast<const float*>(cores.p[k]) + (int64_t)ik[k] * Rk * Rk1;
-                const int last = Rk * Rk1 - 1;
-                float w[kMaxRank];
-#pragma unroll
-                for (int c = 0; c < kMaxRank; ++c) w[c] = 0.f;
-                for (int c = 0; c < Rk1; ++c) {
-                    float col[kMaxRank];
-#pragma unroll
-                    for (int r = 0; r < kMaxRank; ++r) col[r] = A[min(r + Rk * c, last)];
-                    float acc = 0.f;
-#pragma unroll
-                    for (int r = 0; r < kMaxRank; ++r) acc += r < Rk ? v[r] * col[r] : 0.f;
-#pragma unroll
-                    for (int q = 0; q < kMaxRank; ++q)
-                        if (q == c) w[q] = acc;
-                }
-#pragma unroll
-                for (int c = 0; c < kMaxRank; ++c) v[c] = w[c];
-            }
-            for (int r = 0; r < R0; ++r) out[r] = v[r];
-        }
+        recon_rows<16, kMaxOrder - 1>(d, cores, sidx, sS, SP);
     }
     for (int e = tid; e < kRmCols * (2 * KT - RR); e += blockDim.x) {   // K padding
         const int jj = e / (2 * KT - RR);
@@ -411,8 +356,8 @@ __global__ __launch_bounds__(256) void k_recon_mfma(tr_desc d, Ptrs cores, const
         // Split the block's rows: every thread reads its share of sS into
         // registers (and its largest magnitude), then, after the block's
         // largest is known and every read is done, writes the hi/lo halves
-        // over the same LDS (row pitch HP halves; the FP32 rows, the staged
-        // slices and column indices behind them are no longer needed).
+        // over the same LDS (row pitch HP halves; the FP32 rows and
+        // the column indices behind them are no longer needed).
         constexpr int K16 = KT / 8, KW = 16 * K16, HP = KW + 8;
         constexpr int PT = kRmCols * KW / 256;   // values per thread
         float v[PT];
@@ -443,74 +388,95 @@ __global__ __launch_bounds__(256) void k_recon_mfma(tr_desc d, Ptrs cores, const
         h16x8 bh[K16], bl[K16];
         int it_loaded = -1;
         double bscale = 0.0;   // 2^-(eA + escale): applied in FP64, exact at any tensor scale
-        // X_true entries of pair pr, read at clamped indices and kept as
-        // loaded (no select on them, which would wait for the load at
-        // once); entries outside the tensor are skipped where they are used
-        auto load_x = [&](int pr, TX (&x)[16]) {
-            const int it = pr >> 2, ct = pr & 3;
-            const int i = 32 * it + lc;
-            const int64_t ic = i < I0 ? i : I0 - 1;
-            const int64_t* offw = sOff + 32 * ct + 4 * lh;
+        // The pairs of the wavefront; O32: every entry lies within 4 GiB of
+        // X_true's base at a non-negative offset, and a column's byte offset is
+        // one 32-bit value (four of a lane's columns to an LDS read) added to
+        // the lane's own.
+        const int nc = (int)(J - j0 < kRmCols ? J - j0 : kRmCols);   // the block's columns
+        auto sweep = [&](auto o32) {
+            constexpr bool O32 = decltype(o32)::value;
+            // X_true entries of pair pr, read at clamped indices and kept as
+            // loaded (no select on them, which would wait for the load at
+            // once); entries outside the tensor are skipped where they are used
+            auto load_x = [&](int pr, TX (&x)[16]) {
+                const int it = pr >> 2, ct = pr & 3;
+                const int i = 32 * it + lc;
+                const int64_t ic = i < I0 ? i : I0 - 1;
+                if constexpr (O32) {
+                    const uint32_t oi = (uint32_t)ic * (uint32_t)xs0 * (uint32_t)sizeof(TX);
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int64_t o = offw[8 * (r >> 2) + (r & 3)];
-                x[r] = Xt[(o >= 0 ? o : 0) + ic * xs0];
-            }
-        };
-        auto pair = [&](int pr, const TX (&x)[16]) {
-            const int it = pr >> 2, ct = pr & 3;
-            const int i = 32 * it + lc;
-            const bool iok = i < I0;
-            if (it != it_loaded) {   // B fragment of row tile it, kept across its column tiles
-                it_loaded = it;
-                const h16x8* sh = reinterpret_cast<const h16x8*>(Bh) + (int64_t)it * K16 * 64 + l;
-                const h16x8* sl = reinterpret_cast<const h16x8*>(Bl) + (int64_t)it * K16 * 64 + l;
+                    for (int q = 0; q < 4; ++q) {
+                        const uint4 o = *reinterpret_cast<const uint4*>(sOff32 + 32 * ct + 4 * lh + 8 * q);
+                        const char* base = reinterpret_cast<const char*>(Xt);
+                        x[4 * q] = *reinterpret_cast<const TX*>(base + (o.x + oi));
+                        x[4 * q + 1] = *reinterpret_cast<const TX*>(base + (o.y + oi));
+                        x[4 * q + 2] = *reinterpret_cast<const TX*>(base + (o.z + oi));
+                        x[4 * q + 3] = *reinterpret_cast<const TX*>(base + (o.w + oi));
+                    }
+                } else {
+                    const int64_t* offw = sOff + 32 * ct + 4 * lh;
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) {
+                        const int64_t o = offw[8 * (r >> 2) + (r & 3)];
+                        x[r] = Xt[(o >= 0 ? o : 0) + ic * xs0];
+                    }
+                }
+            };
+            auto pair = [&](int pr, const TX (&x)[16]) {
+                const int it = pr >> 2, ct = pr & 3;
+                const bool iok = 32 * it + lc < I0;
+                if (it != it_loaded) {   // B fragment of row tile it, kept across its column tiles
+                    it_loaded = it;
+                    const h16x8* sh = reinterpret_cast<const h16x8*>(Bh) + (int64_t)it * K16 * 64 + l;
+                    const h16x8* sl = reinterpret_cast<const h16x8*>(Bl) + (int64_t)it * K16 * 64 + l;
+#pragma unroll
+                    for (int q = 0; q < K16; ++q) {
+                        bh[q] = sh[q * 64];
+                        bl[q] = sl[q * 64];
+                    }
+                    bscale = ldexp(1.0, -(eA + escale[it]));
+                }
+                const h16x8* ah = reinterpret_cast<const h16x8*>(Ah + (32 * ct + lc) * HP + 8 * lh);
+                const h16x8* al = reinterpret_cast<const h16x8*>(Al + (32 * ct + lc) * HP + 8 * lh);
+                f32x16 acc;
+#pragma unroll
+                for (int r = 0; r < 16; ++r) acc[r] = 0.f;
 #pragma unroll
                 for (int q = 0; q < K16; ++q) {
-                    bh[q] = sh[q * 64];
-                    bl[q] = sl[q * 64];
+                    const h16x8 a_h = ah[2 * q], a_l = al[2 * q];
+                    acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(a_l, bh[q], acc, 0, 0, 0);
+                    acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(a_h, bl[q], acc, 0, 0, 0);
+                    acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(a_h, bh[q], acc, 0, 0, 0);
                 }
-                bscale = ldexp(1.0, -(eA + escale[it]));
-            }
-            const int64_t* offw = sOff + 32 * ct + 4 * lh;
-            const h16x8* ah = reinterpret_cast<const h16x8*>(Ah + (32 * ct + lc) * HP + 8 * lh);
-            const h16x8* al = reinterpret_cast<const h16x8*>(Al + (32 * ct + lc) * HP + 8 * lh);
-            f32x16 acc;
+                const bool full = 32 * ct + 32 <= nc;   // uniform
+                if (iok) {
 #pragma unroll
-            for (int r = 0; r < 16; ++r) acc[r] = 0.f;
-#pragma unroll
-            for (int q = 0; q < K16; ++q) {
-                const h16x8 a_h = ah[2 * q], a_l = al[2 * q];
-                acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(a_l, bh[q], acc, 0, 0, 0);
-                acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(a_h, bl[q], acc, 0, 0, 0);
-                acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(a_h, bh[q], acc, 0, 0, 0);
-            }
-            if (iok) {
-#pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const int64_t o = offw[8 * (r >> 2) + (r & 3)];
-                    if (o < 0) continue;
-                    const double xd = (double)Cvt<TX>::to_f32(x[r]);
-                    const double df = (double)acc[r] * bscale - xd;
-                    err += df * df;
-                    xx += xd * xd;
+                    for (int r = 0; r < 16; ++r) {
+                        if (!full && 32 * ct + 4 * lh + 8 * (r >> 2) + (r & 3) >= nc) continue;
+                        const double xd = (double)Cvt<TX>::to_f32(x[r]);
+                        const double df = (double)acc[r] * bscale - xd;
+                        err += df * df;
+                        xx += xd * xd;
+                    }
+                }
+            };
+            // Two register buffers in turn: the entries of the next pair are
+            // requested before this pair's products, so a pair's X_true reads
+            // have a whole pair of matrix work to arrive in.
+            TX xa[16], xb[16];
+            const int pb = w * nti, pe = (w + 1) * nti;
+            load_x(pb, xa);
+            for (int pr = pb; pr < pe; pr += 2) {
+                if (pr + 1 < pe) load_x(pr + 1, xb);
+                pair(pr, xa);
+                if (pr + 1 < pe) {
+                    if (pr + 2 < pe) load_x(pr + 2, xa);
+                    pair(pr + 1, xb);
                 }
             }
         };
-        // Two register buffers in turn: the entries of the next pair are
-        // requested before this pair's products, so a pair's X_true reads
-        // have a whole pair of matrix work to arrive in.
-        TX xa[16], xb[16];
-        const int pb = w * nti, pe = (w + 1) * nti;
-        load_x(pb, xa);
-        for (int pr = pb; pr < pe; pr += 2) {
-            if (pr + 1 < pe) load_x(pr + 1, xb);
-            pair(pr, xa);
-            if (pr + 1 < pe) {
-                if (pr + 2 < pe) load_x(pr + 2, xa);
-                pair(pr + 1, xb);
-            }
-        }
+        if (off32) sweep(std::true_type{});   // uniform
+        else sweep(std::false_type{});
     } else {
         float b[KT];
         int it_loaded = -1;
@@ -554,8 +520,24 @@ __global__ __launch_bounds__(256) void k_recon_mfma(tr_desc d, Ptrs cores, const
 }
 
 static size_t recon_mfma_shm(int KT) {
-    return (size_t)kRmCols * 8 + (size_t)kRmCols * (2 * KT + 1) * 4 + (size_t)kRmMaxOuter * kMaxRR * 4 +
-           (size_t)kRmCols * 8;   // per-column i_2 and i_3 (order 3)
+    return (size_t)kRmCols * 8 + (size_t)kRmCols * (2 * KT + 1) * 4 + (size_t)kRmCols * kMaxOrder * 4;
+}
+
+// Diagonal blocks of the chain operands: every rank within 4, 8 or 16.
+static int recon_rb(const tr_desc& d) {
+    const int r = shape_of(d).maxR;
+    return r <= 4 ? 4 : (r <= 8 ? 8 : 16);
+}
+
+// Every entry's byte offset fits 32 bits: then the error kernel addresses X_true
+// with one 32-bit addition an entry.
+static bool recon_off32(const tr_desc& d, size_t size) {
+    double span = 0.0;
+    for (int k = 0; k < d.N; ++k) {
+        if (d.x_stride[k] < 0) return false;
+        span += (double)(d.I[k] - 1) * (double)d.x_stride[k];
+    }
+    return (span + 1.0) * (double)size <= 4294967296.0;
 }
 
 static int64_t recon_mfma_blocks(const tr_desc& d) {
@@ -582,7 +564,7 @@ static hipError_t launch_recon_write(const tr_desc& d, Ptrs cores, TX* Xo, hipSt
         if (!allow_lds(reinterpret_cast<const void*>(&k_recon_mfma<TX, KTV, 1>), shm))                  \
             return hipErrorInvalidConfiguration;                                                         \
         hipLaunchKernelGGL((k_recon_mfma<TX, KTV, 1>), grid, block, shm, st, d, cores, (const TX*)nullptr, Xo, \
-                           nullptr, nullptr, nullptr, nullptr);                                          \
+                           nullptr, nullptr, nullptr, nullptr, recon_rb(d), 0);                          \
         break;
     switch (KT) {
         TRK_RM(8)
@@ -608,7 +590,7 @@ static hipError_t launch_recon_h3(const tr_desc& d, Ptrs cores, const _Float16* 
         if (!allow_lds(reinterpret_cast<const void*>(&k_recon_mfma<TX, 8 * K, 0>), shm))                 \
             return hipErrorInvalidConfiguration;                                                          \
         hipLaunchKernelGGL((k_recon_mfma<TX, 8 * K, 0>), grid, block, shm, st, d, cores, Xt, (TX*)nullptr, \
-                           part, Bh, Bl, escale);                                                         \
+                           part, Bh, Bl, escale, recon_rb(d), (int)recon_off32(d, sizeof(TX)));           \
         break;
     switch (K16) {
         TRK_RH(1)

@@ -6,7 +6,7 @@ import torch
 
 import tr_inputs as ti
 from gpu_util import DEV, TOL, fold, problem, rel, rounded, say, to_dev, unfold
-from oracle import brsgd, entry, sampling
+from oracle import brsgd, entry, sampling, tr
 from paper_2303_16492_amd import _lib as L
 from paper_2303_16492_amd import api
 from paper_2303_16492_amd.driver import TRSolver
@@ -325,3 +325,30 @@ def test_optimal_law_from_replicas(I, R, prec):
         w = _weights(solver.cdf_J[:J])
         assert int(solver.status.item()) == 0
         assert np.max(np.abs(w - sampling.quantize(q).astype(np.int64))) <= 64 + 16 * np.max(q)
+
+
+# the chains of the error kernel: ranks within 4, 8 and 16 (R_1 R_2 <= 128),
+# orders 2 to 8, columns below, at and past one block of 128 and of 32, rows
+# around one tile of 32; entries in paper order, reversed order and (``far``)
+# more than 4 GiB apart
+@pytest.mark.parametrize("I,R,order", [([33, 5], [4, 3], "paper"), ([40, 130], [8, 16], "paper"), ([31, 16, 8], [3, 4, 2], "reversed"),
+                                       ([32, 43, 3], [8, 5, 7], "paper"), ([70, 9, 31], [10, 11, 16], "reversed"),
+                                       ([5, 4, 3, 9], [9, 13, 2, 16], "paper"), ([9, 4, 3, 5, 6], [7, 8, 6, 7, 5], "reversed"),
+                                       ([3, 2, 3, 2, 3, 2, 4], [4, 3, 9, 2, 5, 3, 4], "paper"),
+                                       ([2, 3, 2, 3, 2, 3, 2, 3], [3, 2, 3, 4, 2, 3, 2, 3], "reversed"),
+                                       ([6, 5, 7], [5, 4, 3], "far"), ([6, 5, 7, 3], [9, 12, 3, 4], "far")])
+@pytest.mark.parametrize("xdt", [torch.float32, torch.float16])
+def test_relative_error_chains(I, R, order, xdt):
+    I, R, cores, X, dcores, dX = problem(53, len(I), I, R, torch.float32)
+    X = rounded(X, xdt)
+    strides = api.paper_strides(I)
+    if order == "reversed":
+        strides = [int(np.prod(I[k + 1:])) for k in range(len(I))]
+    if order == "far":
+        strides[-1] = 1 << 29
+    flat = torch.empty(1 + sum((i - 1) * s for i, s in zip(I, strides)), dtype=xdt, device=DEV)
+    flat.as_strided(I, strides).copy_(to_dev(X, xdt))
+    desc = api.make_desc(I, R, torch.float32, xdt, strides)
+    say("relative error chains", I, R, order, xdt)
+    got = float(api.tr_relerr(desc, dcores, flat))
+    assert abs(got / tr.rse(cores, X) - 1) < 1e-5
