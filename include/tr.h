@@ -82,7 +82,7 @@ enum {
     TR_DEV_NONFINITE = 1,   /* NaN/Inf met in an update                  */
     TR_DEV_NOT_SPD = 2,     /* Gram not positive definite even damped    */
     TR_DEV_ZERO_DIST = 4,   /* law with zero total mass; uniform used    */
-    TR_DEV_DAMPED = 8       /* Cholesky needed the damping fallback      */
+    TR_DEV_DAMPED = 8       /* the inverse needed the damping fallback   */
 };
 
 typedef enum { TR_F64 = 0, TR_F32 = 1, TR_F16 = 2, TR_BF16 = 3 } tr_dtype;
@@ -143,7 +143,8 @@ int32_t tr_mode(uint64_t seed, uint64_t step, int32_t N);
  * Leverage scores are l_i = g_i^T (G^T G)^{-1} g_i with the FP64 Gram
  * G^T G of G = G_{k(2)}, inverted by the blocked FP64 sweep.  The rank is
  * found on the Gram: when a pivot of that factorisation is at or below
- * 2^-43 of the largest diagonal entry, or when I_k <= R_k R_{k+1}, the
+ * 2^-43 of the largest diagonal entry (of G G^T where I_k <= R_k R_{k+1}:
+ * past that test its rank is I_k and the law uniform), the
  * scores come from a Cholesky with diagonal pivoting of G^T G stopped at
  * pivots <= R_k R_{k+1} 2^-52 max diag: the rank r is the number of pivots
  * taken, l_i = g_i[P]^T (G_P^T G_P)^{-1} g_i[P] over the chosen columns P

@@ -12,7 +12,7 @@
 //          the same sampled rows to 16 mantissa bits (a scaled step built from
 //          mismatched rows is off by that mismatch times the condition
 //          number of the Gram).
-//   Gram   FP64 (separate kernel), Cholesky FP64.
+//   Gram   FP64 (separate kernel), inverse FP64.
 //
 // Tiles as in the FP32 kernel: block = 4 wavefronts = 64 rows x groups of
 // 64-sample chunks.  Operand layouts of v_mfma_f32_16x16x32_{bf16,f16}
