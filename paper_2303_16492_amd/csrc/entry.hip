@@ -11,11 +11,12 @@
 // Forward: a few packs of entries per wavefront; the trace is the sum of T^T S
 // over the last slice.  Only the residuals leave the kernel.
 //
-// Backward: a workgroup owns the gradient slice of one (core, index).  Each of
+// Backward: a workgroup owns the gradient slice of one (core, index), or of one
+// part of the batch where the mode has few indices.  Each of
 // its wavefronts scans its share of the batch's indices of that mode, compacts
 // the entries that fall on the slice into an LDS list in entry order, forms
 // their M_{!=k} and adds r M_{!=k} by accumulating the chain's last product;
-// the wavefronts' sums are added in a fixed order.  No float atomics: results
+// the wavefronts' sums and the parts are added in a fixed order.  No float atomics: results
 // are bitwise reproducible.  (One 4-byte compare per entry and slice is far
 // cheaper than private gradient slices per workgroup, whose zeroing, scattered
 // read-modify-writes and reduction took most of the time, or than a stable
@@ -131,9 +132,12 @@ __global__ __launch_bounds__(kEntBlock, NM <= 5 ? 4 : 2) void k_entry_fwd(tr_des
     if (threadIdx.x == 0) part[blockIdx.x] = tot;
 }
 
-// First workgroup of each mode in the backward's grid.
+// The backward's grid: mode k's workgroups start at base[k], ``parts[k]`` of them
+// (one a range of the batch) for each of its I_k slices.  at[k]: where the
+// partial gradients of a mode of several parts start.
 struct EntGroups {
-    int64_t base[kMaxOrder + 1];
+    int64_t base[kMaxOrder + 1], at[kMaxOrder];
+    int parts[kMaxOrder];
 };
 constexpr int kBwdWaves = 16;     // at most
 constexpr int64_t kBwdGrid = 1 << 22;
@@ -141,8 +145,12 @@ constexpr int64_t kBwdGrid = 1 << 22;
 // 4096, at least 512 (a 16 x 16 partial tile fits the list's 2-byte places).
 constexpr int kBwdWindow = 4096, kBwdWindowMin = 512;
 
-// Gradient slice (k, i), number base[k] + i (see the top of the file), one per
-// workgroup up to a grid of kBwdGrid.  An entry with an invalid index in another mode contributes nothing.
+// Part p of gradient slice (k, i) (see the top of the file): the entries of the
+// p-th of parts[k] equal ranges of the batch, to grads.p[k] + p I_k R_k R_{k+1}.
+// One per workgroup up to a grid of kBwdGrid.  An entry with an invalid index in
+// another mode contributes nothing.  The FP32 accumulator covers at most 64 entries
+// of the list before it is added to an FP64 total, so the rounding of a slice does
+// not grow with the entries that fall on it.
 template <int RB, bool VEC, int NM, typename OT>
 __global__ __launch_bounds__(64 * kBwdWaves) void k_entry_bwd(tr_desc d, Ptrs cores, const int32_t* __restrict__ idx,
                                                               const float* __restrict__ resid, int B, float scale,
@@ -159,18 +167,19 @@ __global__ __launch_bounds__(64 * kBwdWaves) void k_entry_bwd(tr_desc d, Ptrs co
         resolve_mode(only, N, &t, &step_mode);
     }
     int k = 0;
-    for (int64_t slice = blockIdx.x; slice < gr.base[N]; slice += gridDim.x) {
-        while (k + 1 < N && slice >= gr.base[k + 1]) ++k;
+    for (int64_t unit = blockIdx.x; unit < gr.base[N]; unit += gridDim.x) {
+        while (k + 1 < N && unit >= gr.base[k + 1]) ++k;
         if (block && step_mode != k) continue;   // uniform
-        const int i = (int)(slice - gr.base[k]), k0 = ring_next(k, N);
+        const int parts = gr.parts[k], at_k = (int)(unit - gr.base[k]);
+        const int i = at_k / parts, part = at_k - i * parts, k0 = ring_next(k, N);
         uint16_t* list = reinterpret_cast<uint16_t*>(smem_raw) + w * window;
         // dL/dG_k of L = 1/(2B) sum r^2: the 1/B of the mean applied here
         const float sc = (float)((double)scale * (dscale ? *dscale : 1.0) / (double)B);
         const ChainSlots<float, NM - 1, VEC> sl(d, k0, N - 1, L);
         const bool in0 = L.col < d.R[k0];
-        ef4 acc = {0.f, 0.f, 0.f, 0.f};
-        const int64_t share = (((int64_t)B + W - 1) / W + 63) & ~63;
-        const int64_t s0 = w * share, s1 = min((int64_t)B, s0 + share);
+        double tot[4] = {0.0, 0.0, 0.0, 0.0};
+        const int64_t share = (((int64_t)B + W * parts - 1) / (W * parts) + 63) & ~63;
+        const int64_t s0 = ((int64_t)part * W + w) * share, s1 = min((int64_t)B, s0 + share);
         for (int64_t w0 = s0; w0 < s1; w0 += window) {
             const int len = (int)min((int64_t)window, s1 - w0);
             int n = 0;   // uniform
@@ -195,6 +204,7 @@ __global__ __launch_bounds__(64 * kBwdWaves) void k_entry_bwd(tr_desc d, Ptrs co
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
             __builtin_amdgcn_wave_barrier();
             for (int q0 = 0; q0 < n; q0 += 64) {
+                ef4 acc = {0.f, 0.f, 0.f, 0.f};
                 int nb = min(64, n - q0);
                 const int64_t b = w0 + list[q0 + (l < nb ? l : nb - 1)];
                 float rl = resid[b] * sc;
@@ -272,38 +282,93 @@ __global__ __launch_bounds__(64 * kBwdWaves) void k_entry_bwd(tr_desc d, Ptrs co
 #pragma unroll 1
                 for (; at + U * P <= nb; at += U * P) round(at, std::false_type{});
                 if (at < nb) round(at, std::true_type{});
+#pragma unroll
+                for (int j = 0; j < 4; ++j) tot[j] += (double)acc[j];
             }
         }
         // the packed blocks, then the wavefronts, in a fixed order
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-            if constexpr (RB == 4) acc[j] += __shfl_xor(acc[j], 20, 64);
-            if constexpr (RB <= 8) acc[j] += __shfl_xor(acc[j], 40, 64);
+            if constexpr (RB == 4) tot[j] += __shfl_xor(tot[j], 20, 64);
+            if constexpr (RB <= 8) tot[j] += __shfl_xor(tot[j], 40, 64);
         }
         const int Rk = d.R[k], RR = Rk * d.R[k0];
         __syncthreads();   // every list has been read
-        float* part = reinterpret_cast<float*>(smem_raw);   // [wavefronts][RB * RB]
+        float* wsum = reinterpret_cast<float*>(smem_raw);   // [wavefronts][RB * RB]
         if (L.on[0] && L.p == 0) {
 #pragma unroll
-            for (int j = 0; j < 4; ++j) part[w * (RB * RB) + L.col * RB + L.row[j]] = acc[j];
+            for (int j = 0; j < 4; ++j) wsum[w * (RB * RB) + L.col * RB + L.row[j]] = (float)tot[j];
         }
         __syncthreads();
+        float* out = static_cast<float*>(grads.p[k]) + ((int64_t)part * d.I[k] + i) * RR;
         for (int e = tid; e < RR; e += blockDim.x) {
-            const float* p = part + (e / Rk) * RB + e % Rk;
-            float sum = 0.f;
-            for (int v = 0; v < W; ++v) sum += p[v * (RB * RB)];
-            static_cast<float*>(grads.p[k])[(int64_t)i * RR + e] = sum;
+            const float* p = wsum + (e / Rk) * RB + e % Rk;
+            double sum = 0.0;
+            for (int v = 0; v < W; ++v) sum += (double)p[v * (RB * RB)];
+            out[e] = (float)sum;
         }
         __syncthreads();   // the partial tiles have been read
     }
 }
+
+// Entry o of core k's gradient from its partial sums at ``g`` (mode k's), in part
+// order.
+__device__ __forceinline__ double entry_part_sum(const float* __restrict__ g, int64_t o, int parts, int64_t len) {
+    double s = (double)g[o];
+#pragma unroll 8
+    for (int p = 1; p < parts; ++p) s += (double)g[o + p * len];
+    return s;
+}
+
+// Element e of all cores, core after core: its core, its place there, the core's
+// length.
+__device__ __forceinline__ int entry_core_of(const tr_desc& d, int64_t e, int64_t* o, int64_t* len) {
+    int k = 0;
+    for (;; ++k) {
+        *len = (int64_t)d.I[k] * d.R[k] * d.R[ring_next(k, d.N)];
+        if (e < *len) break;
+        e -= *len;
+    }
+    *o = e;
+    return k;
+}
+
+// The gradients of the modes of several parts.
+__global__ __launch_bounds__(256) void k_entry_bwd_sum(tr_desc d, const float* __restrict__ gpart, EntGroups gr,
+                                                       int64_t slice_len, MutPtrs grads) {
+    const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (e >= slice_len) return;
+    int64_t o, len;
+    const int k = entry_core_of(d, e, &o, &len);
+    if (gr.parts[k] > 1) static_cast<float*>(grads.p[k])[o] = (float)entry_part_sum(gpart + gr.at[k], o, gr.parts[k], len);
+}
+
+// Split of the batch.  A slice's workgroup gets more wavefronts until one's share
+// is kBwdShare entries, unless there are so many slices that the wavefronts' fixed
+// cost is what counts (kBwdSplit of them in all): a wavefront walks its hits in a
+// chain of dependent loads, some 0.4 us an entry, so the share bounds it however
+// the entries fall on the slices.  Modes of so few indices that a wavefront expects
+// more than kBwdHits entries, and batches past kBwdFar entries a wavefront, are
+// split over several workgroups per slice, at most kBwdParts and kBwdPartBytes of
+// partial gradients.
+//
+// Backward of uniform batches in us, one workgroup a slice with its wavefronts by
+// the number of slices alone, against this split: sizes 2049, 5, 6, ranks 4/8/4, B
+// 65536: 1942, 110; 14456, 826, 580, 9, 2, ranks 3/2/2/7/8, B 7975: 1444, 142; 2 and
+// 145, ranks 16/6, B 15486: 99, 34; 1 and 1, ranks 16/12, B 65536: 686, 34.  Half of
+// the batch on one index of every mode, 301 x 250 x 127, ranks 10/9/7, B 16384: 1136,
+// 633 (uniform: 31).  kBwdSplit 4 times as large: 150 and 162 for the first two.
+constexpr int kBwdShare = 2048, kBwdHits = 128, kBwdFar = 8192, kBwdParts = 512;
+constexpr int64_t kBwdSplit = 1 << 15;
+constexpr int64_t kBwdPartBytes = (int64_t)8 << 20;   // a mode
 
 struct EntryPlan {
     int fwd_blocks, fwd_iters, rb, nm, waves, window;
     bool vec, big;   // big: a core of 4 GiB or more
     int64_t slice_len;
     EntGroups gr;
-    size_t part_off, total;
+    int64_t part_len;                    // floats of the partial gradients
+    size_t part_off, gpart_off, total;
 };
 
 static EntryPlan entry_plan(const tr_desc& d, int B) {
@@ -328,10 +393,23 @@ static EntryPlan entry_plan(const tr_desc& d, int B) {
     // scan each
     P.waves = 1;
     while (P.waves < kBwdWaves && 2 * P.gr.base[d.N] * P.waves <= 4096 && (int64_t)64 * P.waves < B) P.waves *= 2;
+    const int64_t slices = P.gr.base[d.N];
+    while (P.waves < kBwdWaves && (int64_t)kBwdShare * P.waves < B && 2 * slices * P.waves <= kBwdSplit) P.waves *= 2;
+    for (int k = 0; k < d.N; ++k) {
+        const int64_t len = (int64_t)d.I[k] * d.R[k] * d.R[ring_next(k, d.N)];
+        const int64_t hits = (int64_t)d.I[k] * kBwdHits < kBwdFar ? (int64_t)d.I[k] * kBwdHits : kBwdFar;
+        const int64_t parts = std::min(std::min<int64_t>((B + hits * P.waves - 1) / (hits * P.waves), kBwdParts),
+                                       kBwdPartBytes / (len * 4));
+        P.gr.parts[k] = (int)std::max<int64_t>(1, parts);
+        P.gr.base[k + 1] = P.gr.base[k] + (int64_t)d.I[k] * P.gr.parts[k];
+        P.gr.at[k] = P.part_len;
+        if (P.gr.parts[k] > 1) P.part_len += len * P.gr.parts[k];
+    }
     const int64_t share = (((int64_t)B + P.waves - 1) / P.waves + 63) & ~(int64_t)63;
     P.window = (int)std::max<int64_t>(kBwdWindowMin, std::min<int64_t>(kBwdWindow, share));
     P.part_off = 0;
-    P.total = align_up((size_t)P.fwd_blocks * 8);
+    P.gpart_off = align_up((size_t)P.fwd_blocks * 8);
+    P.total = P.gpart_off + align_up((size_t)P.part_len * 4);
     return P;
 }
 
@@ -388,24 +466,18 @@ __global__ __launch_bounds__(1024) void k_completion_loss(tr_desc d, const doubl
 // The update; its last block advances the step counter.
 __global__ __launch_bounds__(256) void k_completion_update(tr_desc d, const uint64_t* __restrict__ t_dev,
                                                            uint64_t seed, int block, MutPtrs cores, MutPtrs accum,
-                                                           const float* __restrict__ grads, int64_t slice_len,
+                                                           const float* __restrict__ grads, EntGroups gr, int64_t slice_len,
                                                            double lam, tr_step rule, int32_t* status, StepBump step) {
     const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const bool reads_t = block || rule.kind == 2;
     if (e < slice_len) {
         const uint64_t t = reads_t ? *t_dev : 0;
-        int k = 0;
-        int64_t base = 0;
-        for (; k < d.N; ++k) {
-            const int64_t len = (int64_t)d.I[k] * d.R[k] * d.R[ring_next(k, d.N)];
-            if (e < base + len) break;
-            base += len;
-        }
+        int64_t o, len;
+        const int k = entry_core_of(d, e, &o, &len);
         if (!block || k == pick_mode(seed, t, d.N)) {
             float* G = static_cast<float*>(cores.p[k]);
             float* A = static_cast<float*>(accum.p[k]);
-            const int64_t o = e - base;
-            const double p = -((double)grads[e] + lam * (double)G[o]);
+            const double p = -(entry_part_sum(grads + gr.at[k], o, gr.parts[k], len) + lam * (double)G[o]);
             apply_rule(G, A, o, p, rule, t, status);
         }
     }
@@ -461,7 +533,8 @@ struct BwdLaunch {
     }
 };
 
-// ``block`` nonzero: only the core of ``only``'s mode.
+// ``block`` nonzero: only the core of ``only``'s mode.  grads: of a mode of several
+// parts its partial sums.
 static hipError_t launch_entry_bwd(const tr_desc& d, const EntryPlan& P, Ptrs cp, const int32_t* idx,
                                    const float* resid, int B, float scale, const double* scale_dev, ModeSrc only,
                                    int block, MutPtrs grads, hipStream_t st) {
@@ -479,7 +552,7 @@ struct CompletionWs {
 static CompletionWs completion_layout(const tr_desc& d, int B) {
     CompletionWs L{};
     L.P = entry_plan(d, B);
-    size_t o = align_up(L.P.total);
+    size_t o = align_up(L.P.gpart_off);   // the forward's part of the plan; the gradient parts are ``grads``
     L.bidx = o;
     o += align_up((size_t)B * d.N * 4);
     L.bx = o;
@@ -487,7 +560,12 @@ static CompletionWs completion_layout(const tr_desc& d, int B) {
     L.resid = o;
     o += align_up((size_t)B * 4);
     L.grads = o;
-    o += align_up((size_t)L.P.slice_len * 4);
+    int64_t len = 0;   // every mode's partial sums, or its gradient
+    for (int k = 0; k < d.N; ++k) {
+        L.P.gr.at[k] = len;
+        len += (int64_t)d.I[k] * d.R[k] * d.R[ring_next(k, d.N)] * L.P.gr.parts[k];
+    }
+    o += align_up((size_t)len * 4);
     L.ctr = o;
     o += align_up(4);
     L.total = o;
@@ -558,13 +636,20 @@ tr_status tr_entry_bwd(const tr_desc* d, const void* const* cores, const int32_t
     hipStream_t st = (hipStream_t)stream;
     Ptrs cp{};
     MutPtrs gp{};
+    float* gpart = reinterpret_cast<float*>(static_cast<char*>(ws) + P.gpart_off);
+    MutPtrs to{};   // where the slices go: grads, or the parts
     for (int k = 0; k < d->N; ++k) {
         cp.p[k] = cores[k];
         gp.p[k] = grads[k];
+        to.p[k] = P.gr.parts[k] > 1 ? static_cast<void*>(gpart + P.gr.at[k]) : grads[k];
     }
-    return launch_entry_bwd(*d, P, cp, idx, resid, B, (float)scale, scale_dev, ModeSrc{}, 0, gp, st) == hipSuccess
-               ? TR_OK
-               : TR_E_HIP;
+    hipError_t e = launch_entry_bwd(*d, P, cp, idx, resid, B, (float)scale, scale_dev, ModeSrc{}, 0, to, st);
+    if (e == hipSuccess && P.part_len > 0) {
+        hipLaunchKernelGGL(k_entry_bwd_sum, dim3((unsigned)((P.slice_len + 255) / 256)), dim3(256), 0, st, *d, gpart,
+                           P.gr, P.slice_len, gp);
+        e = hipGetLastError();
+    }
+    return e == hipSuccess ? TR_OK : TR_E_HIP;
 }
 
 static tr_status completion_checks(const tr_desc* d, const tr_completion_config* c) {
@@ -609,13 +694,11 @@ tr_status tr_completion_run(const tr_desc* d, void* const* cores, void* const* a
     unsigned* ctr = reinterpret_cast<unsigned*>(w + L.ctr);
     Ptrs cp{};
     MutPtrs mc{}, ac{}, gp{};
-    int64_t off = 0;
     for (int k = 0; k < d->N; ++k) {
         cp.p[k] = cores[k];
         mc.p[k] = cores[k];
         ac.p[k] = accum ? accum[k] : nullptr;
-        gp.p[k] = grads + off;
-        off += (int64_t)d->I[k] * d->R[k] * d->R[ring_next(k, d->N)];
+        gp.p[k] = grads + L.P.gr.at[k];
     }
     const int B = c->B;
     const dim3 gd((unsigned)((B + 255) / 256));
@@ -640,7 +723,7 @@ tr_status tr_completion_run(const tr_desc* d, void* const* cores, void* const* a
         if (launch_entry_bwd(*d, L.P, cp, bidx, resid, B, 1.0f, nullptr, only, (int)c->block, gp, st) != hipSuccess)
             return TR_E_HIP;
         hipLaunchKernelGGL(k_completion_update, gu, dim3(256), 0, st, *d, t_dev, c->seed, (int)c->block, mc, ac,
-                           grads, L.P.slice_len, c->lambda, c->rule, dev_status, StepBump{t_dev, ctr});
+                           grads, L.P.gr, L.P.slice_len, c->lambda, c->rule, dev_status, StepBump{t_dev, ctr});
         if (hipGetLastError() != hipSuccess) return TR_E_HIP;
     }
     return TR_OK;
