@@ -98,7 +98,10 @@ hipError_t launch_zero_u32(unsigned* p, int n, hipStream_t st) {
 
 constexpr int kMaxM = 1 << 24;
 
-// Workspace plan of tr_run.
+// Workspace plan of tr_run.  The laws' workspaces lie over the step's buffers: a
+// law is formed between two steps on the stream that orders them (the second
+// stream's work of a step is joined before its update), so neither holds anything
+// the other still reads.
 struct RunWs {
     size_t idx, pF, S, g, gram, idxH, pH, SH, grad, gramws, upd, dist, opt, loss, ctr, mode, total;
     GradWs gl;
@@ -106,7 +109,7 @@ struct RunWs {
     UpdWs ul;
 };
 
-static RunWs run_layout(const tr_problem* p, const tr_config* c) {
+static RunWs run_layout_of(const tr_problem* p, const tr_config* c, const GradWs& gl) {
     RunWs L{};
     const tr_desc& d = p->desc;
     const Shape sh = shape_of(d);
@@ -126,20 +129,32 @@ static RunWs run_layout(const tr_problem* p, const tr_config* c) {
     L.idxH = take(mH > 0 ? (size_t)mH * d.N * 4 : 0);
     L.pH = take(mH > 0 ? (size_t)mH * 8 : 0);
     L.SH = take(mH > 0 ? (size_t)mH * sh.maxRR * es : 0);
-    L.gl = grad_ws_layout(d, m, c->prec);
+    L.gl = gl;
     L.grad = take(L.gl.total);
     L.ml = gram_ws_layout(d, m);
     L.mlH = gram_ws_layout(d, mH > 0 ? mH : m);
     L.gramws = take(L.ml.total > L.mlH.total ? L.ml.total : L.mlH.total);
     L.ul = upd_ws_layout(d);
     L.upd = take(L.ul.total);
-    L.dist = take(dist_ws_bytes(d, c->law));
-    L.opt = take(c->law == TR_LAW_OPTIMAL ? dist_opt_ws_bytes(d) : 0);
+    L.dist = L.opt = 0;
+    const size_t law = align_up(c->law == TR_LAW_OPTIMAL ? dist_opt_ws_bytes(d) : dist_ws_bytes(d, c->law));
+    if (o < law) o = law;
     L.loss = take(8);
     L.ctr = take(4);
     L.mode = take(4);
     L.total = o;
     return L;
+}
+
+// As many sample groups of the gradient as serve its speed, unless fewer let the
+// run fit the library's own scratch.
+static RunWs run_layout(const tr_problem* p, const tr_config* c) {
+    constexpr size_t kScratch = TR_NOALLOC_SCRATCH_BYTES;
+    const RunWs L = run_layout_of(p, c, grad_ws_layout(p->desc, c->m, c->prec));
+    const size_t rest = L.total - align_up(L.gl.total);
+    if (L.total <= kScratch || rest >= kScratch) return L;
+    const RunWs F = run_layout_of(p, c, grad_ws_layout(p->desc, c->m, c->prec, kScratch - rest));
+    return F.total <= kScratch ? F : L;
 }
 
 // Workspace of tr_sweep_run: the step driver's layout for the largest block
@@ -168,7 +183,7 @@ static tr_config sweep_as_config(const tr_problem* p, const tr_sweep_config* c) 
 static SweepRunWs sweep_layout(const tr_problem* p, const tr_sweep_config* c) {
     SweepRunWs L{};
     const tr_config rc = sweep_as_config(p, c);
-    L.r = run_layout(p, &rc);
+    L.r = run_layout_of(p, &rc, grad_ws_layout(p->desc, rc.m, rc.prec));
     const tr_desc& d = p->desc;
     const size_t es = dtype_size(d.core_dtype);
     size_t o = L.r.total;

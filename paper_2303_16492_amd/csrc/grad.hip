@@ -57,7 +57,7 @@ __global__ __launch_bounds__(256) void k_grad_reduce(tr_desc d, ModeSrc ms, cons
     bump_if_last(step, rule.kind == 2);
 }
 
-GradWs grad_ws_layout(const tr_desc& d, int m, int prec) {
+GradWs grad_ws_layout(const tr_desc& d, int m, int prec, size_t cap) {
     GradWs L{};
     const Shape sh = shape_of(d);
     const bool f64 = d.core_dtype == TR_F64;
@@ -85,12 +85,16 @@ GradWs grad_ws_layout(const tr_desc& d, int m, int prec) {
         // blocks (the streaming FP32 form keeps its chunks of 64)
         else if (sh.maxRR <= 128 && 2 * ((m + 127) / 128) >= groups) L.tf = 128;
     }
+    // fewer groups where the partials would not fit ``cap`` (a multiple of 8
+    // when there are as many, see above); both forms take any number
+    const size_t es = f64 ? 8 : 4, per = (size_t)sh.maxI * sh.maxRR * es + (size_t)L.row_tiles * 8;
+    const size_t fit = cap > 512 ? (cap - 512) / per : 0;
+    if (fit < (size_t)groups) groups = fit >= 8 ? (int)(fit & ~(size_t)7) : (fit > 1 ? (int)fit : 1);
     const int nchunks = (m + L.tf - 1) / L.tf;
     groups = groups > nchunks ? nchunks : groups;
     const int cpg = (nchunks + groups - 1) / groups;
     L.groups = (nchunks + cpg - 1) / cpg;
     if (L.groups < 1) L.groups = 1;
-    const size_t es = f64 ? 8 : 4;
     L.gpart_off = 0;
     L.lpart_off = align_up((size_t)L.groups * sh.maxI * sh.maxRR * es);
     L.total = L.lpart_off + align_up((size_t)L.groups * L.row_tiles * 8);

@@ -90,7 +90,8 @@ struct GradWs {
     size_t gpart_off, lpart_off, total;
     int groups, row_tiles, ti, tf;
 };
-GradWs grad_ws_layout(const tr_desc& d, int m, int prec);
+// cap: the sample groups are as many as a total of this size holds, at least one.
+GradWs grad_ws_layout(const tr_desc& d, int m, int prec, size_t cap = SIZE_MAX);
 // FP64: rows of a block and samples of a staged chunk.
 constexpr int kGradF64Rows = 64, kGradF64Samples = 32;
 hipError_t launch_grad_f64(const tr_desc& d, ModeSrc ms, Ptrs cores, XSrc xs, const int32_t* idx, const double* S,
