@@ -10,6 +10,7 @@ device step counter, so successive replays continue the same trajectory.
 from __future__ import annotations
 
 import ctypes as C
+import sys
 
 import numpy as np
 import torch
@@ -39,6 +40,19 @@ def cores_to_device(cores3, dtype=torch.float32, device="cuda"):
 def cores_to_host(cores2, R):
     N = len(cores2)
     return [unfold_to_core(c.double().cpu().numpy(), R[k], R[(k + 1) % N]) for k, c in enumerate(cores2)]
+
+
+class StepGraph(torch.cuda.CUDAGraph):
+    """A captured run.  It replays into its solver's buffers (and into
+    ``loss_out``), so it keeps them alive; when it is dropped, the graph is
+    gone from the device before they are."""
+
+    owner = None
+
+    def __del__(self):
+        if self.owner is not None and not sys.is_finalizing():
+            self.reset()
+            torch.cuda.synchronize(self.owner[0].X.device)
 
 
 class TRSolver:
@@ -100,7 +114,8 @@ class TRSolver:
         """HIP graph of ``steps`` iterations (replay with graph.replay());
         with ``loss_out`` (``steps`` float64 on the device) every replay
         writes each step's loss estimate there."""
-        g = torch.cuda.CUDAGraph()
+        g = StepGraph()
+        g.owner = (self, loss_out)
         s = torch.cuda.Stream()
         s.wait_stream(torch.cuda.current_stream())
         with torch.cuda.stream(s):

@@ -1,0 +1,58 @@
+"""A captured run outlives the names of its solver and of its loss buffer."""
+import gc
+import weakref
+
+import numpy as np
+import pytest
+import torch
+
+import tr_inputs as ti
+from gpu_util import DEV, flat_paper, rounded, say, to_dev, unfold
+from oracle import tr
+
+pytestmark = pytest.mark.gpu
+
+from paper_2303_16492_amd import _lib as L  # noqa: E402
+from paper_2303_16492_amd import api  # noqa: E402
+from paper_2303_16492_amd.driver import TRSolver  # noqa: E402
+
+
+def _solver(prec, scaled=True, m_H=0, seed=3):
+    dtype = torch.float64 if prec == "f64" else torch.float32
+    I, R = [30, 25, 28], [3, 4, 3]
+    X = rounded(tr.full_tensor(ti.gaussian_cores(1, 3, I, R)), dtype)
+    cores = [to_dev(unfold(rounded(c, dtype)), dtype) for c in ti.gaussian_cores(2, 3, I, R, scale=0.5)]
+    return TRSolver(cores, to_dev(flat_paper(X), dtype), I, R, 200, scaled=scaled, prec=prec, m_H=m_H, seed=seed,
+                    rule=api.step_rule("fixed", alpha=0.5 if scaled else 0.05))
+
+
+@pytest.mark.parametrize("scaled", [False, True])
+def test_graph_keeps_what_it_replays_into(scaled, monkeypatch):
+    ref = _solver("f32", scaled)
+    ref.run(7)
+    torch.cuda.synchronize()
+    sol = _solver("f32", scaled)
+    losses = torch.zeros(3, dtype=torch.float64, device=DEV)
+    say("graph lifetime, scaled", scaled)
+    g = sol.capture(3, losses)
+    cores, alive, buf = sol.cores, weakref.ref(sol), weakref.ref(losses)
+    del sol, losses
+    gc.collect()
+    junk = [torch.full((1 << 18,), float("nan"), device=DEV) for _ in range(8)]   # takes freed blocks, if any are
+    g.replay()
+    g.replay()
+    torch.cuda.synchronize()
+    assert alive() is not None and buf() is not None
+    assert all(torch.equal(a, b) for a, b in zip(cores, ref.cores))
+    assert np.all(np.isfinite(buf().cpu().numpy()))
+    del junk
+    # dropped: the graph first, then the events and buffers
+    order = []
+    gone = L.HipEvent.__del__
+    monkeypatch.setattr(L.HipEvent, "__del__", lambda self: (order.append("event"), gone(self)))
+    reset = type(g).reset
+    monkeypatch.setattr(type(g), "reset", lambda self: (order.append("graph"), reset(self)), raising=False)
+    del g
+    gc.collect()
+    assert alive() is None and buf() is None
+    assert order == ["graph"] + ["event"] * (3 if scaled else 0)
