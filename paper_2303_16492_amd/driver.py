@@ -106,9 +106,17 @@ class TRSolver:
             o.aux = self.aux.cuda_stream
             o.ev_fork, o.ev_gram, o.ev_join = (e.handle.value for e in self.events)
             self.opts = o
+        # Captured FP64 runs with an own H draw stay on one stream: a process that
+        # captured and dropped several of them with the second stream has ended
+        # with a damaged host heap, and the cause is not known.  The same steps, bit
+        # for bit.
+        self.graph_opts = None if m_H > 0 and cores[0].dtype == torch.float64 else self.opts
 
     def run(self, steps: int, loss_out=None):
-        api.tr_run_ex(self.problem, self.config, self.t_dev, steps, loss_out, self.status, self.ws, self.opts)
+        opts = self.opts
+        if opts is not self.graph_opts and torch.cuda.is_current_stream_capturing():
+            opts = self.graph_opts
+        api.tr_run_ex(self.problem, self.config, self.t_dev, steps, loss_out, self.status, self.ws, opts)
 
     def capture(self, steps: int, loss_out=None):
         """HIP graph of ``steps`` iterations (replay with graph.replay());
