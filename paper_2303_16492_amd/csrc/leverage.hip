@@ -142,18 +142,46 @@ __device__ void leverage_pivoted(const TC* __restrict__ G, int Ik, int RR, doubl
     __syncthreads();
 }
 
-// G^T G of the whole core by one block (the rank-revealing route of a wide
-// core, whose fast test needs only G G^T).
+// G^T G of the whole core (the rank-revealing route of a wide core, whose fast
+// test needs only G G^T): every ``units``-th of its lower 16 x 16 tiles from
+// ``unit``, by one wavefront on the FP64 matrix cores, both triangles written.
+// Ranks 16, 256 x 256 deficient, FP32, whole law: 13.0 ms with one serial sum per
+// entry by one workgroup, 11.1 so; 64 x 256 (one launch) 3.6, 2.8 ms.
 template <typename TC>
-__device__ void gram_one_block(const TC* __restrict__ G, int Ik, int RR, double* __restrict__ Bm) {
-    __syncthreads();
-    for (int e = threadIdx.x; e < RR * RR; e += blockDim.x) {
-        const int r = e / RR, c = e - r * RR;
-        double s = 0.0;
-        for (int i = 0; i < Ik; ++i) s = __builtin_fma((double)G[(int64_t)i * RR + r], (double)G[(int64_t)i * RR + c], s);
-        Bm[e] = s;
+__device__ __forceinline__ void gram_wave_tiles(const TC* __restrict__ G, int Ik, int RR, double* __restrict__ Bm,
+                                                int unit, int units) {
+    const int l = threadIdx.x & 63, lr = l & 15, lk = l >> 4;
+    const int nt = (RR + 15) >> 4, T = nt * (nt + 1) / 2;
+    constexpr int U = 8;
+    for (int tile = unit; tile < T; tile += units) {   // uniform
+        int rt = 0;
+        while ((rt + 1) * (rt + 2) / 2 <= tile) ++rt;
+        const int r = 16 * rt + lr, c = 16 * (tile - rt * (rt + 1) / 2) + lr;
+        const int rc = r < RR ? r : RR - 1, cc = c < RR ? c : RR - 1;
+        dbl4 acc = {0.0, 0.0, 0.0, 0.0};
+        for (int f0 = 0; f0 < Ik; f0 += 4 * U) {
+            TC a[U], b[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int f = f0 + 4 * u + lk, fc = f < Ik ? f : Ik - 1;
+                a[u] = G[(int64_t)fc * RR + rc];
+                b[u] = G[(int64_t)fc * RR + cc];
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const bool in = f0 + 4 * u + lk < Ik;
+                acc = __builtin_amdgcn_mfma_f64_16x16x4f64(in ? (double)a[u] : 0.0, in ? (double)b[u] : 0.0, acc, 0, 0, 0);
+            }
+        }
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int row = 16 * rt + 4 * j + lk;
+            if (row < RR && c <= row) {
+                Bm[(int64_t)row * RR + c] = acc[j];
+                Bm[(int64_t)c * RR + row] = acc[j];
+            }
+        }
     }
-    __syncthreads();
 }
 
 // Leverage law of core k in five launches across the GPU: the
@@ -163,7 +191,8 @@ __device__ void gram_one_block(const TC* __restrict__ G, int Ik, int RR, double*
 // for every row on the FP64 matrix cores, then the weights, CDF and
 // (inside a step) the counter advance in one block.  A wide core (I_k <=
 // R_k R_{k+1}) takes G G^T (I_k x I_k) through the same Gram and sweep, whose
-// rank test is all that is needed: with full row rank every score is 1.
+// rank test is all that is needed: with full row rank every score is 1, and
+// without it the launch of the scores forms G^T G for the rank-revealing route.
 
 constexpr int kLevRows = 16;
 
@@ -174,15 +203,20 @@ constexpr int kLevRows = 16;
 // column blocks' loads are in flight together, above it one block's.
 template <typename TC, int RB>
 __global__ __launch_bounds__(256) void k_lev_rows(tr_desc d, ModeSrc ms, int use_mode, int k_fixed, Ptrs cores,
-                                                  const double* __restrict__ hm, double* __restrict__ lev) {
+                                                  const double* __restrict__ hm, const int* __restrict__ flag,
+                                                  double* __restrict__ gram, double* __restrict__ lev) {
     uint64_t t;
     int k = k_fixed;
     if (use_mode) resolve_mode(ms, d.N, &t, &k);
     const int Ik = d.I[k];
     const int RR = d.R[k] * d.R[ring_next(k, d.N)];
     const int r0 = blockIdx.x * kLevRows;
-    if (r0 >= Ik || Ik <= RR) return;
     const TC* G = static_cast<const TC*>(cores.p[k]);
+    if (Ik <= RR) {   // wide: no scores; G^T G over G G^T, which the sweep has read
+        if (*flag != 0) gram_wave_tiles(G, Ik, RR, gram, (int)blockIdx.x * 4 + (int)(threadIdx.x >> 6), (int)gridDim.x * 4);
+        return;
+    }
+    if (r0 >= Ik) return;
     const int tid = threadIdx.x, l = tid & 63, lr = l & 15, lk = l >> 4, w = tid >> 6;
     constexpr int KS = RB / 4, U = RB <= 128 ? RB / 64 : 1;
     const int row = r0 + lr, rowc = row < Ik ? row : Ik - 1;
@@ -266,7 +300,6 @@ __global__ __launch_bounds__(1024) void k_lev_cdf(tr_desc d, ModeSrc ms, int use
     uint64_t* w = Ik <= lds_rows ? reinterpret_cast<uint64_t*>(smem_raw) : cdf;
     if (*flag != 0) {
         const TC* G = static_cast<const TC*>(cores.p[k]);
-        if (Ik <= RR) gram_one_block(G, Ik, RR, gram);
         leverage_pivoted(G, Ik, RR, gram, w, status);
     } else if (Ik <= RR) {
         write_uniform_weights(w, Ik);
@@ -402,7 +435,8 @@ __global__ __launch_bounds__(kLevSmallThreads) void k_lev_small(tr_desc d, ModeS
     if (ok_at < 0) {
         if (wide) {
             double* Bm = wide_gram + (size_t)(mode_src == kLawEveryMode ? k : 0) * wide_stride;
-            gram_one_block(G, Ik, RR, Bm);
+            gram_wave_tiles(G, Ik, RR, Bm, wv, W);
+            __syncthreads();
             leverage_pivoted(G, Ik, RR, Bm, w, status);
         } else {
             leverage_pivoted(G, Ik, RR, gram, w, status);
@@ -510,13 +544,17 @@ static hipError_t launch_leverage_one(const tr_desc& d, ModeSrc ms, int mode_src
     const double* hm = reinterpret_cast<const double*>(w + L.upd_off + L.u.L_off);
     const int* flag = reinterpret_cast<const int*>(w + L.upd_off + L.u.flag_off);
     double* lev = reinterpret_cast<double*>(w + L.lev_off);
-    const dim3 grid((sh.maxI + kLevRows - 1) / kLevRows);
+    // a block a 16 rows of the scores, or a wavefront a tile of a wide core's G^T G
+    const int ntr = (sh.maxRR + 15) / 16, gt = (ntr * (ntr + 1) / 2 + 3) / 4, gr = (sh.maxI + kLevRows - 1) / kLevRows;
+    bool wide = false;
+    for (int q = 0; q < d.N; ++q) wide = wide || d.I[q] <= d.R[q] * d.R[ring_next(q, d.N)];
+    const dim3 grid(wide && gt > gr ? gt : gr);
     // the CDF kernel's static LDS (rank-revealing route, about 20 KB)
     // plus the staged weights stay within 64 KB
     const int lds_rows = sh.maxI <= kLevLdsRows ? sh.maxI : 0;
     const size_t lds = (size_t)lds_rows * 8;
 #define TRK_LEV_ROWS(TC, RB) \
-    hipLaunchKernelGGL((k_lev_rows<TC, RB>), grid, dim3(256), 0, st, d, ms, use_mode, k, cores, hm, lev)
+    hipLaunchKernelGGL((k_lev_rows<TC, RB>), grid, dim3(256), 0, st, d, ms, use_mode, k, cores, hm, flag, gram, lev)
     if (f64) {
         if (sh.maxRR <= 128) TRK_LEV_ROWS(double, 128);
         else TRK_LEV_ROWS(double, 256);
