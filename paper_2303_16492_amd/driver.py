@@ -49,8 +49,8 @@ class StepGraph(torch.cuda.CUDAGraph):
 
     owner = None
 
-    def __del__(self):
-        if self.owner is not None and not sys.is_finalizing():
+    def __del__(self, finalizing=sys.is_finalizing):   # (module names may be gone at the interpreter's end)
+        if self.owner is not None and not finalizing():
             self.reset()
             torch.cuda.synchronize(self.owner[0].X.device)
 
