@@ -107,64 +107,22 @@ __global__ __launch_bounds__(256) void k_sample_subchain(tr_desc d, ModeSrc ms, 
         __syncthreads();
     } else if (do_sample) {
         if (cdf_J) {
-            // A wavefront searches for four samples at once, 64 probes a
-            // sample and round: every lane draws the word of sample l % 4 of
-            // its wavefront, then the probes of all four go out together.
-            // (One thread per sample halving the range is a dependent round
-            // trip per bit of J_n.)
-            const int wv = tid >> 6, l = tid & 63;
+            // thread fl draws sample fl's column (rounds of eight probes, see
+            // cdf_pick), decoded in 32-bit divisions where J_n allows
             const int64_t J = J_of(d, n);
-            const int fw = wv + 4 * (l & 3);   // wavefront w: samples w, w + 4, w + 8, w + 12
-            const uint64_t W = cdf_J[J - 1];
-            const uint64_t uw = mulhi64(draw_word(ms.seed, t, (uint64_t)(f0 + fw), (uint64_t)n, (uint64_t)stream_tag), W);
-            uint64_t u[4], before[4], at[4];
-            int64_t lo[4], hi[4];
-            bool more = J > 1;
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                u[q] = (uint64_t)__shfl((unsigned long long)uw, q, 64);
-                lo[q] = 0;
-                hi[q] = J - 1;
-                before[q] = 0;
-                at[q] = W;
-            }
-            while (more) {   // uniform: first j with cdf_J[j] > u
-                uint64_t v[4];
-                int64_t step[4];
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    step[q] = (hi[q] - lo[q] + 64) >> 6;
-                    const int64_t pos = lo[q] + (l + 1) * step[q] - 1;
-                    v[q] = cdf_J[pos < hi[q] ? pos : hi[q]];
+            for (int fl = tid; fl < nb; fl += blockDim.x) {
+                const uint64_t r = draw_word(ms.seed, t, (uint64_t)(f0 + fl), (uint64_t)n, (uint64_t)stream_tag);
+                int64_t j = cdf_pick(cdf_J, J, r, &sp[fl * kMaxOrder]);
+                const bool narrow = J <= ((int64_t)1 << 32);   // uniform
+                int k = n1;
+                for (int q = 0; q < N - 1; ++q) {
+                    const int64_t quo = narrow ? (int64_t)((uint32_t)j / (uint32_t)d.I[k]) : j / d.I[k];
+                    sidx[fl * kMaxOrder + k] = (int)(j - quo * d.I[k]);
+                    j = quo;
+                    k = ring_next(k, N);
                 }
-                more = false;
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const int64_t pos = lo[q] + (l + 1) * step[q] - 1;
-                    const int below = (int)__popcll(__ballot(pos < hi[q] && v[q] <= u[q]));   // a prefix of the lanes
-                    const uint64_t vb = (uint64_t)__shfl((unsigned long long)v[q], below > 0 ? below - 1 : 0, 64);
-                    const uint64_t va = (uint64_t)__shfl((unsigned long long)v[q], below < 64 ? below : 63, 64);
-                    before[q] = below > 0 ? vb : before[q];
-                    if (lo[q] + (below + 1) * step[q] - 1 < hi[q]) at[q] = va;
-                    lo[q] += below * step[q];
-                    hi[q] = lo[q] + step[q] - 1 < hi[q] ? lo[q] + step[q] - 1 : hi[q];
-                    more = more || lo[q] < hi[q];
-                }
-            }
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int fl = wv + 4 * q;
-                if (l == q && fl < nb) {
-                    sp[fl * kMaxOrder] = (double)(at[q] - before[q]) / (double)W;
-                    int64_t j = lo[q];
-                    for (int c = 0; c < N - 1; ++c) {
-                        const int k = (n + 1 + c) % N;
-                        sidx[fl * kMaxOrder + k] = (int)(j % d.I[k]);
-                        j /= d.I[k];
-                    }
-                    sidx[fl * kMaxOrder + n] = -1;
-                    sok[fl] = 1;
-                }
+                sidx[fl * kMaxOrder + n] = -1;
+                sok[fl] = 1;
             }
         } else if (early_draws) {
             // thread (sample fl, mode k): its draw at chain position q
