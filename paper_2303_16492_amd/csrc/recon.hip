@@ -236,10 +236,11 @@ __global__ __launch_bounds__(256) void k_recon_pack_h3(tr_desc d, const float* _
 // (chain.hpp; NM slices at most), 32 columns a wavefront, 16 / RB of them to an
 // operand.  sidx: the columns' indices.
 //
-// Against one thread per (column, row of the product), with the outer slice in
-// LDS at order 3 and loaded anew by every thread above it, and 64-bit entry
-// offsets (whole call of the error, us, before and so): 400^3 ranks 10 145, 141;
-// 400 x 300 x 200 ranks 11 83, 74; 64^4 ranks 5 109, 85; 30^4 x 20 ranks 7 395, 182.
+// Against one thread per (column, row of the product), every slice loaded anew by
+// every thread (the written reconstruction, us, threads, chains): 30^4 ranks 5 25,
+// 15; ranks 10 62, 28; 16^5 ranks 8 71, 34; 8^6 ranks 4 24, 15; ranks 11 136, 38; 6^7
+// ranks 3 29, 22; past order 5 only ranks 2 are slower (8^6 12, 14; 5^8 21, 29).  One
+// entry an operand there whatever the ranks: 8^6 ranks 2 32, ranks 4 33; 5^8 ranks 2 81.
 template <int RB, int NM>
 __device__ __forceinline__ void recon_rows(const tr_desc& d, const Ptrs& cores, const int* sidx, float* sS, int SP) {
     constexpr int P = 16 / RB, PK = 32 / P, UM = NM > 4 ? 1 : (NM > 2 ? 2 : 8), U = UM < PK ? UM : PK;
@@ -284,6 +285,62 @@ __device__ __forceinline__ void recon_rows(const tr_desc& d, const Ptrs& cores, 
     }
 }
 
+// The same rows at order 3, one thread per (column, row s of the product): the
+// slices of the last core that the block's columns touch are staged in LDS (sP),
+// and each item loads one row of the column's first slice, the next item's in
+// flight (see recon_rb).
+constexpr int kRmMaxOuter = 8;
+__device__ __forceinline__ void recon_rows_staged(const tr_desc& d, const Ptrs& cores, const int* sidx, float* sS,
+                                                  float* sP, int SP) {
+    const int tid = threadIdx.x, R0 = d.R[0], R1 = d.R[1], R2 = d.R[2], RR2 = R2 * R0;
+    const float* G2 = static_cast<const float*>(cores.p[2]);
+    const int o_lo = sidx[2], n_outer = sidx[(kRmCols - 1) * kMaxOrder + 2] - o_lo + 1;
+    {   // all loads of a thread in flight (clamped, masked after)
+        constexpr int UB = (kRmMaxOuter * kMaxRR + 255) / 256;
+        const int tot = n_outer * RR2;
+        float pv[UB];
+#pragma unroll
+        for (int u = 0; u < UB; ++u) {
+            const int e = u * 256 + tid;
+            pv[u] = G2[(int64_t)o_lo * RR2 + (e < tot ? e : tot - 1)];
+        }
+#pragma unroll
+        for (int u = 0; u < UB; ++u)
+            if (u * 256 + tid < tot) sP[u * 256 + tid] = pv[u];
+    }
+    __syncthreads();
+    const float* G1 = static_cast<const float*>(cores.p[1]);
+    const int RR1 = R1 * R2, last = RR1 - 1, total = kRmCols * R1;
+    auto load_row = [&](int e, float (&v)[kMaxRank]) {   // row s of G_2(i_2), clamped in bounds
+        const int jj = e / R1, s = e - jj * R1;
+        const float* A = G1 + (int64_t)sidx[jj * kMaxOrder + 1] * RR1;
+#pragma unroll
+        for (int c = 0; c < kMaxRank; ++c) v[c] = A[min(s + R1 * c, last)];
+#pragma unroll
+        for (int c = 0; c < kMaxRank; ++c) v[c] = c < R2 ? v[c] : 0.f;   // uniform mask
+    };
+    float v[kMaxRank];
+    if (tid < total) load_row(tid, v);
+    for (int e = tid; e < total; e += 256) {
+        float vn[kMaxRank];
+        if (e + 256 < total) load_row(e + 256, vn);
+        const int jj = e / R1, s = e - jj * R1;
+        float* out = sS + jj * SP + R0 * s;
+        // every LDS read of a row issued together: no read behind a branch
+        // (entries past R_3 multiply the zeros of v)
+        const float* P = sP + (sidx[jj * kMaxOrder + 2] - o_lo) * RR2;
+        for (int r = 0; r < R0; ++r) {
+            const float* Pr = P + R2 * r;
+            float acc = 0.f;
+#pragma unroll
+            for (int c = 0; c < kMaxRank; ++c) acc += v[c] * Pr[c < R2 ? c : R2 - 1];
+            out[r] = acc;
+        }
+#pragma unroll
+        for (int c = 0; c < kMaxRank; ++c) v[c] = vn[c];
+    }
+}
+
 // MODE 0: per-block sums of (X_hat - X_true)^2 and X_true^2 into part, on
 // the split FP16 products with KT = 8 K16, the B operand from
 // k_recon_pack_h3 (Bh, Bl, escale) and the block's subchain rows split into
@@ -294,7 +351,9 @@ __device__ __forceinline__ void recon_rows(const tr_desc& d, const Ptrs& cores, 
 // (row tile, column tile) pairs are taken in row-tile-major order, and each
 // wavefront takes a contiguous quarter of them (exactly ceil(I_1/32) pairs
 // each), so it loads a B fragment only when its row tile changes.
-template <typename TX, int KT, int MODE>
+// HRB: rb at orders above 5 with ranks up to 8, kernels of their own (their seven
+// slices in flight would cost the others a wavefront per SIMD), 0 otherwise.
+template <typename TX, int KT, int MODE, int HRB>
 __global__ __launch_bounds__(256) void k_recon_mfma(tr_desc d, Ptrs cores, const TX* __restrict__ Xt,
                                                     TX* __restrict__ Xo, double* __restrict__ part,
                                                     const _Float16* __restrict__ Bh, const _Float16* __restrict__ Bl,
@@ -328,7 +387,11 @@ __global__ __launch_bounds__(256) void k_recon_mfma(tr_desc d, Ptrs cores, const
         if (MODE == 0) sOff32[tid] = (uint32_t)off * (uint32_t)sizeof(TX);
     }
     __syncthreads();
-    if (N <= 3) {
+    if constexpr (HRB > 0) {
+        recon_rows<HRB, kMaxOrder - 1>(d, cores, sidx, sS, SP);
+    } else if (rb == 0) {   // (every test here is uniform)
+        recon_rows_staged(d, cores, sidx, sS, reinterpret_cast<float*>(sidx + kRmCols * kMaxOrder), SP);
+    } else if (N <= 3) {
         if (rb == 4) recon_rows<4, 2>(d, cores, sidx, sS, SP);
         else if (rb == 8) recon_rows<8, 2>(d, cores, sidx, sS, SP);
         else recon_rows<16, 2>(d, cores, sidx, sS, SP);
@@ -519,14 +582,38 @@ __global__ __launch_bounds__(256) void k_recon_mfma(tr_desc d, Ptrs cores, const
     }
 }
 
-static size_t recon_mfma_shm(int KT) {
-    return (size_t)kRmCols * 8 + (size_t)kRmCols * (2 * KT + 1) * 4 + (size_t)kRmCols * kMaxOrder * 4;
+// Diagonal blocks of the chain operands: every rank within 4, 8 or 16; 0 for the
+// staged thread form of order 3, whose rounds (one row of the product per thread:
+// its load, then R_1 R_3 products) cost less than a pack's product of padded slices
+// where few rounds do.  Measured on the written reconstruction, us, threads against
+// chains: 20 x 900 x 900 ranks 2 51, 62; ranks 5 95, 116; ranks 6 145, 141; ranks 7
+// 167, 139; ranks 11 364, 352; 300 x 200 x 100 ranks 16/4/8 40, 50; 16/2/16 28, 41;
+// 16/8/2 62, 59; 8/16/4 64, 59 (ranks 8 to 10 equal within 5%).  Its columns may touch
+// kRmMaxOuter slices of the last core at most.
+static int recon_rb(const tr_desc& d) {
+    const int r = shape_of(d).maxR, rb = r <= 4 ? 4 : (r <= 8 ? 8 : 16);
+    if (d.N == 3 && (kRmCols - 1) / d.I[1] + 2 <= kRmMaxOuter) {
+        const int rounds = (kRmCols * d.R[1] + 255) / 256, cost = rounds * (150 + d.R[0] * d.R[2]);
+        if (cost < (rb == 4 ? 340 : (rb == 8 ? 540 : 700))) return 0;
+    }
+    return rb;
 }
 
-// Diagonal blocks of the chain operands: every rank within 4, 8 or 16.
-static int recon_rb(const tr_desc& d) {
-    const int r = shape_of(d).maxR;
-    return r <= 4 ? 4 : (r <= 8 ? 8 : 16);
+template <typename TX, int KT, int MODE>
+static auto recon_kernel(const tr_desc& d) {
+    const int rb = d.N > 5 ? recon_rb(d) : 0;
+    if constexpr (KT <= 8) {   // 2 KT holds R_1 R_2: 16 at most with ranks up to 4, 64 with ranks up to 8
+        if (rb == 4) return &k_recon_mfma<TX, KT, MODE, 4>;
+    }
+    if constexpr (KT <= 32) {
+        if (rb == 8) return &k_recon_mfma<TX, KT, MODE, 8>;
+    }
+    return &k_recon_mfma<TX, KT, MODE, 0>;
+}
+
+static size_t recon_mfma_shm(const tr_desc& d, int KT) {
+    return (size_t)kRmCols * 8 + (size_t)kRmCols * (2 * KT + 1) * 4 + (size_t)kRmCols * kMaxOrder * 4 +
+           (recon_rb(d) == 0 ? (size_t)kRmMaxOuter * kMaxRR * 4 : 0);
 }
 
 // Every entry's byte offset fits 32 bits: then the error kernel addresses X_true
@@ -558,14 +645,15 @@ template <typename TX>
 static hipError_t launch_recon_write(const tr_desc& d, Ptrs cores, TX* Xo, hipStream_t st) {
     const int KT = recon_kt(d.R[0] * d.R[1 % d.N]);
     const dim3 grid((unsigned)recon_mfma_blocks(d)), block(256);
-    const size_t shm = recon_mfma_shm(KT);
+    const size_t shm = recon_mfma_shm(d, KT);
 #define TRK_RM(KTV)                                                                                      \
-    case KTV:                                                                                            \
-        if (!allow_lds(reinterpret_cast<const void*>(&k_recon_mfma<TX, KTV, 1>), shm))                  \
-            return hipErrorInvalidConfiguration;                                                         \
-        hipLaunchKernelGGL((k_recon_mfma<TX, KTV, 1>), grid, block, shm, st, d, cores, (const TX*)nullptr, Xo, \
-                           nullptr, nullptr, nullptr, nullptr, recon_rb(d), 0);                          \
-        break;
+    case KTV: {                                                                                          \
+        auto kern = recon_kernel<TX, KTV, 1>(d);                                                         \
+        if (!allow_lds(reinterpret_cast<const void*>(kern), shm)) return hipErrorInvalidConfiguration;   \
+        hipLaunchKernelGGL(kern, grid, block, shm, st, d, cores, (const TX*)nullptr, Xo, nullptr, nullptr, nullptr, \
+                           nullptr, recon_rb(d), 0);                                                     \
+        break;                                                                                           \
+    }
     switch (KT) {
         TRK_RM(8)
         TRK_RM(16)
@@ -584,14 +672,15 @@ static hipError_t launch_recon_h3(const tr_desc& d, Ptrs cores, const _Float16* 
                                   const int* escale, const TX* Xt, double* part, hipStream_t st) {
     const int K16 = recon_k16(d);
     const dim3 grid((unsigned)recon_mfma_blocks(d)), block(256);
-    const size_t shm = recon_mfma_shm(8 * K16);
+    const size_t shm = recon_mfma_shm(d, 8 * K16);
 #define TRK_RH(K)                                                                                         \
-    case K:                                                                                               \
-        if (!allow_lds(reinterpret_cast<const void*>(&k_recon_mfma<TX, 8 * K, 0>), shm))                 \
-            return hipErrorInvalidConfiguration;                                                          \
-        hipLaunchKernelGGL((k_recon_mfma<TX, 8 * K, 0>), grid, block, shm, st, d, cores, Xt, (TX*)nullptr, \
-                           part, Bh, Bl, escale, recon_rb(d), (int)recon_off32(d, sizeof(TX)));           \
-        break;
+    case K: {                                                                                             \
+        auto kern = recon_kernel<TX, 8 * K, 0>(d);                                                        \
+        if (!allow_lds(reinterpret_cast<const void*>(kern), shm)) return hipErrorInvalidConfiguration;    \
+        hipLaunchKernelGGL(kern, grid, block, shm, st, d, cores, Xt, (TX*)nullptr, part, Bh, Bl, escale,  \
+                           recon_rb(d), (int)recon_off32(d, sizeof(TX)));                                 \
+        break;                                                                                            \
+    }
     switch (K16) {
         TRK_RH(1)
         TRK_RH(2)
