@@ -55,7 +55,10 @@ typedef ChainVec<float>::V ef4;
 constexpr int ent_packs(int NM) { return NM <= 3 ? 4 : (NM <= 5 ? 2 : 1); }
 
 // ``iters`` rounds of ent_packs packs per wavefront; NM bounds the order, OT
-// holds a byte offset into any core.
+// holds a byte offset into any core.  Four wavefronts a SIMD up to order 5: without
+// whole 16-byte pieces orders 4 and 5 then keep 3 or 4 of their registers in scratch,
+// which costs less than the wavefront (60^4, ranks 10, B 16384: 18.7 us; three
+// wavefronts and no scratch 21.1).
 template <typename TX, int RB, bool VEC, int NM, typename OT>
 __global__ __launch_bounds__(kEntBlock, NM <= 5 ? 4 : 2) void k_entry_fwd(tr_desc d, Ptrs cores,
                                                                          const int32_t* __restrict__ idx,
@@ -139,7 +142,9 @@ struct EntGroups {
     int64_t base[kMaxOrder + 1], at[kMaxOrder];
     int parts[kMaxOrder];
 };
-constexpr int kBwdWaves = 16;     // at most
+// Wavefronts of a workgroup at most; half of them past order 5, whose seven slices
+// in flight take the registers of two.
+constexpr int bwd_waves(int NM) { return NM <= 5 ? 16 : 8; }
 constexpr int64_t kBwdGrid = 1 << 22;
 // Entries of a wavefront's share scanned into its list at a time: at most
 // 4096, at least 512 (a 16 x 16 partial tile fits the list's 2-byte places).
@@ -152,7 +157,7 @@ constexpr int kBwdWindow = 4096, kBwdWindowMin = 512;
 // of the list before it is added to an FP64 total, so the rounding of a slice does
 // not grow with the entries that fall on it.
 template <int RB, bool VEC, int NM, typename OT>
-__global__ __launch_bounds__(64 * kBwdWaves) void k_entry_bwd(tr_desc d, Ptrs cores, const int32_t* __restrict__ idx,
+__global__ __launch_bounds__(64 * bwd_waves(NM)) void k_entry_bwd(tr_desc d, Ptrs cores, const int32_t* __restrict__ idx,
                                                               const float* __restrict__ resid, int B, float scale,
                                                               const double* __restrict__ dscale, EntGroups gr,
                                                               int window, ModeSrc only, int block, MutPtrs grads) {
@@ -392,9 +397,9 @@ static EntryPlan entry_plan(const tr_desc& d, int B) {
     // at most four wavefronts per SIMD over all slices, at least 64 entries of
     // scan each
     P.waves = 1;
-    while (P.waves < kBwdWaves && 2 * P.gr.base[d.N] * P.waves <= 4096 && (int64_t)64 * P.waves < B) P.waves *= 2;
+    while (P.waves < bwd_waves(P.nm) && 2 * P.gr.base[d.N] * P.waves <= 4096 && (int64_t)64 * P.waves < B) P.waves *= 2;
     const int64_t slices = P.gr.base[d.N];
-    while (P.waves < kBwdWaves && (int64_t)kBwdShare * P.waves < B && 2 * slices * P.waves <= kBwdSplit) P.waves *= 2;
+    while (P.waves < bwd_waves(P.nm) && (int64_t)kBwdShare * P.waves < B && 2 * slices * P.waves <= kBwdSplit) P.waves *= 2;
     for (int k = 0; k < d.N; ++k) {
         const int64_t len = (int64_t)d.I[k] * d.R[k] * d.R[ring_next(k, d.N)];
         const int64_t hits = (int64_t)d.I[k] * kBwdHits < kBwdFar ? (int64_t)d.I[k] * kBwdHits : kBwdFar;
