@@ -353,17 +353,20 @@ __global__ __launch_bounds__(256) void k_entry_bwd_sum(tr_desc d, const float* _
 // cost is what counts (kBwdSplit of them in all): a wavefront walks its hits in a
 // chain of dependent loads, some 0.4 us an entry, so the share bounds it however
 // the entries fall on the slices.  Modes of so few indices that a wavefront expects
-// more than kBwdHits entries, and batches past kBwdFar entries a wavefront, are
-// split over several workgroups per slice, at most kBwdParts and kBwdPartBytes of
-// partial gradients.
+// more than kBwdRounds rounds of hits, and batches past kBwdFar entries a wavefront,
+// are split over several workgroups per slice, at most kBwdParts and kBwdPartBytes
+// of partial gradients.
 //
 // Backward of uniform batches in us, one workgroup a slice with its wavefronts by
 // the number of slices alone, against this split: sizes 2049, 5, 6, ranks 4/8/4, B
-// 65536: 1942, 110; 14456, 826, 580, 9, 2, ranks 3/2/2/7/8, B 7975: 1444, 142; 2 and
-// 145, ranks 16/6, B 15486: 99, 34; 1 and 1, ranks 16/12, B 65536: 686, 34.  Half of
-// the batch on one index of every mode, 301 x 250 x 127, ranks 10/9/7, B 16384: 1136,
-// 633 (uniform: 31).  kBwdSplit 4 times as large: 150 and 162 for the first two.
-constexpr int kBwdShare = 2048, kBwdHits = 128, kBwdFar = 8192, kBwdParts = 512;
+// 65536: 1946, 110; 14456, 826, 580, 9, 2, ranks 3/2/2/7/8, B 7975: 1445, 118; 2 and
+// 145, ranks 16/6, B 15486: 100, 24; 1 and 1, ranks 16/12, B 65536: 685, 25; 10^6,
+// ranks 7, B 8192: 96, 38; 16^4, ranks 11, B 32768: 227, 77.  Half of the batch on one
+// index of every mode, 301 x 250 x 127, ranks 10/9/7, B 16384: 1136, 633 (uniform: 31).
+// kBwdRounds 32: 132, 141, 34, 34, 60, 131; 8: 107, 109, 19, 27, 56, 82, but 60^4,
+// ranks 10, B 16384: 50 instead of 41.  kBwdSplit 4 times as large: 150 and 162 for the
+// first two.
+constexpr int kBwdShare = 2048, kBwdRounds = 16, kBwdFar = 8192, kBwdParts = 512;
 constexpr int64_t kBwdSplit = 1 << 15;
 constexpr int64_t kBwdPartBytes = (int64_t)8 << 20;   // a mode
 
@@ -402,7 +405,8 @@ static EntryPlan entry_plan(const tr_desc& d, int B) {
     while (P.waves < bwd_waves(P.nm) && (int64_t)kBwdShare * P.waves < B && 2 * slices * P.waves <= kBwdSplit) P.waves *= 2;
     for (int k = 0; k < d.N; ++k) {
         const int64_t len = (int64_t)d.I[k] * d.R[k] * d.R[ring_next(k, d.N)];
-        const int64_t hits = (int64_t)d.I[k] * kBwdHits < kBwdFar ? (int64_t)d.I[k] * kBwdHits : kBwdFar;
+        const int64_t round = (16 / P.rb) * ent_packs(P.nm);   // entries of one
+        const int64_t hits = std::min<int64_t>(d.I[k] * round * kBwdRounds, kBwdFar);
         const int64_t parts = std::min(std::min<int64_t>((B + hits * P.waves - 1) / (hits * P.waves), kBwdParts),
                                        kBwdPartBytes / (len * 4));
         P.gr.parts[k] = (int)std::max<int64_t>(1, parts);
