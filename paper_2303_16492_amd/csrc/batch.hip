@@ -76,7 +76,7 @@ __global__ __launch_bounds__(64 * WAVES) void k_batch_steps(const tr_batch_item*
     float* sw = reinterpret_cast<float*>(smem_raw + Lz::w_off);
     int64_t* soff = reinterpret_cast<int64_t*>(smem_raw + Lz::o_off);
     __shared__ double red[WAVES];
-    const ChainLane<float, 16> L;
+    const ChainLane<16> L;
 
     uint64_t t = *it.t_dev;
     const int m = it.m;
@@ -167,10 +167,10 @@ __global__ __launch_bounds__(64 * WAVES) void k_batch_steps(const tr_batch_item*
             constexpr int U = WAVES > 4 ? 2 : 4;   // what the registers of the wavefronts hold
             int k0 = n1;
             asm volatile("" : "+v"(k0));
-            const ChainSlots<float, kBatchMaxN - 1, false> sl(d, k0, N - 1, L);
+            const ChainSlots<kBatchMaxN - 1, false> sl(d, k0, N - 1, L);
 #pragma unroll 1
             for (int g = wv; g < CH; g += U * WAVES) {
-                ChainVec<float>::V v[U][kBatchMaxN - 1];
+                chain4 v[U][kBatchMaxN - 1];
 #pragma unroll
                 for (int u = 0; u < U; ++u) {
                     const int f = g + u * WAVES, fc = f < nb ? f : nb - 1;
@@ -186,13 +186,13 @@ __global__ __launch_bounds__(64 * WAVES) void k_batch_steps(const tr_batch_item*
 #pragma unroll
                 for (int u = 0; u < U; ++u) {
                     const int f = g + u * WAVES;
-                    ChainVec<float>::V T = sl.mask(v[u][0], 0);
+                    chain4 T = sl.mask(v[u][0], 0);
                     int k = n1;
 #pragma unroll
                     for (int q = 1; q < kBatchMaxN - 1; ++q) {
                         if (q >= N - 1) break;
                         k = ring_next(k, N);
-                        T = chain_mul(sl.mask(v[u][q], q), T, ChainVec<float>::V{0.f, 0.f, 0.f, 0.f});
+                        T = chain_mul(sl.mask(v[u][q], q), T, chain4{0.f, 0.f, 0.f, 0.f});
                         if (q + 1 < N - 1) T = chain_mask(T, L, L.col < Rn1, d.R[ring_next(k, N)]);
                     }
                     if (L.col < Rn1) {   // s = the lane's column, r = its rows

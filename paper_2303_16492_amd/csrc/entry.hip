@@ -47,7 +47,7 @@ __global__ __launch_bounds__(256) void k_entry_loss(const double* __restrict__ p
     if (threadIdx.x == 0) *loss = s / (2.0 * (double)B);
 }
 
-typedef ChainVec<float>::V ef4;
+typedef chain4 ef4;
 
 // Packs whose slices a wavefront has in flight together: a pack's chain is a
 // few hundred cycles of products behind a memory round trip of several times
@@ -66,9 +66,9 @@ __global__ __launch_bounds__(kEntBlock, NM <= 5 ? 4 : 2) void k_entry_fwd(tr_des
                                                                          float* __restrict__ resid,
                                                                          double* __restrict__ part) {
     constexpr int P = 16 / RB, U = ent_packs(NM);
-    const ChainLane<float, RB> L;
+    const ChainLane<RB> L;
     const int N = d.N, wv = threadIdx.x >> 6;
-    const ChainSlots<float, NM, VEC> sl(d, 0, N, L);
+    const ChainSlots<NM, VEC> sl(d, 0, N, L);
     const bool in0 = L.col < d.R[0];
     double sq = 0.0;
 #pragma unroll 1
@@ -163,7 +163,7 @@ __global__ __launch_bounds__(64 * bwd_waves(NM)) void k_entry_bwd(tr_desc d, Ptr
                                                               int window, ModeSrc only, int block, MutPtrs grads) {
     constexpr int P = 16 / RB, U = ent_packs(NM), KI = 16;
     extern __shared__ __align__(16) unsigned char smem_raw[];   // [wavefronts][window] 2-byte places
-    const ChainLane<float, RB> L;
+    const ChainLane<RB> L;
     const int N = d.N, tid = threadIdx.x, l = tid & 63, W = blockDim.x >> 6;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     int step_mode = -1;   // block mode: only the step's core moves
@@ -180,7 +180,7 @@ __global__ __launch_bounds__(64 * bwd_waves(NM)) void k_entry_bwd(tr_desc d, Ptr
         uint16_t* list = reinterpret_cast<uint16_t*>(smem_raw) + w * window;
         // dL/dG_k of L = 1/(2B) sum r^2: the 1/B of the mean applied here
         const float sc = (float)((double)scale * (dscale ? *dscale : 1.0) / (double)B);
-        const ChainSlots<float, NM - 1, VEC> sl(d, k0, N - 1, L);
+        const ChainSlots<NM - 1, VEC> sl(d, k0, N - 1, L);
         const bool in0 = L.col < d.R[k0];
         double tot[4] = {0.0, 0.0, 0.0, 0.0};
         const int64_t share = (((int64_t)B + W * parts - 1) / (W * parts) + 63) & ~63;

@@ -245,13 +245,13 @@ template <int RB, int NM>
 __device__ __forceinline__ void recon_rows(const tr_desc& d, const Ptrs& cores, const int* sidx, float* sS, int SP) {
     constexpr int P = 16 / RB, PK = 32 / P, UM = NM > 4 ? 1 : (NM > 2 ? 2 : 8), U = UM < PK ? UM : PK;
     const int N = d.N, k0 = ring_next(0, N), R0 = d.R[0], R1 = d.R[k0];
-    const ChainLane<float, RB> L;
-    const ChainSlots<float, NM, false> sl(d, k0, N - 1, L);
+    const ChainLane<RB> L;
+    const ChainSlots<NM, false> sl(d, k0, N - 1, L);
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const bool in0 = L.col < R1;
 #pragma unroll 1
     for (int g = 0; g < PK; g += U) {
-        ChainVec<float>::V v[U][NM];
+        chain4 v[U][NM];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const int* ix = sidx + (32 * w + (g + u) * P + L.p) * kMaxOrder;
@@ -266,13 +266,13 @@ __device__ __forceinline__ void recon_rows(const tr_desc& d, const Ptrs& cores, 
         }
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            ChainVec<float>::V T = sl.mask(v[u][0], 0);
+            chain4 T = sl.mask(v[u][0], 0);
             int k = k0;
 #pragma unroll
             for (int q = 1; q < NM; ++q) {
                 if (q >= N - 1) break;
                 k = ring_next(k, N);
-                T = chain_mul(sl.mask(v[u][q], q), T, ChainVec<float>::V{0.f, 0.f, 0.f, 0.f});
+                T = chain_mul(sl.mask(v[u][q], q), T, chain4{0.f, 0.f, 0.f, 0.f});
                 if (q + 1 < N - 1) T = chain_mask(T, L, in0, d.R[ring_next(k, N)]);
             }
             if (in0) {   // M(s, r): s = the lane's column, r = its rows

@@ -36,9 +36,8 @@ constexpr int kSampleBlock = 16;   // samples of a block
 
 // Packs whose slices a wavefront has in flight together (at most 64 registers
 // of slices), NM - 1 slices a sample.
-template <typename TC>
 constexpr int sample_packs(int NM) {
-    const int u = 64 / ((NM - 1) * 4 * (int)(sizeof(TC) / 4));
+    const int u = 64 / ((NM - 1) * 4);
     return u >= 4 ? 4 : (u >= 2 ? 2 : 1);
 }
 
@@ -197,16 +196,15 @@ __global__ __launch_bounds__(256) void k_sample_subchain(tr_desc d, ModeSrc ms, 
 
     if constexpr (sizeof(TC) == 4) {
         // FP32.  Wavefront w takes packs w, w + 4, ... of P samples.
-        using V = typename ChainVec<TC>::V;
-        constexpr int P = 16 / RB, NPK = kSampleBlock / P, PW = (NPK + 3) / 4, UP = sample_packs<TC>(NM), U = UP < PW ? UP : PW;
-        const ChainLane<TC, RB> L;
-        const ChainSlots<TC, NM - 1, VEC> sl(d, n1, N - 1, L);
+        constexpr int P = 16 / RB, NPK = kSampleBlock / P, PW = (NPK + 3) / 4, UP = sample_packs(NM), U = UP < PW ? UP : PW;
+        const ChainLane<RB> L;
+        const ChainSlots<NM - 1, VEC> sl(d, n1, N - 1, L);
         const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
         const bool in0 = L.col < Rn1;
         bool wrote = !do_sample;
 #pragma unroll 1
         for (int g = 0; g < PW; g += U) {
-            V v[U][NM - 1];
+            chain4 v[U][NM - 1];
             int fl[U], ok[U];
 #pragma unroll
             for (int u = 0; u < U; ++u) {
@@ -230,13 +228,13 @@ __global__ __launch_bounds__(256) void k_sample_subchain(tr_desc d, ModeSrc ms, 
             wrote = true;
 #pragma unroll
             for (int u = 0; u < U; ++u) {
-                V T = sl.mask(v[u][0], 0);
+                chain4 T = sl.mask(v[u][0], 0);
                 int k = n1;
 #pragma unroll
                 for (int q = 1; q < NM - 1; ++q) {
                     if (q >= N - 1) break;
                     k = ring_next(k, N);
-                    T = chain_mul(sl.mask(v[u][q], q), T, V{TC(0), TC(0), TC(0), TC(0)});
+                    T = chain_mul(sl.mask(v[u][q], q), T, chain4{0.f, 0.f, 0.f, 0.f});
                     if (q + 1 < N - 1) T = chain_mask(T, L, in0, d.R[ring_next(k, N)]);
                 }
                 if (fl[u] < nb && in0) {   // S(f, r + R_n s) = M_f(s, r), s = the lane's column, r = its rows
