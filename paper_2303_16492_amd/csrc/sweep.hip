@@ -81,7 +81,8 @@ __global__ __launch_bounds__(256) void k_sweep(tr_desc d, ModeSrc ms, const doub
 // matrix-core products over three SIMDs (2.8 K cycles at NT = 11) or the
 // factor wavefront's link (2.4 K cycles), whichever is longer.  136 tiles of
 // 2 KB exceed the LDS but fit the vector registers of six wavefronts (at most
-// 23 tiles of 8 registers each).  Every update wavefront runs the same code
+// 23 tiles of 8 registers each, which at 16 tile columns leaves 15 of the
+// other registers in scratch).  Every update wavefront runs the same code
 // on tile coordinates held in scalar registers (the per-wavefront code of the
 // narrow sweep would be some 150 KB here, past the instruction cache), and
 // passes Z = B V~ of its columns to its tiles through its own LDS slots.
