@@ -3,10 +3,12 @@
 //   Euclidean (Lemma euc_est): p(i) = ||G_k(:,i,:)||_F^2 / ||G_k||_F^2.
 //   Leverage (Lemma lev_est):  p(i) = l_i(G_{k(2)}) / rank, l_i = g_i^T (G^T G)^{-1} g_i
 //                              with the FP64 Gram G^T G of G = G_{k(2)} and its
-//                              sweep inverse; a Gram that is singular or close to
-//                              it, and I_k <= R_k R_{k+1}, take the rank-revealing
-//                              route (pivoted Cholesky, scores on the chosen
-//                              columns, divided by the rank found).
+//                              sweep inverse; with I_k <= R_k R_{k+1} the smaller
+//                              G G^T instead, whose full rank makes every l_i 1.  A
+//                              Gram that is singular or close to it takes the
+//                              rank-revealing route (pivoted Cholesky of G^T G,
+//                              scores on the chosen columns, divided by the rank
+//                              found).
 //   Optimal (eq:optimal_prob): q(j) ~ ||X_[n](:,j) - G_{n(2)} s_j|| * ||s_j||
 //                              over the J_n columns, FP64.
 // Weights w = floor(p 2^40) + 1 and their inclusive prefix sums are exact
