@@ -417,9 +417,23 @@ static EntryPlan entry_plan(const tr_desc& d, int B) {
     const int64_t share = (((int64_t)B + P.waves - 1) / P.waves + 63) & ~(int64_t)63;
     P.window = (int)std::max<int64_t>(kBwdWindowMin, std::min<int64_t>(kBwdWindow, share));
     P.part_off = 0;
-    P.gpart_off = align_up((size_t)P.fwd_blocks * 8);
+    P.gpart_off = align_up((size_t)std::max<int64_t>(P.fwd_blocks, std::min<int64_t>(fb, 1024)) * 8);
     P.total = P.gpart_off + align_up((size_t)P.part_len * 4);
     return P;
+}
+
+// Largest ``bytes`` of a batch of at most B entries, so that the workspace of the
+// largest batch serves smaller ones: the forward's blocks fall where its wavefronts
+// take one round more, a mode's parts where a workgroup gets more wavefronts (at 64
+// or kBwdShare entries for each); between those sizes neither falls.
+template <typename F>
+static size_t entry_size_upto(int B, F&& bytes) {
+    size_t most = bytes(B);
+    for (int w = 1; w <= 8; w *= 2) {
+        if (64 * w < B) most = std::max(most, bytes(64 * w));
+        if (kBwdShare * w < B) most = std::max(most, bytes(kBwdShare * w));
+    }
+    return most;
 }
 
 // 16-byte slice loads: every rank a multiple of 4 (so every slice is whole
@@ -589,7 +603,7 @@ extern "C" {
 
 size_t tr_entry_workspace_size(const tr_desc* d, int32_t B) {
     if (validate_desc(d) != TR_OK || B < 1) return 0;
-    return entry_plan(*d, B).total;
+    return entry_size_upto(B, [&](int b) { return entry_plan(*d, b).total; });
 }
 
 static tr_status entry_checks(const tr_desc* d, const void* const* cores, const int32_t* idx, int32_t B) {
@@ -676,7 +690,7 @@ static tr_status completion_checks(const tr_desc* d, const tr_completion_config*
 
 size_t tr_completion_workspace_size(const tr_desc* d, const tr_completion_config* c) {
     if (completion_checks(d, c) != TR_OK) return 0;
-    return completion_layout(*d, c->B).total;
+    return entry_size_upto(c->B, [&](int b) { return completion_layout(*d, b).total; });
 }
 
 tr_status tr_completion_run(const tr_desc* d, void* const* cores, void* const* accum, const int32_t* obs_idx,

@@ -42,3 +42,25 @@ def test_runs_that_fitted_the_library_scratch_still_do(I, R, prec, m, m_H, law):
 def test_larger_runs_keep_a_size_above_the_scratch():
     from paper_2303_16492_amd import _lib as L
     assert _run_size([400, 400, 400], [16, 16, 16], "f32", 60000) > L.TR_NOALLOC_SCRATCH_BYTES
+
+
+def test_an_entry_workspace_serves_smaller_batches():
+    """The workspace of a batch of B entries is enough for every smaller batch: no
+    size falls as B grows, across the batch sizes where the split over workgroups
+    changes."""
+    from paper_2303_16492_amd import _lib as L, api
+    sizes = sorted({max(1, e) for b in (64, 2048, 8192) for w in (1, 2, 4, 8, 16) for e in (b * w - 1, b * w, b * w + 1)}
+                   | {1 << k for k in range(19)} | {3 << k for k in range(17)})
+    for I, R in [([1, 1], [16, 12]), ([2, 145], [16, 6]), ([2049, 5, 6], [4, 8, 4]), ([40, 30, 5], [7, 9, 3]),
+                 ([14456, 826, 580, 9, 2], [3, 2, 2, 7, 8]), ([16, 16, 16, 16], [11] * 4), ([6] * 8, [5] * 8),
+                 ([32] * 5, [8] * 5)]:
+        d = api.make_desc(I, R, torch.float32)
+        c = L.tr_completion_config()
+        last = last_c = 0
+        for B in sizes:
+            size = L.lib().tr_entry_workspace_size(C.byref(d), B)
+            c.B = B
+            size_c = L.lib().tr_completion_workspace_size(C.byref(d), C.byref(c))
+            assert size >= last and size_c >= last_c, (I, R, B)
+            assert size > 0 and size_c > 0
+            last, last_c = size, size_c
