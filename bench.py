@@ -1170,8 +1170,8 @@ def main():
                   other: {"steps_per_s": round(1e3 / alt["ms_per_step"], 2), "rse_after": alt["rse_after"],
                           "gradient_us": round(alt["grad_us"], 3),
                           "inverse_us": None if alt["inv_us"] is None else round(alt["inv_us"], 3)}},
-        "timing": "value: K steps replayed from a captured HIP graph of 50 steps (the Gram/inverse branch forks "
-                  "and joins as graph edges); kernel durations: HIP start/stop events recorded by every dispatch of "
+        "timing": "value: K steps replayed from a captured HIP graph of 50 steps on one stream (eager steps "
+                  "take the Gram/inverse branch on a second one); kernel durations: HIP start/stop events recorded by every dispatch of "
                   "the inverse and gradient kernels themselves (hipExtLaunchKernelGGL) over 200 eager steps of the "
                   "same run",
         "eager_steps_per_s": round(1e3 / main["eager_ms_per_step"], 2),

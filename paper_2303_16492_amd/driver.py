@@ -52,7 +52,8 @@ class StepGraph(torch.cuda.CUDAGraph):
     def __del__(self, finalizing=sys.is_finalizing):   # (module names may be gone at the interpreter's end)
         if self.owner is not None and not finalizing():
             self.reset()
-            torch.cuda.synchronize(self.owner[0].X.device)
+            if not torch.cuda.is_current_stream_capturing():   # (dropped by a collection inside another capture)
+                torch.cuda.synchronize(self.owner[0].X.device)
 
 
 class TRSolver:
@@ -97,7 +98,7 @@ class TRSolver:
         self.config = c
         self.ws = api.workspace(api.tr_run_workspace_size(p, c), dev)
         self.rse_ws = None
-        # scaled steps: the Gram/inverse branch on a second stream
+        # scaled steps: the Gram/inverse branch on a second stream (launched, not captured)
         self.opts = None
         if overlap and scaled:
             self.aux = torch.cuda.Stream(device=dev)
@@ -106,16 +107,14 @@ class TRSolver:
             o.aux = self.aux.cuda_stream
             o.ev_fork, o.ev_gram, o.ev_join = (e.handle.value for e in self.events)
             self.opts = o
-        # Captured FP64 runs with an own H draw stay on one stream: a process that
-        # captured and dropped several of them with the second stream has ended
-        # with a damaged host heap, and the cause is not known.  The same steps, bit
-        # for bit.
-        self.graph_opts = None if m_H > 0 and cores[0].dtype == torch.float64 else self.opts
 
     def run(self, steps: int, loss_out=None):
+        # A run that is being captured stays on one stream: processes that captured
+        # and dropped several with the second stream have ended with a damaged host
+        # heap, and the cause is not known.  The same steps, bit for bit.
         opts = self.opts
-        if opts is not self.graph_opts and torch.cuda.is_current_stream_capturing():
-            opts = self.graph_opts
+        if opts is not None and torch.cuda.is_current_stream_capturing():
+            opts = None
         api.tr_run_ex(self.problem, self.config, self.t_dev, steps, loss_out, self.status, self.ws, opts)
 
     def capture(self, steps: int, loss_out=None):

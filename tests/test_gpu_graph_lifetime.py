@@ -58,13 +58,14 @@ def test_graph_keeps_what_it_replays_into(scaled, monkeypatch):
     assert order == ["graph"] + ["event"] * (3 if scaled else 0)
 
 
-def test_captured_fp64_run_with_its_own_hessian_draw_stays_on_one_stream(monkeypatch):
-    ref = _solver("f64", m_H=150)
-    assert ref.opts is not None and ref.graph_opts is None
+@pytest.mark.parametrize("prec,m_H", [("f32", 0), ("f32", 150), ("f64", 0), ("f64", 150), ("bf16", 0), ("f16", 0)])
+def test_captured_run_stays_on_one_stream(prec, m_H, monkeypatch):
+    ref = _solver(prec, m_H=m_H)
+    assert ref.opts is not None
     ref.run(7)   # eager: two streams
     torch.cuda.synchronize()
-    sol = _solver("f64", m_H=150)
-    say("captured FP64 run with an own H draw")
+    sol = _solver(prec, m_H=m_H)
+    say("captured run", prec, m_H)
     used = []
     run_ex = api.tr_run_ex
     monkeypatch.setattr(api, "tr_run_ex", lambda *a: (used.append((torch.cuda.is_current_stream_capturing(), a[-1])),
@@ -75,6 +76,3 @@ def test_captured_fp64_run_with_its_own_hessian_draw_stays_on_one_stream(monkeyp
     g.replay()
     torch.cuda.synchronize()
     assert sol.t == 7 and all(torch.equal(a, b) for a, b in zip(sol.cores, ref.cores))
-    for prec, m_H in (("f64", 0), ("f32", 150), ("f32", 0)):
-        other = _solver(prec, m_H=m_H)
-        assert other.graph_opts is other.opts is not None
