@@ -48,13 +48,14 @@ def _torch_lib_dir() -> str | None:
         return None
 
 
-# Per-source code-generation options.  sweep.hip, leverage.hip: the FP64 matrix-core
+# Per-source code-generation options.  sweep.hip, leverage.hip, grad_sweep.hip: the FP64 matrix-core
 # accumulators of the one-workgroup inverse are selected in ordinary vector
 # registers (the VGPR form of the MFMA instructions), which removes the
 # copies between accumulation and vector registers from every block step.
 PER_SOURCE = {
     "sweep.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"],
     "leverage.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"],
+    "grad_sweep.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"],
 }
 
 

@@ -561,14 +561,23 @@ tr_status tr_run_ex(const tr_problem* p, const tr_config* c, uint64_t* t_dev, in
                                     fork ? (hipEvent_t)o.ev_gram : nullptr);
                 }
             }
-            if (e == hipSuccess) {
+            // On one stream the gradient and the inverse are one launch where
+            // they can be.
+            bool both = false;
+            if (e == hipSuccess && !fork && !o.ev_inv_begin && !o.ev_inv_end && !ev_begin && !ev_end) {
+                e = launch_sweep_grad(d, ms_shape, gram, damp, L.ul, w + L.upd, dev_status, ms, cores, xs, idx, S, pF,
+                                      c->m, c->prec, w + L.grad, L.gl, st);
+                both = e == hipSuccess;
+                if (e == hipErrorNotSupported) e = hipSuccess;
+            }
+            if (e == hipSuccess && !both) {
                 TimedDispatch td(o.ev_inv_begin ? (hipEvent_t)o.ev_inv_begin[it] : nullptr,
                                  o.ev_inv_end ? (hipEvent_t)o.ev_inv_end[it] : nullptr);
                 e = launch_sweep_inverse(d, ms_shape, gram, damp, L.ul, w + L.upd, dev_status, hs);
             }
             if (e == hipSuccess && fork) e = hipEventRecord((hipEvent_t)o.ev_join, hs);
             if (e == hipSuccess && fork) e = hipStreamWaitEvent(st, (hipEvent_t)o.ev_gram, 0);
-            if (e == hipSuccess) {
+            if (e == hipSuccess && !both) {
                 TimedDispatch td(ev_begin ? (hipEvent_t)ev_begin[it] : nullptr,
                                  ev_end ? (hipEvent_t)ev_end[it] : nullptr);
                 e = launch_grad_partial(d, ms, cores, xs, idx, S, pF, c->m, c->prec, w + L.grad, L.gl, st);

@@ -71,8 +71,7 @@ hipError_t launch_sample_subchain_mode(const tr_desc& d, ModeSrc ms, int m, CdfP
 inline unsigned xcd_grid(int T, int G) {
     return G >= 8 ? 8u * (unsigned)T * (unsigned)((G + 7) / 8) : (unsigned)(T * G);
 }
-__device__ inline bool xcd_tile_group(int T, int G, int& tile, int& grp) {
-    const int b = (int)blockIdx.x;
+__device__ inline bool xcd_tile_group(int T, int G, int& tile, int& grp, int b = (int)blockIdx.x) {
     if (G < 8) {
         grp = b / T;
         tile = b - grp * T;
@@ -194,6 +193,10 @@ hipError_t launch_sweep_update(const tr_desc& d, ModeSrc ms, const double* gram,
 // row-parallel p = g (-M^{-1}) with the rule.
 hipError_t launch_sweep_inverse(const tr_desc& d, ModeSrc ms, const double* gram, Damp damping, const UpdWs& L,
                                 void* ws, int32_t* status, hipStream_t st, double rank_tol = 0.0);
+hipError_t launch_sweep_grad(const tr_desc& d, ModeSrc ms_shape, const double* gram, Damp damping, const UpdWs& U,
+                             void* upd_ws, int32_t* status, ModeSrc ms, Ptrs cores, XSrc xs, const int32_t* idx,
+                             const void* S, const double* pF, int m, int prec, void* grad_ws, const GradWs& L,
+                             hipStream_t st);
 hipError_t launch_sweep_apply(const tr_desc& d, ModeSrc ms, const void* g, LossParts lp, double* loss, MutPtrs cores,
                               MutPtrs accum, tr_step rule, int32_t* status, void* ws, const UpdWs& L, StepBump step,
                               hipStream_t st);

@@ -489,4 +489,40 @@ __device__ __forceinline__ int sweep_wave(const double* __restrict__ gram, int R
     return -1;
 }
 
+// Order of the system: R_n R_{n+1}, or I_n where that is smaller and the Gram
+// is the leverage law's.
+__device__ __forceinline__ int sweep_dim(const tr_desc& d, int n, double rank_tol) {
+    const int RR = d.R[n] * d.R[ring_next(n, d.N)];
+    return rank_tol > 0.0 && d.I[n] < RR ? d.I[n] : RR;
+}
+
+// -(gram + eta I)^{-1} into hm (RR x RR, row-major, both triangles), with
+// the fallback ladder; flag: 0 ok, 1 damped, 2 failed.  With rank_tol > 0
+// (the leverage law) there is no ladder: flag 2 means a pivot at or below
+// rank_tol * max_i gram_ii, i.e. the Gram is taken as singular.  256 threads.
+template <int NT>
+__device__ __forceinline__ void sweep_block(const tr_desc& d, const ModeSrc& ms, const double* __restrict__ gram,
+                                            const Damp& dmp, double rank_tol, double* __restrict__ hm,
+                                            int* __restrict__ flag, int32_t* status, SweepShared& sh) {
+    uint64_t t;
+    int n;
+    resolve_mode(ms, d.N, &t, &n);
+    const double damping = dmp.at(t);
+    const int RR = sweep_dim(d, n, rank_tol);
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    int ok_at;
+    switch (w) {
+        case 0: ok_at = sweep_wave<NT, 0>(gram, RR, damping, rank_tol, hm, sh); break;
+        case 1: ok_at = sweep_wave<NT, 1>(gram, RR, damping, rank_tol, hm, sh); break;
+        case 2: ok_at = sweep_wave<NT, 2>(gram, RR, damping, rank_tol, hm, sh); break;
+        default: ok_at = sweep_wave<NT, 3>(gram, RR, damping, rank_tol, hm, sh); break;
+    }
+    if (threadIdx.x == 0) {
+        const int fl = ok_at < 0 ? 2 : (ok_at > 0 ? 1 : 0);
+        *flag = fl;
+        if (fl == 1) set_status(status, TR_DEV_DAMPED);
+        if (fl == 2) set_status(status, TR_DEV_NOT_SPD);
+    }
+}
+
 }  // namespace trk
