@@ -685,8 +685,8 @@ def cpu_baseline(seconds, seed, I, R, kappa, m, alpha, threads=None):
 
 
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "hbm_traffic_scaled-illcond-n3-i400-r10.txt")
-KERNEL_SOURCE = {"k_sweep": "sweep.hip", "k_grad_mfma_f32": "grad_mfma.hip", "k_grad_mfma_f32w": "grad_mfma.hip",
-                 "k_grad_mixed": "grad_mixed.hip", "k_grad_mixed_w": "grad_mixed.hip"}
+KERNEL_SOURCE = {"k_sweep": "sweep.hpp", "k_grad_mfma_f32": "grad_mfma.hip", "k_grad_mfma_f32w": "grad_wide.hpp",
+                 "k_grad_mixed": "grad_mixed.hip", "k_grad_mixed_w": "mixed_wide.hpp"}
 
 
 def measured_traffic(kernel):
@@ -1170,8 +1170,9 @@ def main():
                   other: {"steps_per_s": round(1e3 / alt["ms_per_step"], 2), "rse_after": alt["rse_after"],
                           "gradient_us": round(alt["grad_us"], 3),
                           "inverse_us": None if alt["inv_us"] is None else round(alt["inv_us"], 3)}},
-        "timing": "value: K steps replayed from a captured HIP graph of 50 steps on one stream (eager steps "
-                  "take the Gram/inverse branch on a second one); kernel durations: HIP start/stop events recorded by every dispatch of "
+        "timing": "value: K steps replayed from a captured HIP graph of 50 steps on one stream (the inverse "
+                  "and the gradient in one launch; eager steps take the Gram/inverse branch on a second stream); "
+                  "kernel durations: HIP start/stop events recorded by every dispatch of "
                   "the inverse and gradient kernels themselves (hipExtLaunchKernelGGL) over 200 eager steps of the "
                   "same run",
         "eager_steps_per_s": round(1e3 / main["eager_ms_per_step"], 2),
