@@ -326,9 +326,10 @@ tr_status tr_run_events(const tr_problem* p, const tr_config* c, uint64_t* t_dev
  *     gradient (so the gradient runs beside the reduction and the one-
  *     workgroup inverse instead of competing with the Gram); ev_join is
  *     recorded on ``aux`` after the inverse and waited on by ``stream``
- *     before the update.  Work of one step never overlaps the next; the
- *     fork/join is graph-capturable; results are bitwise those of the
- *     one-stream run.  All four must be set together, or all NULL.
+ *     before the update.  Work of one step never overlaps the next;
+ *     results are bitwise those of the one-stream run, which is what a
+ *     stream that is being captured records.  All four must be set
+ *     together, or all NULL.
  *   ev_begin, ev_end: as in tr_run_events.
  *   ev_inv_begin, ev_inv_end: the same for the dispatch of the RR x RR
  *     inverse of step i (scaled steps). */

@@ -473,6 +473,16 @@ tr_status tr_run_ex(const tr_problem* p, const tr_config* c, uint64_t* t_dev, in
     if (steps == 0) return TR_OK;
 
     hipStream_t st = (hipStream_t)stream;
+    // A captured run stays on one stream: processes that captured and dropped many
+    // runs of two have ended with a damaged host heap, and the cause is not known.
+    bool capturing = false;
+    if (any_aux) {
+        hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+        if (hipStreamIsCapturing(st, &cs) == hipSuccess)
+            capturing = cs != hipStreamCaptureStatusNone;
+        else
+            (void)hipGetLastError();
+    }
     char* w = static_cast<char*>(ws);
     int32_t* idx = reinterpret_cast<int32_t*>(w + L.idx);
     double* pF = reinterpret_cast<double*>(w + L.pF);
@@ -528,7 +538,7 @@ tr_status tr_run_ex(const tr_problem* p, const tr_config* c, uint64_t* t_dev, in
         // ``hs`` reads the step's draws: the branch forks before them, and
         // its sample kernel draws the step's mode itself (the same counter,
         // so the same mode) and runs beside the step's own.
-        const bool fork = any_aux && c->scaled;
+        const bool fork = any_aux && c->scaled && !capturing;
         const bool fork_early = fork && c->m_H > 0 && same_shape;
         hipStream_t hs = fork ? (hipStream_t)o.aux : st;
         if (c->law == TR_LAW_OPTIMAL)

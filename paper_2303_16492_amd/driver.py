@@ -98,7 +98,8 @@ class TRSolver:
         self.config = c
         self.ws = api.workspace(api.tr_run_workspace_size(p, c), dev)
         self.rse_ws = None
-        # scaled steps: the Gram/inverse branch on a second stream (launched, not captured)
+        # scaled steps: the Gram/inverse branch on a second stream (a
+        # captured run stays on one)
         self.opts = None
         if overlap and scaled:
             self.aux = torch.cuda.Stream(device=dev)
@@ -109,13 +110,7 @@ class TRSolver:
             self.opts = o
 
     def run(self, steps: int, loss_out=None):
-        # A run that is being captured stays on one stream: processes that captured
-        # and dropped several with the second stream have ended with a damaged host
-        # heap, and the cause is not known.  The same steps, bit for bit.
-        opts = self.opts
-        if opts is not None and torch.cuda.is_current_stream_capturing():
-            opts = None
-        api.tr_run_ex(self.problem, self.config, self.t_dev, steps, loss_out, self.status, self.ws, opts)
+        api.tr_run_ex(self.problem, self.config, self.t_dev, steps, loss_out, self.status, self.ws, self.opts)
 
     def capture(self, steps: int, loss_out=None):
         """HIP graph of ``steps`` iterations (replay with graph.replay());
